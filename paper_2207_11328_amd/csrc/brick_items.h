@@ -1,0 +1,314 @@
+// Work items of the persistent brick kernels (derivatives and adjoint): the
+// claiming of bricks, the cell scans of a brick and the table of its central
+// particles, all by one wave, ahead of the workgroup.
+//
+// One resident workgroup per CU takes the bricks of the build's table one
+// after the other (heavy ones first: brick_at).  What a brick needs before
+// its pairs can be summed is a chain of dependent loads (brick id, cell
+// ranges, list counts, lists), several microseconds of latency and hardly any
+// arithmetic.  So the items are pipelined: while the workgroup sums the pairs
+// of item k, one wave walks the chain up to the cell ranges of item k + 2
+// (prepare_item), and every wave has the counts of 64 centrals of item k + 1
+// in flight with its staging loads and makes its part of that item's table of
+// centrals (TableMaker).  At the start of an item every wave then knows its
+// centrals and requests their lists together with the staging loads.
+//
+// The table leaves out the central particles with an empty list.  (Grouping
+// the others by list length, in classes of 24 entries, fills 89% of the lanes
+// of the pair loop instead of 87% on the 1.62M-particle dam break, but
+// scatters the list loads: measured slower, 155.6 against 153.3 us.)
+//
+// An item is a run of y rows of a brick.  The staging order has y outermost,
+// so the staged cells of a run (its rows and one halo row on each side) are
+// one contiguous range of staging slots, and the brick-local lists index into
+// it unchanged.  Whole bricks stage the fewest particles per central one;
+// they are cut into parts where the grid's bricks would leave CUs idle
+// (brick_parts), and where a brick holds somewhat more particles than LDS or
+// more centrals than lanes.
+#pragma once
+
+#include "sph_device.h"
+
+namespace sph {
+
+// Into how many runs of rows to cut each of n bricks for wgs workgroups: the
+// smallest of ceil(n parts / wgs) rounds times the cost of an item, about 5 us
+// of staging and latency for a whole brick, 4 for a half, 3.5 for a row, and
+// 16 us of pairs for a whole brick (in halves below).  The still-water tank of
+// 15.5k particles (27 bricks with a pair) takes 18.0 us in rows against 30.0
+// with whole bricks, the 169k-particle dam break (120) 35.8 us in halves
+// against 51.4 (cubic spline, Landrini-Morris, Morris viscosity, diffusion).
+template <int BY>
+__device__ __forceinline__ int brick_parts(int n, int wgs)
+{
+    const int c1 = ((n + wgs - 1) / wgs) * 42;
+    int best = 1, cost = c1;
+    if constexpr (BY % 2 == 0 && BY > 2) {
+        const int c2 = ((2 * n + wgs - 1) / wgs) * (8 + 32 / 2);
+        if (c2 < cost) {
+            best = 2;
+            cost = c2;
+        }
+    }
+    const int c = ((BY * n + wgs - 1) / wgs) * (7 + 32 / BY);
+    return c < cost ? BY : best;
+}
+
+// Descriptor of an item.
+struct BrickItem {
+    int item;    // index in the claim order, -1: none left
+    int brick;
+    int ya, yb;  // inner y rows
+    int yend;    // end of the part of the brick that was claimed (rows yb .. yend follow)
+    int s_lo;    // first staged slot, in the staging order of the whole brick
+    int span;    // staged particles
+    int nc;      // central particles in the rows (with an empty list included)
+    int lds;     // the run fits in LDS
+};
+
+// Bricks with more staged particles than this (the list build's LDS capacity:
+// 1.4 times the lattice density in a 3 x 4 x 3 brick) are not cut into runs
+// but read the global lists, with the bits of the gather form.
+constexpr int kRunTotal = 4800;
+
+// Entry of the table: staged slot (from s_lo) | inner row << 12 | list length << 16.
+constexpr int kCenRowShift = 12, kCenCountShift = 16;
+constexpr uint32_t kCenSlotMask = (1u << kCenRowShift) - 1u;
+
+template <int BX, int BY, int BZ>
+struct BrickScans {
+    using St = Staging<BX, BY, BZ>;
+    static constexpr int NR = BY * BZ;  // inner rows (x-consecutive cells: one particle range each)
+    static_assert(NR <= 16, "a row id fits its field of a table entry");
+    int base[St::S + 1];  // staged slot of each staged cell
+    int delta[St::S];     // slot minus particle index
+    int row_first[16];      // centrals before each inner row of the item (past the last row: all ones)
+    int row_index[16];      // particle index of its first central
+    int row_shift[16];      // particle index minus staged slot (from s_lo)
+    BrickItem d;
+};
+
+// Lane k's value of an inclusive sum over the first 2^STEPS lanes.
+template <int STEPS>
+__device__ __forceinline__ int lanes_scan(int v, int lane)
+{
+#pragma unroll
+    for (int o = 1; o < (1 << STEPS); o <<= 1) {
+        const int t = __shfl_up(v, o);
+        if (lane >= o) v += t;
+    }
+    return v;
+}
+
+// The next item into Q, by one wave: the rows left of item prev, else the next
+// part of a brick from the counter.  CAP: staged particles that fit in LDS;
+// NT: centrals that fit in the table.
+template <int BX, int BY, int BZ, int NT, int CAP>
+__device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const BrickItem &prev, bool first, int lane,
+                                             const int32_t *__restrict__ table, int cap_ids,
+                                             int32_t *__restrict__ next, const int32_t *__restrict__ cell_start,
+                                             const int32_t *__restrict__ cell_end, const BrickGrid &G)
+{
+    using St = Staging<BX, BY, BZ>;
+    constexpr int SX = St::SX, SZ = St::SZ, S = St::S, ROW = SX * SZ, NR = BY * BZ;
+    static_assert(CAP <= (int)kCenSlotMask + 1, "a staged slot fits its field of a table entry");
+    const int pb = __builtin_amdgcn_readfirstlane(prev.yb), pe = __builtin_amdgcn_readfirstlane(prev.yend);
+    int item, b, ya, yend;
+    if (pb < pe) {
+        item = __builtin_amdgcn_readfirstlane(prev.item);
+        b = __builtin_amdgcn_readfirstlane(prev.brick);
+        ya = pb;
+        yend = pe;
+    } else {
+        // the first item of a workgroup is its index, the others come from the
+        // counter (zeroed before the launch)
+        const int heavy = table[0], n_listed = heavy + table[cap_ids + 1];
+        const int guess = first ? table[1 + min((int)blockIdx.x, cap_ids - 1)] : 0;  // (sent for with the counts)
+        const int parts = brick_parts<BY>(n_listed, gridDim.x), items = n_listed * parts;
+        item = items;
+        if (first) {
+            item = blockIdx.x;
+        } else if (__builtin_amdgcn_readfirstlane(prev.item) >= 0 && items > (int)gridDim.x) {
+            int k = 0;
+            if (lane == 0) k = atomicAdd(next, 1);
+            item = __builtin_amdgcn_readfirstlane(k) + gridDim.x;
+        }
+        if (item >= items) {
+            if (lane == 0) {
+                Q.d = BrickItem{};
+                Q.d.item = -1;
+            }
+            return;
+        }
+        b = first && parts == 1 && item < heavy ? guess : brick_at(table, cap_ids, item / parts);
+        const int rows = BY / parts;
+        ya = item % parts * rows;
+        yend = ya + rows;
+    }
+    const int cx0 = (b % G.nbx) * BX, cy0 = ((b / G.nbx) % G.nby) * BY, cz0 = (b / (G.nbx * G.nby)) * BZ;
+    // ranges of the staged cells (empty outside a non-periodic grid edge) and
+    // their slots in the staging order of the whole brick
+    constexpr int NCH = (S + kWave - 1) / kWave;
+    int st[NCH], ct[NCH], total = 0;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const int t = c * kWave + lane;
+        st[c] = 0;
+        ct[c] = 0;
+        if (t < S) {
+            int gx = cx0 - 1 + St::sx_of(t), gy = cy0 - 1 + St::sy_of(t), gz = cz0 - 1 + St::sz_of(t);
+            const bool ok = wrap_axis(gx, G.nx, G.periodic & 1u) && wrap_axis(gy, G.ny, (G.periodic >> 1) & 1u) &&
+                            wrap_axis(gz, G.nz, (G.periodic >> 2) & 1u);
+            if (ok) {
+                const int lin = gx + G.nx * (gy + G.ny * gz);
+                st[c] = cell_start[lin];
+                ct[c] = cell_end[lin] - st[c];
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const int t = c * kWave + lane, inc = lanes_scan<6>(ct[c], lane), ex = total + inc - ct[c];
+        if (t < S) {
+            Q.base[t] = ex;
+            Q.delta[t] = ex - st[c];
+        }
+        total += __builtin_amdgcn_readlane(inc, kWave - 1);
+    }
+    if (lane == 0) Q.base[S] = total;
+    // the inner rows, one per lane (inner cells past the grid edge hold no
+    // centrals: on a periodic axis the staged copy is the wrapped cell, owned
+    // by another brick)
+    const int iy = lane / BZ, iz = lane % BZ;
+    const bool row = lane < NR && cy0 + iy < G.ny && cz0 + iz < G.nz;
+    const int t0 = St::cell(1, row ? iy + 1 : 1, row ? iz + 1 : 1), bxn = min(BX, G.nx - cx0);
+    const int slot0 = Q.base[t0], all = row ? Q.base[t0 + bxn] - slot0 : 0, dl = Q.delta[t0];
+    // the longest run of rows that fits (of a brick that takes runs at all)
+    const int s_lo = __builtin_amdgcn_readfirstlane(Q.base[ya * ROW]);
+    int yb = yend, span = 0, nc = 0;
+    for (;; --yb) {
+        span = __builtin_amdgcn_readfirstlane(Q.base[(yb + 2) * ROW]) - s_lo;
+        nc = lanes_scan<4>(iy >= ya && iy < yb ? all : 0, lane);
+        nc = __builtin_amdgcn_readlane(nc, 15);
+        if (yb == ya + 1 || total > kRunTotal || (span <= CAP && nc <= NT)) break;
+    }
+    const bool lds = span <= CAP && nc <= NT && total <= kRunTotal;
+    const int cnt = iy >= ya && iy < yb ? all : 0;
+    const int inc = lanes_scan<4>(cnt, lane);
+    if (lane < 16) Q.row_first[lane] = lane < NR ? inc - cnt : INT32_MAX;
+    if (lane < NR) {
+        Q.row_index[lane] = slot0 - dl;
+        Q.row_shift[lane] = s_lo - dl;
+    }
+    if (lane == 0) {
+        Q.d.item = item;
+        Q.d.brick = b;
+        Q.d.ya = ya;
+        Q.d.yb = yb;
+        Q.d.yend = yend;
+        Q.d.s_lo = s_lo;
+        Q.d.span = span;
+        Q.d.nc = nc;
+        Q.d.lds = lds ? 1 : 0;
+    }
+}
+
+// Inner row of central q of the item (sorted order): the last one whose first
+// central is q or before (the others of the same first central are empty).
+template <int BX, int BY, int BZ>
+__device__ __forceinline__ int central_row(const BrickScans<BX, BY, BZ> &Q, int q)
+{
+    int r = 0;
+#pragma unroll
+    for (int step = 8; step; step >>= 1) r = Q.row_first[r + step] <= q ? r + step : r;
+    return r;
+}
+
+// Particle index of central q, for items that do not fit in LDS.
+template <int BX, int BY, int BZ>
+__device__ __forceinline__ int item_central(const BrickScans<BX, BY, BZ> &Q, int q)
+{
+    const int r = central_row(Q, q);
+    return Q.row_index[r] + (q - Q.row_first[r]);
+}
+
+// p[i] by a 32-bit byte offset from a scalar base (per-particle arrays have at
+// most 2^26 entries): one address register and no 64-bit arithmetic.
+template <typename T>
+__device__ __forceinline__ T load_at(const T *__restrict__ p, int i)
+{
+    return *(const T *)((const char *)p + (uint32_t)i * (uint32_t)sizeof(T));
+}
+template <typename T>
+__device__ __forceinline__ void store_at(T *__restrict__ p, int i, const T &v)
+{
+    *(T *)((char *)p + (uint32_t)i * (uint32_t)sizeof(T)) = v;
+}
+
+// The table of centrals of an item, made by all waves of the workgroup, 64
+// centrals each: request() sends for the list counts, tally() leaves how many
+// of the wave's centrals have a list, and after a barrier place() writes the
+// entries, in sorted order.
+template <int NT>
+struct CentralTable {
+    uint32_t cen[NT];
+    int tally[NT / kWave];
+    int used;  // entries: centrals with a list
+};
+
+template <int BX, int BY, int BZ, int NT>
+struct TableMaker {
+    uint32_t entry;  // slot and row
+    uint32_t cw;     // list count
+    int len;
+
+    __device__ __forceinline__ void request(const BrickScans<BX, BY, BZ> &Q, int wave, int lane,
+                                            const uint32_t *__restrict__ count)
+    {
+        const int nc = __builtin_amdgcn_readfirstlane(Q.d.nc);
+        entry = 0u;
+        cw = 0u;
+        if (__builtin_amdgcn_readfirstlane(Q.d.item) < 0 || !__builtin_amdgcn_readfirstlane(Q.d.lds) ||
+            wave * kWave >= nc)
+            return;  // uniform
+        const int q = min(wave * kWave + lane, nc - 1);
+        const int r = central_row(Q, q);
+        const int i = Q.row_index[r] + (q - Q.row_first[r]);
+        entry = (uint32_t)(i - Q.row_shift[r]) | (uint32_t)r << kCenRowShift;
+        cw = load_at(count, i);
+        if (wave * kWave + lane >= nc) cw = 0u;
+    }
+
+    // M: list slots per particle
+    __device__ __forceinline__ void tally(CentralTable<NT> &T, int wave, int lane, int M)
+    {
+        // (clamped: a stale or foreign list gives wrong numbers but never an
+        // access outside the lists)
+        const int nf = min((int)(cw & 0xFFFFu), M);
+        len = min(nf + (int)(cw >> 16), M);
+        const int some = (int)__popcll(__builtin_amdgcn_ballot_w64(len > 0));
+        if (lane == 0) T.tally[wave] = some;
+    }
+
+    __device__ __forceinline__ void place(CentralTable<NT> &T, int wave, int lane)
+    {
+        constexpr int NW = NT / kWave;
+        const int inc = lanes_scan<4>(lane < NW ? T.tally[min(lane, NW - 1)] : 0, lane);
+        if (wave == 0 && lane == NW - 1) T.used = inc;
+        const int before = wave == 0 ? 0 : __builtin_amdgcn_readlane(inc, wave - 1);
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(len > 0);
+        const int p = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)before));
+        if (len > 0) T.cen[p] = entry | (uint32_t)len << kCenCountShift;
+    }
+};
+
+// Workgroups of a persistent brick kernel over a grid of `blocks` bricks of BY
+// rows: one per CU (at most one item per row of a brick).
+inline unsigned brick_workgroups(unsigned blocks, unsigned BY)
+{
+    const unsigned cus = (unsigned)sph_device_cus();
+    return blocks < (cus + BY - 1) / BY ? blocks * BY : cus;
+}
+
+}  // namespace sph

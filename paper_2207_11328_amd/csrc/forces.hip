@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kThreads) void k_eos(int n, const float4 *__restric
     const int i = blockIdx.x * kThreads + threadIdx.x;
     if (i >= n) return;
     const float alpha_h = C.cell_alpha && cell[i] >= 0 ? alpha_h_of(i, cell, C) : C.alpha_h;
-    aux[i] = eos_terms(vel[i].w, alpha_h, C);
+    aux[i] = C.landrini ? eos_terms<true>(vel[i].w, alpha_h, C) : eos_terms<false>(vel[i].w, alpha_h, C);
 }
 
 __global__ __launch_bounds__(kThreads) void k_count_interactions(int n, const float4 *__restrict__ pos,
@@ -107,6 +107,8 @@ bool make_const(const sph_grid *g, const sph_params *p, int max_neibs, ForceCons
     C.inv_h = (float)(1.0 / h);
     C.inv_h2 = (float)(1.0 / (h * h));
     C.fcoeff = (float)kernel_coeff(p->kernel, h);
+    C.fcoeff_brick = p->kernel == SPH_KERNEL_WENDLAND ? 8.0f * C.fcoeff : C.fcoeff;
+    C.neg_inv_2h = -0.5f * C.inv_h;
     C.alpha_h = (float)((double)p->alpha * h);
     C.eps_h2 = (float)((double)p->eps_visc * h * h);
     C.four_nu = (float)(4.0 * (double)p->nu);

@@ -13,6 +13,9 @@ struct ForceConst {
     float lim2;       // fl32(2h)^2: interaction iff r2 < lim2
     float inv_h, inv_h2;
     float fcoeff;     // kernel coefficient c of F = c f(q)
+    // brick form: the coefficient staged with the masses (8 c for the Wendland
+    // kernel, F = -8 c t^3 with t = 1 - r/(2h)) and -1/(2h)
+    float fcoeff_brick, neg_inv_2h;
     float alpha_h;    // alpha * h
     float eps_h2;     // eps * h^2
     float four_nu;    // 4 nu (Morris)
@@ -31,6 +34,7 @@ struct ForceConst {
 // terms use it: (P/rho^2, or P for the Landrini-Morris formulation, and
 // alpha h c / 2 with c = c0 (1 + d)^3).  One definition for every kernel that
 // needs it, so both derivative forms see bit-identical values.
+template <bool LANDRINI>
 __device__ __forceinline__ float2 eos_terms(float rho, float alpha_h, const ForceConst &C)
 {
     const float d = (rho - C.rho0) * C.inv_rho0;
@@ -43,7 +47,7 @@ __device__ __forceinline__ float2 eos_terms(float rho, float alpha_h, const Forc
     const float P = C.B * d * poly;
     const float inv_rho = __builtin_amdgcn_rcpf(rho);  // (hardware reciprocal, 1 ulp; no division sequence)
     const float a = 1.0f + d;
-    return make_float2(C.landrini ? P : P * inv_rho * inv_rho, 0.5f * alpha_h * (C.c0 * a * a * a));
+    return make_float2(LANDRINI ? P : P * inv_rho * inv_rho, 0.5f * alpha_h * (C.c0 * a * a * a));
 }
 
 // alpha h of particle j: the coefficient of its cell when a per-cell table is

@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include "brick_items.h"
 #include "forces_common.h"
 
 #ifndef SPH_KERNEL_KIND
@@ -41,31 +42,43 @@ struct PairAcc {
 };
 
 // One pair (i, j) of the derivative sums, branch-free; contributes only when
-// `valid` (slot inside i's list) and r < 2h.  mcj = m_j times the kernel
-// coefficient c of F = c f(q); ai.y, aj.y = alpha h c / 2 (so the mean of
-// the sound speeds and the min(u.x, 0) of Monaghan's term come out of one
-// sum and one subtraction: (ai.y + aj.y)(w - |w|) = alpha h (c_i + c_j) min(w, 0));
+// it is inside i's list and r < 2h.  mcj = m_j times the kernel coefficient c
+// of F = c f(q); ai.y, aj.y = alpha h c / 2 (so the mean of the sound speeds
+// and the min(u.x, 0) of Monaghan's term come out of one sum and one
+// subtraction: (ai.y + aj.y)(w - |w|) = alpha h (c_i + c_j) min(w, 0));
 // ai.x, aj.x = P/rho^2 (golden rule) or P (Landrini-Morris).
 // pair_fluid: both particles are fluid (density diffusion applies).
+// in: 1 inside the list, 0 past its end.
 // LDS: the form of the LDS brick loop, where a pair outside the support or
 // past the list has m_j F set to zero and every term is computed (no branch,
 // fewer registers); the global-gather loop keeps per-term selects, which the
 // compiler turns into a branch that skips the term arithmetic and keeps more
 // gathers in flight.  Both give the same values (the zeroed terms add +-0).
+// For the Wendland kernel the mask costs one instruction instead of four: F
+// = -8 c t^3 with t = 1 - q/2, and the clamp of t to [0, 1] (a modifier of
+// the multiply-add) is the support test; `in` takes the place of the 1.  A
+// pair at r = 2h within rounding then weighs t^3 ~ 1e-21 on either side.
 template <int MODEL, bool LDS>
 __device__ __forceinline__ void pair_core(PairAcc &A, float xx, float xy, float xz, const float4 &vi,
                                           const float2 &ai, float mcj, const float4 &vj, const float2 &aj,
-                                          bool valid, bool pair_fluid, const ForceConst &C)
+                                          float in, bool pair_fluid, const ForceConst &C)
 {
     constexpr int KER = model_kernel(MODEL);
     const float r2 = fmaf(xx, xx, fmaf(xy, xy, xz * xz));
-    bool inter = valid && (r2 < C.lim2);
-    if constexpr (KER == SPH_KERNEL_QUADRATIC) inter = inter && r2 > 0.0f;  // its F is unbounded at r = 0
     const float r = __builtin_amdgcn_sqrtf(r2);
     // m_j F_ij; in the LDS form zero for a pair outside the support or past
     // the list (every term below is a finite factor times mF)
-    const float mF0 = kernel_mF<KER>(mcj, r, r2, C.inv_h, C.inv_h2);
-    const float mF = LDS ? (inter ? mF0 : 0.0f) : mF0;
+    bool inter = true;
+    float mF;
+    if constexpr (LDS && KER == SPH_KERNEL_WENDLAND) {
+        const float t = __builtin_amdgcn_fmed3f(fmaf(r, C.neg_inv_2h, in), 0.0f, 1.0f);
+        mF = -(t * t) * (t * mcj);  // (mcj holds 8 c m_j: fcoeff_brick)
+    } else {
+        inter = in > 0.0f && r2 < C.lim2;
+        if constexpr (KER == SPH_KERNEL_QUADRATIC) inter = inter && r2 > 0.0f;  // its F is unbounded at r = 0
+        const float mF0 = kernel_mF<KER>(mcj, r, r2, C.inv_h, C.inv_h2);
+        mF = LDS ? (inter ? mF0 : 0.0f) : mF0;
+    }
     const float ux = vi.x - vj.x;
     const float uy = vi.y - vj.y;
     const float uz = vi.z - vj.z;
@@ -118,7 +131,7 @@ __device__ __forceinline__ void pair_terms(PairAcc &A, uint32_t e, const float4 
     const float xx = fmaf(entry_k(e, 0), C.csx, pi.x - pj.x);
     const float xy = fmaf(entry_k(e, 1), C.csy, pi.y - pj.y);
     const float xz = fmaf(entry_k(e, 2), C.csz, pi.z - pj.z);
-    pair_core<MODEL, false>(A, xx, xy, xz, vi, ai, pj.w * C.fcoeff, vj, aj, valid, pair_fluid, C);
+    pair_core<MODEL, false>(A, xx, xy, xz, vi, ai, pj.w * C.fcoeff, vj, aj, valid ? 1.0f : 0.0f, pair_fluid, C);
 }
 
 // Pairs of one lane's list gathered from global memory, in list order.
@@ -141,7 +154,7 @@ __device__ __forceinline__ void gather_pairs(PairAcc &A, const uint32_t *tile, i
     float4 P[D], V[D];
     float2 X[D];
     auto terms = [&](uint32_t j, const float4 &v) {
-        return aux ? aux[j] : eos_terms(v.w, alpha_h_of((int)j, cell, C), C);
+        return aux ? aux[j] : eos_terms<(MODEL & kLandrini) != 0>(v.w, alpha_h_of((int)j, cell, C), C);
     };
 #pragma unroll
     for (int s = 0; s < D; ++s) {
@@ -224,8 +237,8 @@ __global__ __launch_bounds__(kThreads) void k_forces(int n, const float4 *__rest
 // derivatives).  A workgroup owns a brick of cells; it first copies
 // the particles of the brick and of its one-cell halo (every possible
 // neighbour of its particles) from HBM/L2 into LDS with coalesced loads, one
-// contiguous cell range after another, then each lane walks the list of one
-// central particle of the brick and reads the neighbour data from LDS.  The
+// contiguous cell range after another, then four lanes share the list of one
+// central particle of the brick and read the neighbour data from LDS.  The
 // 64 lanes of a wave read neighbours scattered over dozens of cache lines,
 // which the global-gather kernel pays in L1/L2 request throughput.
 //
@@ -243,57 +256,272 @@ __global__ __launch_bounds__(kThreads) void k_forces(int n, const float4 *__rest
 // the other.  A brick whose halo does not fit in LDS reads the global
 // lists and the global state with the arithmetic of k_forces.
 
-// Pairs of one central's brick-local list, read from LDS, shared by two
-// lanes: lane h of the pair takes the groups of 8 entries h, h + 2, h + 4, ...
-// The list arrives in 16-byte groups (one load per 8 pairs), requested two
-// iterations ahead; the staged data of pair k + R is requested while pair k
-// is computed (a ring of R slots, R dividing 8 so the ring phase is the same
-// in every group).
+// Pairs of one central's brick-local list, read from LDS, shared by kLanes
+// lanes: lane h takes the groups of 8 entries h, h + kLanes, h + 2 kLanes, ...
+// A group is one 16-byte load for 8 pairs; the staged data of pair k + R is
+// requested while pair k is computed (a ring of R slots, R dividing 8 so the
+// ring phase is the same in every group).  Two lanes run the loop as fast, but
+// their work items are twice as long, and the waves of a brick then wait 5.1
+// instead of 3.3 us for the last one (1.62M-particle dam break).
+//
+// What bounds the loop is VALU issue: 36 instructions per pair, the method's
+// own 31 (two of them at half rate) and 5 for slot, address and list end; LDS
+// is busy 60% of the time, and its bank conflicts (half of its accesses'
+// cycles) cost nothing measurable.
 #ifndef SPH_BRICK_RING
 #define SPH_BRICK_RING 2
 #endif
 constexpr int kRing = SPH_BRICK_RING;
 static_assert(kBrickGroup % kRing == 0, "ring must divide the group");
 
-template <int MODEL, int NT>
-__device__ __forceinline__ void brick_pairs_lds(PairAcc &A, const uint4 *lg, int h, int nt, int ntw, int total,
-                                                const float4 *__restrict__ sP, const float4 *__restrict__ sV,
-                                                const float2 *__restrict__ sA, const float4 &pi, const float4 &vi,
-                                                const float2 &ai, const ForceConst &C)
+// The staged arrays of a brick.  P and V are read with one address register
+// (V's distance fits the 16-bit offset of an LDS read), A with a second one.
+template <int CAP>
+struct Staged {
+    float4 P[CAP];  // brick-relative offset, mass x kernel coefficient
+    float4 V[CAP];  // velocity, density
+    float2 A[CAP];  // equation-of-state terms
+};
+
+// LDS by address (a 32-bit offset in the workgroup's LDS).
+typedef float vf4 __attribute__((ext_vector_type(4)));
+typedef float vf2 __attribute__((ext_vector_type(2)));
+template <typename T>
+using Lds = __attribute__((address_space(3))) T;
+template <typename T>
+__device__ __forceinline__ uint32_t lds_address(const T *p)
 {
-    constexpr int GS = kWave;  // uint4 stride between groups of one central
-    const int lastg = max(nt - 1, 0) / kBrickGroup;
-    const uint32_t smax = (uint32_t)(total - 1);
+    return (uint32_t)(uintptr_t)(Lds<const T> *)p;
+}
+__device__ __forceinline__ float4 lds_float4(uint32_t a, int index)
+{
+    const vf4 v = ((Lds<const vf4> *)(uintptr_t)a)[index];
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float2 lds_float2(uint32_t a)
+{
+    const vf2 v = *(Lds<const vf2> *)(uintptr_t)a;
+    return make_float2(v.x, v.y);
+}
+
+// base + scale x (the 16-bit slot in half `hi` of w): one instruction, the
+// unpacking included.
+__device__ __forceinline__ uint32_t slot_address(uint32_t w, int hi, int scale, uint32_t base)
+{
+    uint32_t a;
+    if (scale == 16) {
+        if (hi) asm("v_mad_u32_u16 %0, %1, 16, %2 op_sel:[1,0,0,0]" : "=v"(a) : "v"(w), "s"(base));
+        else asm("v_mad_u32_u16 %0, %1, 16, %2" : "=v"(a) : "v"(w), "s"(base));
+    } else {
+        if (hi) asm("v_mad_u32_u16 %0, %1, 8, %2 op_sel:[1,0,0,0]" : "=v"(a) : "v"(w), "s"(base));
+        else asm("v_mad_u32_u16 %0, %1, 8, %2" : "=v"(a) : "v"(w), "s"(base));
+    }
+    return a;
+}
+
+// Lanes per central, and the entries one of them takes at a time.
+constexpr int kLanes = 4, kEntries = kBrickGroup;
+typedef uint32_t Entries __attribute__((ext_vector_type(4)));
+// group e of a brick-local list, lg its group 0
+__device__ __forceinline__ Entries list_entries(const uint4 *lg, int e)
+{
+    return load_at((const Entries *)lg, e * kWave);
+}
+// Two slots of a list relative to the first staged one, kept inside the staged
+// range (a stale list gives wrong numbers but no access past it).
+__device__ __forceinline__ uint32_t staged_slots(uint32_t w, uint32_t lo2, uint32_t max2)
+{
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    const us2 d = __builtin_elementwise_sub_sat(__builtin_bit_cast(us2, w), __builtin_bit_cast(us2, lo2));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(d, __builtin_bit_cast(us2, max2)));
+}
+
+// Lane h of a central's kLanes lanes takes the runs of kEntries entries h, h +
+// kLanes, ... of its list; ea and eb are its first two.  The two take turns:
+// each is loaded again as soon as its last slot is read, so that no loaded
+// value is copied (a copy would wait for it) and a run has eight pairs' time
+// to arrive.
+template <int MODEL, int CAP>
+__device__ __forceinline__ void brick_pairs_lds(PairAcc &A, const uint4 *lg, Entries ea, Entries eb, int h, int nt,
+                                                uint32_t lo2, uint32_t max2, const Staged<CAP> &L, const float4 &pi,
+                                                const float4 &vi, const float2 &ai, const ForceConst &C)
+{
+    const int runs = (nt + kEntries - 1) / kEntries;
+    const uint32_t baseP = lds_address(L.P), baseA = lds_address(L.A);
     float4 P[kRing], V[kRing];
     float2 X[kRing];
-    auto fetch = [&](uint32_t slot, float4 &p, float4 &v, float2 &x) {
-        const uint32_t sl = min(slot, smax);  // a stale list stays inside the staged range
-        p = sP[sl];
-        v = sV[sl];
-        x = sA[sl];
+    auto fetch = [&](const Entries &e, int s) {
+        const uint32_t w = staged_slots(e[s >> 1], lo2, max2), a = slot_address(w, s & 1, 16, baseP);
+        const int r = s % kRing;
+        P[r] = lds_float4(a, 0);
+        V[r] = lds_float4(a, CAP);
+        X[r] = lds_float2(slot_address(w, s & 1, 8, baseA));
     };
-    uint4 gc = lg[min(h, lastg) * GS];
-    uint4 gn = lg[min(h + 2, lastg) * GS];
 #pragma unroll
-    for (int r = 0; r < kRing; ++r) fetch(group_entry(gc, r), P[r], V[r], X[r]);
-    for (int k = 0; k < ntw; k += 2 * kBrickGroup) {
-        const int g0 = k / kBrickGroup + h;  // this lane's group
-        const uint4 gnn = lg[min(g0 + 4, lastg) * GS];
-        const int rem = nt - g0 * kBrickGroup;  // entries of the list from this group on
+    for (int s = 0; s < kRing; ++s) fetch(ea, s);
+    float rem = (float)(nt - h * kEntries);  // entries of the list from this lane's run on
+    int g = h;
+    auto run = [&](Entries &e, const Entries &f) {
 #pragma unroll
-        for (int s = 0; s < kBrickGroup; ++s) {
-            const int r = s % kRing;
+        for (int s = 0; s < kEntries; ++s) {
+            const int r = s % kRing, s2 = s + kRing;
             // staged w = +-(m_j x kernel coefficient), negative for boundary particles
             pair_core<MODEL, true>(A, pi.x - P[r].x, pi.y - P[r].y, pi.z - P[r].z, vi, ai, fabsf(P[r].w), V[r], X[r],
-                            s < rem, pi.w > 0.0f && P[r].w > 0.0f, C);
-            const int s2 = s + kRing;
-            fetch(s2 < kBrickGroup ? group_entry(gc, s2) : group_entry(gn, s2 - kBrickGroup), P[r], V[r], X[r]);
+                                   __builtin_amdgcn_fmed3f(rem - (float)s, 0.0f, 1.0f), pi.w > 0.0f && P[r].w > 0.0f,
+                                   C);
+            if (s2 < kEntries)
+                fetch(e, s2);
+            else
+                fetch(f, s2 - kEntries);
+            if (s2 == kEntries - 1) e = list_entries(lg, min(g + 2 * kLanes, runs - 1));
         }
-        gc = gn;
-        gn = gnn;
+        g += kLanes;
+        rem -= (float)(kLanes * kEntries);
+    };
+    while (g < runs) {
+        run(ea, eb);
+        if (g >= runs) break;
+        run(eb, ea);
     }
 }
 
+// The sum of a value over the lanes of a central, in all of them.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lanes_sum(float v)
+{
+    v += dpp<0xB1>(v);  // quad lanes 1, 0, 3, 2
+    v += dpp<0x4E>(v);  // quad lanes 2, 3, 0, 1
+    return v;
+}
+
+// One particle of a staged row on its way to LDS.
+struct Chunk {
+    float4 p, v;
+    float ah;  // alpha h
+    int cx;    // cell along x from the brick's centre cell
+    uint32_t info;
+};
+
+// Staged rows of cells of an item (SX x-consecutive cells: one contiguous LDS
+// range and, away from a periodic seam, one contiguous global range): wave w
+// takes rows w and w + NW.
+template <int BX, int BY, int BZ, int NW>
+struct StagedRows {
+    using St = Staging<BX, BY, BZ>;
+    static constexpr int SX = St::SX, SZ = St::SZ, ROWS = 2;
+    static_assert(St::SY * SZ <= ROWS * NW, "two rows per wave hold every row");
+    int row[ROWS], slot[ROWS], len[ROWS];  // row, its first slot (from s_lo), its particles
+
+    __device__ __forceinline__ void locate(const BrickScans<BX, BY, BZ> &B, int wave)
+    {
+        const bool staged = __builtin_amdgcn_readfirstlane(B.d.item) >= 0 && __builtin_amdgcn_readfirstlane(B.d.lds);
+        const int R0 = __builtin_amdgcn_readfirstlane(B.d.ya * SZ), R1 = __builtin_amdgcn_readfirstlane((B.d.yb + 2) * SZ);
+#pragma unroll
+        for (int k = 0; k < ROWS; ++k) {
+            row[k] = min(R0 + wave + k * NW, R1 - 1);
+            const int b0 = __builtin_amdgcn_readfirstlane(B.base[row[k] * SX]);
+            slot[k] = b0 - __builtin_amdgcn_readfirstlane(B.d.s_lo);
+            const int l = __builtin_amdgcn_readfirstlane(B.base[row[k] * SX + SX]) - b0;
+            len[k] = staged && R0 + wave + k * NW < R1 ? l : 0;
+        }
+    }
+    // particle t of row k (t past its end: particle 0; loads stay
+    // unconditional, so the chunks stay in registers)
+    template <int MODEL>
+    __device__ __forceinline__ Chunk load(const BrickScans<BX, BY, BZ> &B, int k, int t, const float4 *__restrict__ pos,
+                                          const float4 *__restrict__ vel, const int32_t *__restrict__ cell,
+                                          const uint32_t *__restrict__ info, const ForceConst &C) const
+    {
+        const int *base = B.base + row[k] * SX, *delta = B.delta + row[k] * SX;
+        const int s = base[0] + t;
+        int c = -2, d = delta[0];
+#pragma unroll
+        for (int m = 1; m < SX; ++m) {
+            const bool past = s >= base[m];
+            c += past ? 1 : 0;
+            d = past ? delta[m] : d;
+        }
+        const int j = t < len[k] ? s - d : 0;
+        Chunk q;
+        q.p = load_at(pos, j);
+        q.v = load_at(vel, j);
+        q.ah = alpha_h_of(j, cell, C);
+        q.cx = c;
+        q.info = (MODEL & kDiffusion) ? load_at(info, j) : 0u;
+        return q;
+    }
+    template <int MODEL, int CAP>
+    __device__ __forceinline__ void store(Staged<CAP> &L, const Chunk &q, int k, int t, const ForceConst &C) const
+    {
+        if (t >= len[k]) return;
+        const int l = slot[k] + t;
+        // positions relative to the centre cell of the whole brick
+        const float sx = (float)q.cx, sy = (float)(row[k] / SZ - 2), sz = (float)(row[k] % SZ - 2);
+        // w = m x kernel coefficient, negated for boundary particles when the
+        // density diffusion needs the type
+        const float mf = q.p.w * C.fcoeff_brick;
+        L.P[l] = make_float4(fmaf(sx, C.csx, q.p.x), fmaf(sy, C.csy, q.p.y), fmaf(sz, C.csz, q.p.z),
+                             (MODEL & kDiffusion) && ptype(q.info) == kBoundary ? -mf : mf);
+        L.V[l] = q.v;
+        // equation-of-state terms from the staged density
+        L.A[l] = eos_terms<(MODEL & kLandrini) != 0>(q.v.w, q.ah, C);
+    }
+};
+
+// The brick-local list of particle i (brick_entry(i, 0, groups)): group g at
+// [g * kWave].
+__device__ __forceinline__ const uint4 *list_groups(const uint16_t *__restrict__ neibs_brick, int i, uint32_t groups)
+{
+    const uint32_t u = (uint32_t)i;
+    return (const uint4 *)((const char *)neibs_brick + (uint64_t)(u / kWave) * (groups * (kWave * 16u)) +
+                           (u % kWave) * 16u);
+}
+
+// Particles with an empty list (in no table of centrals; also those the build
+// dropped) get zero derivatives, by the first T lanes of every workgroup
+// while the last wave walks the chain of loads of the first item: no other
+// lane writes them.
+template <int T>
+__device__ __forceinline__ void empty_lists(int n, const uint32_t *__restrict__ count, const float4 *__restrict__ vel,
+                                            float4 *__restrict__ out, float tau, const Corrector &K)
+{
+    constexpr int U = 4;  // counts in flight per lane
+    const int stride = gridDim.x * T;
+    for (int i0 = blockIdx.x * T + threadIdx.x; i0 < n; i0 += U * stride) {
+        uint32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = count[min(i0 + u * stride, n - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * stride;
+            if (i < n && c[u] == 0u) {
+                const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (out) out[i] = z;
+                if (K.d_dt && K.cell[i] >= 0) corrector_at(i, z, vel[i], tau, K);
+            }
+        }
+    }
+}
+
+// One resident workgroup per CU (its LDS is the CU's) takes items, bricks or
+// runs of their rows, one after the other (brick_items.h).  In the time of
+// item k:
+//   * the staging loads of item k, requested before its turn, are turned into
+//     staged particles; the first lists of its centrals and the list counts of
+//     item k + 1 are on their way;
+//   * after a barrier, the pairs: a wave takes 16 centrals at a time, wave w
+//     group w first, then the next unclaimed group (LDS counter) as it finishes
+//     one; the lists of a group are requested one group ahead.  One wave first
+//     prepares item k + 2;
+//   * a wave without a group writes its part of the table of item k + 1 and
+//     requests its share of that item's particles.
+// Per item on the 1.62M-particle dam break (full bricks, 6.1 items per CU,
+// times of the mean wave): 1.9 us to stage, 0.8 us at the barrier, 13.7 us of
+// pairs, 1.0 us for the next item, 3.3 us waiting for the last wave.
 template <int MODEL, int BX, int BY, int BZ, int NT, int CAP>
 __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__restrict__ pos,
                                                      const float4 *__restrict__ vel,
@@ -310,382 +538,218 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
                                                      Corrector K)
 {
     using St = Staging<BX, BY, BZ>;
-    constexpr int SX = BX + 2, SY = BY + 2, SZ = BZ + 2;
-    constexpr int S = SX * SY * SZ;  // staged cells
-    constexpr int NI = BX * BY * BZ; // inner cells
-    static_assert(S <= NT && NI <= NT, "one thread per cell");
-    __shared__ float4 sP[CAP];  // brick-relative offset, mass x kernel coefficient
-    __shared__ float4 sV[CAP];
-    __shared__ float2 sA[CAP];
-    // cell scans of the brick (two buffers: the next brick's are computed
-    // ahead into the other one, see below)
-    __shared__ int cBaseB[2][S + 1];
-    __shared__ int cDeltaB[2][S];
-    __shared__ int iBaseB[2][NI + 1];
-    __shared__ int iStartB[2][NI];
-    __shared__ int wsum[NT / kWave];
-    __shared__ int sNext;
-    __shared__ int sGroup;  // groups of centrals claimed in the brick, past the first NT / kWave
-    __shared__ int sPre[4]; // scan ahead: claimed, next brick's list index, total, centrals
+    constexpr int NI = St::NI, NW = NT / kWave;
+    __shared__ Staged<CAP> L;
+    __shared__ BrickScans<BX, BY, BZ> Q[3];  // this item's, the next one's and the one after
+    __shared__ CentralTable<NT> T[2];        // this item's and the next one's
+    __shared__ int sGroup;  // groups of centrals claimed in the item
     // (corrector with a step per scene) each inner cell's scene (-1: none) and step
     __shared__ int sSc[NI];
     __shared__ float sTau[NI];
-    static_assert(NI <= kWave, "one lane per inner cell in the scan ahead");
 
-    // One resident workgroup per CU takes the bricks with a pair one at a time
-    // from the counter `next`, heavy ones first (brick_at order; the build's
-    // table): no workgroup is launched for an empty brick, the bricks'
-    // different costs even out across CUs, and the cheap bricks come last,
-    // where they fill the gaps.
-    const int n_listed = table[0] + table[cap_ids + 1];
+    const int M = C.max_neibs;
     const float tau = K.d_dt && !K.cell_scene ? (float)*K.d_dt : 0.0f;  // (the corrector's step)
     corrector_clock(K);
-    // cell range (start, count) of staged cell t < S of brick b (count 0 for a
-    // cell outside a non-periodic grid edge)
-    auto ranges = [&](int b, int t, int &st, int &cnt) {
-        const int cx0 = (b % G.nbx) * BX, cy0 = ((b / G.nbx) % G.nby) * BY, cz0 = (b / (G.nbx * G.nby)) * BZ;
-        st = 0;
-        cnt = 0;
-        if (t < S) {
-            int gx = cx0 - 1 + St::sx_of(t), gy = cy0 - 1 + St::sy_of(t), gz = cz0 - 1 + St::sz_of(t);
-            const bool ok = wrap_axis(gx, G.nx, G.periodic & 1u) && wrap_axis(gy, G.ny, (G.periodic >> 1) & 1u) &&
-                            wrap_axis(gz, G.nz, (G.periodic >> 2) & 1u);
-            if (ok) {
-                const int lin = gx + G.nx * (gy + G.ny * gz);
-                st = cell_start[lin];
-                cnt = cell_end[lin] - st;
-            }
-        }
+    using Rows = StagedRows<BX, BY, BZ, NW>;
+    constexpr int SUB = 2;          // chunks of kWave particles of a row carried to the next item
+    constexpr int PREP = NW - 1;    // the wave that prepares items
+    Chunk chunk[Rows::ROWS][SUB];
+    auto load_chunks = [&](const BrickScans<BX, BY, BZ> &N, int wave, int lane) {
+        // (always loads, so that no chunk is kept from one item to the next)
+        Rows rows;
+        rows.locate(N, wave);
+#pragma unroll
+        for (int k = 0; k < Rows::ROWS; ++k)
+#pragma unroll
+            for (int u = 0; u < SUB; ++u)
+                chunk[k][u] = rows.template load<MODEL>(N, k, u * kWave + lane, pos, vel, cell, info, C);
     };
-    // inner cell u of brick b holds centrals (inner cells past the grid edge
-    // hold none: on a periodic axis the staged copy would be the wrapped cell,
-    // owned by another brick)
-    auto inner_in_grid = [&](int b, int u) {
-        const int cx0 = (b % G.nbx) * BX, cy0 = ((b / G.nbx) % G.nby) * BY, cz0 = (b / (G.nbx * G.nby)) * BZ;
-        return cx0 + St::ix_of(u) < G.nx && cy0 + St::iy_of(u) < G.ny && cz0 + St::iz_of(u) < G.nz;
-    };
-    // Scan ahead, by one wave: claim the next brick and write its cell scans
-    // (the same values as the workgroup's block scans below) into buffer buf,
-    // with wave operations only, while the other waves finish the current
-    // brick's pairs.
-    auto scan_ahead = [&](int lane, int buf) {
-        int kb2 = 0;
-        if (lane == 0) kb2 = atomicAdd(next, 1);
-        kb2 = __shfl(kb2, 0);
-        int total2 = 0, nc2 = 0;
-        if (kb2 < n_listed) {
-            const int b2 = brick_at(table, cap_ids, kb2);
-            constexpr int NCH = (S + kWave - 1) / kWave;
-            int st[NCH], ct[NCH], ex[NCH];
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) ranges(b2, c * kWave + lane, st[c], ct[c]);
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                int inc = ct[c];
-#pragma unroll
-                for (int o = 1; o < kWave; o <<= 1) {
-                    const int v = __shfl_up(inc, o);
-                    if (lane >= o) inc += v;
-                }
-                ex[c] = total2 + inc - ct[c];
-                const int t = c * kWave + lane;
-                if (t < S) {
-                    cBaseB[buf][t] = ex[c];
-                    cDeltaB[buf][t] = ex[c] - st[c];
-                }
-                total2 += __shfl(inc, kWave - 1);
-            }
-            if (lane == 0) cBaseB[buf][S] = total2;
-            // inner cell `lane`: the count and start of its staged cell, taken
-            // from the lane that scanned it
-            const int t = St::inner(min(lane, NI - 1));
-            int vct = 0, vst = 0;
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const int a = __shfl(ct[c], t % kWave), s2 = __shfl(st[c], t % kWave);
-                if (t / kWave == c) {
-                    vct = a;
-                    vst = s2;
-                }
-            }
-            const int icnt = lane < NI && inner_in_grid(b2, lane) ? vct : 0;
-            int inc = icnt;
-#pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                const int v = __shfl_up(inc, o);
-                if (lane >= o) inc += v;
-            }
-            nc2 = __shfl(inc, kWave - 1);
-            if (lane < NI) {
-                iBaseB[buf][lane] = inc - icnt;
-                iStartB[buf][lane] = vst;
-            }
-            if (lane == 0) iBaseB[buf][NI] = nc2;
-        }
-        if (lane == 0) {
-            sPre[1] = kb2;
-            sPre[2] = total2;
-            sPre[3] = nc2;
-        }
-    };
-    int cur = 0;       // buffer of the current brick's scans
-    bool pre = false;  // uniform: they were scanned ahead
-    for (;;) {
-        // the thread index is re-read per brick (an empty asm hides that it is
+    // The first item (prepared, staging loads under way, table made) and the second (prepared)
+    {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+        if (threadIdx.x == 0) Q[2].d = BrickItem{};
+        __syncthreads();
+        if (wave == PREP)
+            prepare_item<BX, BY, BZ, NT, CAP>(Q[0], Q[2].d, true, lane, table, cap_ids, next, cell_start, cell_end, G);
+        else
+            empty_lists<PREP * kWave>(n, count, vel, out, tau, K);
+        __syncthreads();
+        TableMaker<BX, BY, BZ, NT> maker;
+        maker.request(Q[0], wave, lane, count);
+        load_chunks(Q[0], wave, lane);
+        maker.tally(T[0], wave, lane, M);
+        __syncthreads();
+        maker.place(T[0], wave, lane);
+        if (wave == PREP)
+            prepare_item<BX, BY, BZ, NT, CAP>(Q[1], Q[0].d, false, lane, table, cap_ids, next, cell_start, cell_end, G);
+        __syncthreads();
+    }
+    int cur = 0;
+    for (int k = 0;; ++k) {
+        const int nxt = cur == 2 ? 0 : cur + 1, far = nxt == 2 ? 0 : nxt + 1;
+        // the thread index is re-read per item (an empty asm hides that it is
         // the same), so nothing derived from it is kept live across the pair loop
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        int kb, total, nc;
-        if (pre) {
-            kb = sPre[1];
-            total = sPre[2];
-            nc = sPre[3];
-        } else {
-            if (tid == 0) sNext = atomicAdd(next, 1);
-            __syncthreads();
-            kb = sNext;
-        }
-        if (kb >= n_listed) break;  // uniform
-        const int b = brick_at(table, cap_ids, kb);
-        const int cx0 = (b % G.nbx) * BX, cy0 = ((b / G.nbx) % G.nby) * BY, cz0 = (b / (G.nbx * G.nby)) * BZ;
-        int *cBase = cBaseB[cur], *cDelta = cDeltaB[cur], *iBase = iBaseB[cur], *iStart = iStartB[cur];
+        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+        const BrickScans<BX, BY, BZ> &B = Q[cur];
+        const CentralTable<NT> &D = T[k & 1];
+        CentralTable<NT> &DN = T[(k & 1) ^ 1];
+        if (__builtin_amdgcn_readfirstlane(B.d.item) < 0) break;
+        const int s_lo = __builtin_amdgcn_readfirstlane(B.d.s_lo), span = __builtin_amdgcn_readfirstlane(B.d.span);
+        const bool use_lds = __builtin_amdgcn_readfirstlane(B.d.lds) != 0;
+        const int nc = __builtin_amdgcn_readfirstlane(use_lds ? D.used : B.d.nc);
+        TableMaker<BX, BY, BZ, NT> maker;
+        maker.request(Q[nxt], wave, lane, count);
 
-        if (!pre) {
-            // 1. ranges of the staged cells and their LDS bases (the staging
-            //    order of the list build)
-            int st, cnt;
-            ranges(b, tid, st, cnt);
-            const int ex = block_scan<NT>(cnt, total, wsum);
-            if (tid < S) {
-                cBase[tid] = ex;
-                cDelta[tid] = ex - st;
-            }
-            if (tid == 0) cBase[S] = total;
-            __syncthreads();
-            // inner cells (x fastest: each inner row is one contiguous particle range)
-            int icnt = 0, ist = 0;
-            if (tid < NI && inner_in_grid(b, tid)) {
-                const int t = St::inner(tid);
-                icnt = cBase[t + 1] - cBase[t];
-                ist = cBase[t] - cDelta[t];
-            }
-            const int iex = block_scan<NT>(icnt, nc, wsum);
-            if (tid < NI) {
-                iBase[tid] = iex;
-                iStart[tid] = ist;
-            }
-            if (tid == 0) iBase[NI] = nc;
-        }
-        if (nc == 0) {  // uniform: no particle in the brick
-            pre = false;
-            __syncthreads();
-            continue;
-        }
-        __syncthreads();
-        const bool use_lds = total <= CAP;
+        // a wave takes QG consecutive centrals of the table at a time
+        constexpr int QG = kWave / kLanes;
+        const int h = lane % kLanes;
+        // this lane's central of group g: particle, list length (0: none),
+        // table entry, and the first of its list entries, requested here (one
+        // group of centrals ahead of its use; the item's first one before the
+        // staging)
+        struct Central {
+            int i, nt;
+            uint32_t e;
+            const uint4 *lg;
+            Entries list, more;
+        };
+        const uint32_t lo2 = (uint32_t)s_lo * 0x10001u, max2 = (uint32_t)(span - 1) * 0x10001u;
+        // (without a branch, so that no loaded value is copied: past the table,
+        // or where there is none, a lane loads some particle's list)
+        auto take = [&](int g) {
+            Central c;
+            const int q = g * QG + lane / kLanes;
+            c.e = D.cen[max(min(q, nc - 1), 0)];
+            c.nt = q < nc ? (int)(c.e >> kCenCountShift) : 0;
+            const uint32_t i = (c.e & kCenSlotMask) + (uint32_t)B.row_shift[c.e >> kCenRowShift & 15u];
+            c.i = (int)min(i, (uint32_t)(n - 1));
+            c.lg = list_groups(neibs_brick, c.i, brick_groups(M));
+            const int last = max((int)(c.e >> kCenCountShift) - 1, 0) / kEntries;
+            c.list = list_entries(c.lg, min(h, last));
+            c.more = list_entries(c.lg, min(h + kLanes, last));
+            return c;
+        };
+        int g = wave;
+        Central now = take(g);
         if (K.cell_scene && tid < NI) {
             // the step of each inner cell's scene, for the corrector of its
             // centrals (read after the staging barrier)
+            const int b = B.d.brick;
+            const int cx = (b % G.nbx) * BX + St::ix_of(tid), cy = ((b / G.nbx) % G.nby) * BY + St::iy_of(tid),
+                      cz = (b / (G.nbx * G.nby)) * BZ + St::iz_of(tid);
             int sc = -1;
-            if (inner_in_grid(b, tid)) {
-                const int lin = (cx0 + St::ix_of(tid)) +
-                                G.nx * ((cy0 + St::iy_of(tid)) + G.ny * (cz0 + St::iz_of(tid)));
-                sc = K.cell_scene[lin];
+            if (cx < G.nx && cy < G.ny && cz < G.nz) {
+                sc = K.cell_scene[cx + G.nx * (cy + G.ny * cz)];
                 if ((unsigned)sc >= (unsigned)K.n_scenes) sc = -1;
             }
             sSc[tid] = sc;
             sTau[tid] = sc >= 0 ? (float)K.d_dt[sc] : 0.0f;
         }
-        // central particle of lane q (binary search over the inner cells)
-        auto central = [&](int q, int &u, int &i) {
-            int lo = 0, hi = NI - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (iBase[mid] <= q) lo = mid;
-                else hi = mid - 1;
-            }
-            u = lo;
-            i = iStart[u] + (q - iBase[u]);
-        };
-        // two lanes per central particle (lanes 2q', 2q' + 1): a brick holds
-        // fewer centrals than the workgroup has lanes (about 840 at lattice
-        // density), and half lists spread the work over all 16 waves
-        const int h = tid & 1;
-        if (tid == 0) sGroup = 0;  // read after the staging barrier
-        // the list count of each wave's first group is requested before the staging loads
-        // so the two latencies overlap (consecutive centrals stay on consecutive
-        // lanes: their list groups are contiguous, one coalesced load per wave)
-        int u0, i0;
-        central(min(tid / 2, nc - 1), u0, i0);
-        const uint32_t cnt0 = tid / 2 < nc ? count[i0] : 0u;
+        if (tid == 0) sGroup = NW;  // read after the staging barrier
         if (use_lds) {
-            // 2. stage the brick and its halo.  Wave w takes the staged rows w,
-            //    w + NW, ... (a row is SX x-consecutive cells: one contiguous
-            //    LDS range and, away from a periodic seam, one contiguous
-            //    global range); the wave walks its rows as one range in chunks
-            //    of 64 particles, the loads of SB chunks issued before their
-            //    LDS stores so that their latencies overlap
-            constexpr int NW = NT / kWave, NR = SY * SZ, RPW = (NR + NW - 1) / NW, SB = 4;
-            const int wave = tid / kWave, lane = tid % kWave;
-            int dlt[RPW], off[RPW + 1], e[RPW][SX - 1];
-            off[0] = 0;
+            // the item's particles into LDS: the chunks requested at the end of
+            // the last item, then what is left of rows longer than those
+            Rows rows;
+            rows.locate(B, wave);
 #pragma unroll
-            for (int k = 0; k < RPW; ++k) {
-                const int r = wave + k * NW, rr = min(r, NR - 1);
-                const int b0 = cBase[rr * SX];
-                dlt[k] = b0 - off[k];
-                off[k + 1] = off[k] + (r < NR ? cBase[rr * SX + SX] - b0 : 0);
+            for (int r = 0; r < Rows::ROWS; ++r)
 #pragma unroll
-                for (int m = 0; m < SX - 1; ++m) e[k][m] = cBase[rr * SX + 1 + m];
-            }
-            const int L = off[RPW];
-            for (int tb = 0; tb < L; tb += SB * kWave) {
-                int slot[SB], cc[SB], rw[SB];
-                float4 p[SB], v[SB];
-                float ah[SB];  // alpha h of each loaded particle
-                bool bnd[SB];
+                for (int u = 0; u < SUB; ++u) rows.template store<MODEL>(L, chunk[r][u], r, u * kWave + lane, C);
 #pragma unroll
-                for (int u = 0; u < SB; ++u) {
-                    const int t = tb + u * kWave + lane;
-                    int k = 0;
+            for (int r = 0; r < Rows::ROWS; ++r)
+                for (int t = SUB * kWave + lane; t - lane < rows.len[r]; t += kWave)
+                    rows.template store<MODEL>(L, rows.template load<MODEL>(B, r, t, pos, vel, cell, info, C), r, t, C);
+        }
+        maker.tally(DN, wave, lane, M);
+        __syncthreads();
+        auto claim = [&]() {
+            int c = 0;
+            if (lane == 0) c = atomicAdd(&sGroup, 1);
+            return __builtin_amdgcn_readfirstlane(c);
+        };
+        if (wave == PREP) {
+            // (few instructions in a long chain of latencies: it goes first)
+            __builtin_amdgcn_s_setprio(3);
+            prepare_item<BX, BY, BZ, NT, CAP>(Q[far], Q[nxt].d, false, lane, table, cap_ids, next, cell_start, cell_end,
+                                              G);
+            __builtin_amdgcn_s_setprio(0);
+        }
+        while (g * QG < nc) {  // wave-uniform
+            if (use_lds) {
+                const int gn = claim();
+                Central c = now;
+                now = take(gn);
+                const int si = (int)(c.e & kCenSlotMask);
+                PairAcc A = {0.0f, 0.0f, 0.0f, 0.0f};
+                if (c.nt > 0)
+                    brick_pairs_lds<MODEL, CAP>(A, c.lg, c.list, c.more, h, c.nt, lo2, max2, L, L.P[si], L.V[si],
+                                                L.A[si], C);
+                A.ax = lanes_sum(A.ax);
+                A.ay = lanes_sum(A.ay);
+                A.az = lanes_sum(A.az);
+                A.dr = lanes_sum(A.dr);
+                if (h == 0 && c.nt > 0) {
+                    const float4 f = make_float4(A.ax, A.ay, A.az, A.dr);
+                    if (out) store_at(out, c.i, f);
+                    if (K.d_dt) {
+                        const float4 ustar = L.V[si];
+                        if (!K.cell_scene) {
+                            corrector_apply(c.i, f, ustar, tau, K);
+                        } else {
+                            // the central's inner cell: its place in its row
+                            const int r = (int)(c.e >> kCenRowShift & 15u);
+                            const int t0 = St::cell(1, r / BZ + 1, r % BZ + 1);
+                            int u = r * BX;
 #pragma unroll
-                    for (int m = 1; m < RPW; ++m) k += t >= off[m] ? 1 : 0;
-                    int d = dlt[0], ee[SX - 1];
-#pragma unroll
-                    for (int m = 0; m < SX - 1; ++m) ee[m] = e[0][m];
-#pragma unroll
-                    for (int q = 1; q < RPW; ++q)
-                        if (k == q) {
-                            d = dlt[q];
-#pragma unroll
-                            for (int m = 0; m < SX - 1; ++m) ee[m] = e[q][m];
+                            for (int m = 1; m < BX; ++m) u += si + s_lo >= B.base[t0 + m] ? 1 : 0;
+                            if (sSc[u] >= 0) corrector_apply(c.i, f, ustar, sTau[u], K);
                         }
-                    const int s2 = t + d;
-                    int c = 0;
-#pragma unroll
-                    for (int m = 0; m < SX - 1; ++m) c += s2 >= ee[m] ? 1 : 0;
-                    const int r = min(wave + k * NW, NR - 1);
-                    slot[u] = t < L ? s2 : -1;
-                    cc[u] = c;
-                    rw[u] = r;
-                    // past the wave's range a lane loads particle 0 (loads stay
-                    // unconditional, so the chunk buffers stay in registers)
-                    const int j = t < L ? s2 - cDelta[r * SX + c] : 0;
-                    p[u] = pos[j];
-                    v[u] = vel[j];
-                    ah[u] = alpha_h_of(j, cell, C);
-                    bnd[u] = (MODEL & kDiffusion) ? ptype(info[j]) == kBoundary : false;
-                }
-#pragma unroll
-                for (int u = 0; u < SB; ++u) {
-                    if (slot[u] >= 0) {
-                        const float sx = (float)(cc[u] - 2), sy = (float)(rw[u] / SZ - 2),
-                                    sz = (float)(rw[u] % SZ - 2);
-                        // w = m x kernel coefficient, negated for boundary particles
-                        // when the density diffusion needs the type
-                        const float mf = p[u].w * C.fcoeff;
-                        sP[slot[u]] = make_float4(fmaf(sx, C.csx, p[u].x), fmaf(sy, C.csy, p[u].y),
-                                                  fmaf(sz, C.csz, p[u].z), bnd[u] ? -mf : mf);
-                        sV[slot[u]] = v[u];
-                        // equation-of-state terms from the staged density
-                        sA[slot[u]] = eos_terms(v[u].w, ah[u], C);
                     }
                 }
-            }
-        }
-        __syncthreads();
-        // (every thread read sPre at the top of this brick)
-        if (tid == 0) sPre[0] = 0;
-
-        // 3. two lanes per central particle of the brick, a wave taking
-        //    kWave / 2 consecutive centrals at a time: wave w takes group w
-        //    first (its counts were requested before the staging), then claims
-        //    the next unclaimed group as it finishes one, so that waves that
-        //    drew cheap groups (short lists) take more of the brick
-        const int M = C.max_neibs;
-        const uint32_t jmax = (uint32_t)(n - 1);
-        constexpr int NW = NT / kWave, QG = kWave / 2;
-        int g = tid / kWave;
-        for (bool first = true; g * QG < nc; first = false) {  // wave-uniform
-            const int q = g * QG + (tid % kWave) / 2;
-            const bool act = q < nc;
-            int u = u0, i = i0;
-            uint32_t cntw = cnt0;
-            if (!first) {
-                central(act ? q : nc - 1, u, i);
-                cntw = act ? count[i] : 0u;
-            }
-            const int nf = min((int)(cntw & 0xFFFFu), M);
-            const int nt = min(nf + (int)(cntw >> 16), M);
-            const int ntw = __builtin_amdgcn_readfirstlane(wave_max(nt));
-            PairAcc A = {0.0f, 0.0f, 0.0f, 0.0f};
-            float4 ustar;  // the central's own velocity (corrector stage)
-            if (ntw > 0) {
-                const size_t toff = (size_t)(i / kWave) * (kWave * M) + (i % kWave);
-                if (use_lds) {
-                    const int tc = St::inner(u);
-                    const int si = i + cDelta[tc];
-                    const uint4 *lg = (const uint4 *)(neibs_brick + brick_entry(i, 0, brick_groups(M)));
-                    brick_pairs_lds<MODEL, NT>(A, lg, h, nt, ntw, total, sP, sV, sA, sP[si], sV[si], sA[si], C);
-                    A.ax += __shfl_xor(A.ax, 1);
-                    A.ay += __shfl_xor(A.ay, 1);
-                    A.az += __shfl_xor(A.az, 1);
-                    A.dr += __shfl_xor(A.dr, 1);
-                    if (K.d_dt) ustar = sV[i + cDelta[St::inner(u)]];
-                } else {
-                    // the first lane of the pair walks the whole list (a shallow
-                    // pipeline: this path shares the register budget of the LDS
-                    // path and runs only where a halo overflows)
+                g = gn;
+            } else {
+                // more particles than LDS holds: the global lists and state with
+                // the arithmetic of k_forces, by the first lane of each central
+                // (a shallow pipeline: this path shares the register budget of
+                // the LDS path)
+                const int q = g * QG + lane / kLanes;
+                const int i = item_central(B, min(q, nc - 1));
+                const uint32_t cw = q < nc && h == 0 ? count[i] : 0u;
+                const int nf = min((int)(cw & 0xFFFFu), M), nt = min(nf + (int)(cw >> 16), M);
+                const int ntw = __builtin_amdgcn_readfirstlane(wave_max(nt));
+                if (ntw > 0) {
                     const bool central_fluid = (MODEL & kDiffusion) ? ptype(info[i]) != kBoundary : true;
                     const float4 vi = vel[i];
-                    gather_pairs<MODEL, 2>(A, neibs + toff, nf, h == 0 ? nt : 0, ntw, M, jmax, pos, vel, nullptr, cell,
-                                           pos[i], vi, eos_terms(vi.w, alpha_h_of(i, cell, C), C), central_fluid, C);
-                    ustar = vi;
+                    PairAcc A = {0.0f, 0.0f, 0.0f, 0.0f};
+                    gather_pairs<MODEL, 2>(A, neibs + (size_t)(i / kWave) * (kWave * M) + (i % kWave), nf, nt, ntw, M,
+                                           (uint32_t)(n - 1), pos, vel, nullptr, cell, pos[i], vi,
+                                           eos_terms<(MODEL & kLandrini) != 0>(vi.w, alpha_h_of(i, cell, C), C), central_fluid, C);
+                    if (nt > 0) {
+                        const float4 f = make_float4(A.ax, A.ay, A.az, A.dr);
+                        if (out) out[i] = f;
+                        if (K.d_dt) corrector_at(i, f, vi, tau, K);
+                    }
                 }
+                g = claim();
             }
-            // (particles with an empty list are written after the last brick)
-            if (act && h == 0 && nt > 0) {
-                const float4 f = make_float4(A.ax, A.ay, A.az, A.dr);
-                if (out) out[i] = f;
-                // (a central lies in one of the brick's cells: inner cell u)
-                if (K.d_dt) {
-                    if (!K.cell_scene)
-                        corrector_apply(i, f, ustar, tau, K);
-                    else if (sSc[u] >= 0)
-                        corrector_apply(i, f, ustar, sTau[u], K);
-                }
-            }
-            int gn = 0;
-            if (tid % kWave == 0) gn = atomicAdd(&sGroup, 1) + NW;
-            g = __builtin_amdgcn_readfirstlane(__shfl(gn, 0));
         }
-        // the first wave left without a group scans the next brick ahead
-        int won = 0;
-        if (tid % kWave == 0) won = atomicCAS(&sPre[0], 0, 1) == 0;
-        if (__builtin_amdgcn_readfirstlane(__shfl(won, 0))) scan_ahead(tid % kWave, cur ^ 1);
-        __syncthreads();  // the next brick reuses the LDS
-        pre = sPre[0] != 0;
-        if (pre) cur ^= 1;
+        // (in the time that waves without a group wait for the others)
+        maker.place(DN, wave, lane);
+        load_chunks(Q[nxt], wave, lane);
+        __syncthreads();  // the next item reuses the LDS
+        cur = nxt;
     }
-    // Particles with an empty list (none of their bricks' pairs; also those
-    // the build dropped) get zero derivatives, by all workgroups as they run
-    // out of bricks: no other lane writes them.
-    for (int i = blockIdx.x * NT + threadIdx.x; i < n; i += gridDim.x * NT)
-        if (count[i] == 0u) {
-            const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (out) out[i] = z;
-            if (K.d_dt && K.cell[i] >= 0) corrector_at(i, z, vel[i], tau, K);
-        }
 }
 
-// LDS capacity (staged particles, 40 bytes each) per brick shape: the halo
-// of a brick at the h = 1.3 dp, r_s = 2.86 dp lattice density holds up to
-// about 27 particles per staged cell (3 x 4 x 3: 150 cells, 3825 at most in
-// the 1.62M dam break; 3 x 3 x 3: 125 cells, 3375; 3 x 2 x 3: 100 cells).
-// Measured on the 1.62M dam break (one workgroup per CU in every case):
-// 3 x 4 x 3 277 us, 3 x 3 x 3 357 us, 4 x 3 x 3 425 us (1% of its bricks
-// overflow the LDS there).
-constexpr int brick_cap(int BX, int BY, int BZ) { return BX * BY * BZ >= 36 ? 4000 : (BX * BY * BZ >= 27 ? 3400 : 2750); }
+// A workgroup has the LDS of a CU to itself whatever the brick shape: 40
+// bytes per staged particle, 13 KB of scans and tables.  The halo of a brick at the h =
+// 1.3 dp, r_s = 2.86 dp lattice density holds up to about 27 particles per
+// staged cell (3 x 4 x 3: 150 cells, 3825 at most in the 1.62M dam break);
+// bricks beyond the capacity are taken in runs of fewer rows.
+constexpr int kBrickThreads = 1024;
+constexpr int kBrickCap = 3760;
 
 template <int MODEL>
 void launch_brick(const ForceArgs &a, const ForceConst &C, hipStream_t s)
@@ -693,11 +757,10 @@ void launch_brick(const ForceArgs &a, const ForceConst &C, hipStream_t s)
     with_shape(a.shape, [&]<int BX, int BY, int BZ>() {
         const BrickGrid G = brick_grid<BX, BY, BZ>(a.grid->ncell, a.grid->periodic);
         const unsigned blocks = (unsigned)G.nbx * G.nby * G.nbz;
-        constexpr int NT = brick_threads(BX * BY * BZ);
         // (the brick counter was zeroed before the launch; the table of
-        // bricks with a pair is the build's)
-        const unsigned wgs = blocks < (unsigned)sph_device_cus() ? blocks : (unsigned)sph_device_cus();
-        k_forces_brick<MODEL, BX, BY, BZ, NT, brick_cap(BX, BY, BZ)><<<wgs, NT, 0, s>>>(
+        // bricks with a pair is the build's; at most one item per row of a brick)
+        const unsigned wgs = brick_workgroups(blocks, BY);
+        k_forces_brick<MODEL, BX, BY, BZ, kBrickThreads, kBrickCap><<<wgs, kBrickThreads, 0, s>>>(
             a.n, a.pos, a.vel, a.cell, a.neibs, a.neibs_brick, a.count, a.cell_start, a.cell_end, a.table,
             a.cap_ids, a.next, a.info, a.out, C, G, a.K);
     });

@@ -1,0 +1,71 @@
+"""The work items of the brick kernels where they can go wrong: bricks that
+hold more particles than LDS (cut into runs of rows, or left to the gather
+path), grids of few bricks (cut so that every CU has work), lists at the
+edges of a lane's runs of eight entries.  Against the FP64 oracle, to the
+derivative bar of the parity tests (1e-5 of the magnitude scale)."""
+import numpy as np
+import pytest
+
+from workloads import scenes as S
+
+from parity import check_forces, compare_build, edge_allowance, log, make_sim, oracle_forces_of, torch_sync
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = [(3, 4, 3), (3, 3, 3), (3, 2, 3)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _brick_totals(sc, brick):
+    """Particles of every brick with its one-cell halo (closed axes)."""
+    nx, ny, nz = (int(v) for v in sc.grid.ncell)
+    cnt = np.bincount(sc.cell, minlength=nx * ny * nz).reshape(nz, ny, nx)
+    return np.array([cnt[max(z - 1, 0):z + brick[2] + 1, max(y - 1, 0):y + brick[1] + 1,
+                         max(x - 1, 0):x + brick[0] + 1].sum()
+                     for z in range(0, nz, brick[2]) for y in range(0, ny, brick[1]) for x in range(0, nx, brick[0])])
+
+
+@pytest.mark.parametrize("brick", SHAPES, ids=["x".join(map(str, b)) for b in SHAPES])
+def test_crowded_bricks(brick):
+    """2.2 times the lattice density: with the default shape every brick is
+    beyond the LDS capacity (3760 particles), some cut into runs of rows, some
+    beyond what is cut (4800); the smaller shapes mix whole and cut bricks."""
+    sc = S.random_cloud(n=17500, box=(0.4, 0.4, 0.4), dp=0.02, seed=21, boundary_frac=0.2, u_sigma=0.2)
+    t = _brick_totals(sc, brick)
+    if brick == (3, 4, 3):
+        assert t.min() > 3760 and (t <= 4800).any() and (t > 4800).any(), t
+    sim = make_sim(sc, max_neibs=416, brick=brick)
+    sim.build()
+    a = sim.forces(bricks=True).clone()
+    b = sim.forces(bricks=True).clone()
+    torch_sync()
+    assert torch.equal(a, b)
+    ob = compare_build(sc, sim, max_neibs=416)
+    _, (acc, drho, sa, sd, _ni) = oracle_forces_of(sc, ob)
+    check_forces(a[: sc.n].cpu().numpy(), acc, drho, sa, sd, label="crowded")
+
+
+@pytest.mark.parametrize("brick", SHAPES, ids=["x".join(map(str, b)) for b in SHAPES])
+@pytest.mark.parametrize("n", [1, 2, 9, 65, 700, 2100])
+def test_few_bricks(n, brick):
+    """One to a few bricks, so that each is cut into its rows; the lists run
+    from empty ones over the edges of a run of eight (n = 9) to full ones."""
+    box = (0.12, 0.12, 0.12) if n < 100 else (0.2, 0.27, 0.16)
+    sc = S.random_cloud(n=n, box=box, dp=0.02, seed=300 + n, boundary_frac=0.2, u_sigma=0.2)
+    log("case few bricks n=%d" % n)
+    sim = make_sim(sc, max_neibs=256, brick=brick, capacity=n + 3)
+    sim.build()
+    sim.forces_n.fill_(float("nan"))
+    f = sim.forces(bricks=True).clone()
+    torch_sync()
+    assert torch.isnan(f[n:]).all(), "rows past n written"
+    ob = compare_build(sc, sim, max_neibs=256)
+    _, (acc, drho, sa, sd, _ni) = oracle_forces_of(sc, ob)
+    check_forces(f[:n].cpu().numpy(), acc, drho, sa, sd, label="few bricks %d" % n, allowance=edge_allowance(sc, ob))
