@@ -252,8 +252,8 @@ size_t sph_build_workspace_bytes(int32_t capacity, int32_t n_cells);
  *      form of sph_forces: [0] the number of heavy bricks (at least 12
  *      particles per inner cell), [1 .. capacity] brick ids bx + nbx (by +
  *      nby bz) of the grid tiled by grid->brick from cell 0, the heavy ones
- *      from the front and the light ones from the back, [capacity + 1] the
- *      number of light bricks, [capacity + 2 ..] reserved (capacity is at
+ *      from the front and the light ones from the back (both in order of
+ *      size, large ones first), [capacity + 1] the number of light bricks, [capacity + 2 ..] reserved (capacity is at
  *      least 1 here);
  * A particle whose neighbours exceed max_neibs keeps the first max_neibs
  * found (scan order: cells z, y, x outer to inner, then sorted index) and is

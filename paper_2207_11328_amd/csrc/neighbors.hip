@@ -5,9 +5,10 @@
 // "Changing perspective: from the particle to the cell").  Instead of a
 // multi-pass radix sort of 64-bit keys, the cell index is used directly as
 // a single radix digit: a histogram over cells, an exclusive scan (which is
-// also the cell-start array) and an atomic scatter put every particle in its
-// cell's range; one wave per cell then ranks the cell's few particles by
-// their (type, id) word, which makes the permutation unique.
+// also the cell-start array) and a scatter put every particle in its cell's
+// range; each particle then ranks itself among the few of its cell by their
+// (type, id) words, which makes the permutation unique, and is copied to its
+// final place.
 //
 // Lists are split (fluid from the front, boundary from the back) and stored
 // neighbour-major (section "Efficient split neighbors list").
@@ -22,9 +23,13 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kScanItems = 4;                       // per thread
 constexpr int kScanTile = kThreads * kScanItems;    // elements per block
+// blocks up to which every block of the scan adds up the sums before it
+// itself (1M cells: at most 4 loads per lane; beyond, the re-reading grows with
+// the square of the grid)
+constexpr int kFewPartials = 1024;
 
 struct BuildLayout {
-    size_t cnt, cursor, start, partials, perm_a, perm_b, t_cell, t_pos, t_vel, t_info, active, flags, total;
+    size_t cnt, hist, start, partials, keys, index, t_cell, t_pos, t_vel, place, active, classes, total;
 };
 
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
@@ -36,45 +41,36 @@ BuildLayout build_layout(int64_t capacity, int64_t n_cells)
     BuildLayout L;
     size_t o = 0;
     L.cnt = o;      o = align_up(o + sizeof(int32_t) * nb);
-    L.cursor = o;   o = align_up(o + sizeof(int32_t) * nb);
+    // (a histogram of 64 classes per 1024 bricks, and at most one brick per
+    // cell: within nb words, or within the 64 of the alignment)
+    L.hist = o;     o = align_up(o + sizeof(int32_t) * nb);
     L.start = o;    o = align_up(o + sizeof(int32_t) * (nb + 1));
     L.partials = o; o = align_up(o + sizeof(int32_t) * (nparts + 1));
-    L.perm_a = o;   o = align_up(o + sizeof(uint32_t) * capacity);
-    L.perm_b = o;   o = align_up(o + sizeof(uint32_t) * capacity);
+    L.keys = o;     o = align_up(o + sizeof(uint32_t) * capacity);
+    L.index = o;    o = align_up(o + sizeof(uint32_t) * capacity);
     L.t_cell = o;   o = align_up(o + sizeof(int32_t) * capacity);
     L.t_pos = o;    o = align_up(o + sizeof(float4) * capacity);
     L.t_vel = o;    o = align_up(o + sizeof(float4) * capacity);
-    L.t_info = o;   o = align_up(o + sizeof(uint32_t) * capacity);
+    L.place = o;    o = align_up(o + sizeof(uint32_t) * capacity);
     L.active = o;   o = align_up(o + sizeof(int32_t) * (n_cells + 1));
-    L.flags = o;    o = align_up(o + (size_t)n_cells + 4);
+    L.classes = o;  o = align_up(o + (size_t)n_cells + 4);
     L.total = o;
     return L;
 }
 
 // Everything the build counts into starts at zero, in one launch (a kernel,
 // not a memset, so that a captured graph holds no memset node): the bucket
-// counts and cursors (nb each), the status words, the cell flags of the
-// table of bricks with a pair (flag_words int32 words, none without brick
-// lists) and the counters of the active-brick list and of that table.
-__global__ void k_build_zero(int64_t nb, int32_t *__restrict__ cnt, int32_t *__restrict__ cursor,
-                             int32_t *__restrict__ status, int64_t flag_words, int32_t *__restrict__ flags,
-                             int32_t *__restrict__ active, int32_t *__restrict__ table_heavy,
-                             int32_t *__restrict__ table_light)
+// counts (nb), the status words, the size classes of the bricks with a pair
+// (key_words int32 words, none without brick lists) and the counter of the
+// active-brick list.
+__global__ void k_build_zero(int64_t nb, int32_t *__restrict__ cnt, int32_t *__restrict__ status, int64_t key_words,
+                             int32_t *__restrict__ keys, int32_t *__restrict__ active)
 {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = t; i < nb; i += stride) {
-        cnt[i] = 0;
-        cursor[i] = 0;
-    }
-    for (int64_t i = t; i < flag_words; i += stride) flags[i] = 0;
+    for (int64_t i = t; i < nb; i += stride) cnt[i] = 0;
+    for (int64_t i = t; i < key_words; i += stride) keys[i] = 0;
     if (t < SPH_STATUS_WORDS) status[t] = 0;
-    if (t == 0) {
-        *active = 0;
-        if (table_heavy) {
-            *table_heavy = 0;
-            *table_light = 0;
-        }
-    }
+    if (t == 0) *active = 0;
 }
 
 // atomicAdd(&cnt[key], 1) for every valid lane of a wave, combined over runs
@@ -104,51 +100,71 @@ __device__ __forceinline__ int run_atomic_inc(int32_t *cnt, int key, bool valid)
 
 // Re-bin offsets into [-cs/2, cs/2) (float32, at most 4 cells per axis) and
 // count particles per cell.  Particles that leave a non-periodic axis, or
-// whose offsets are not finite, become dropped (cell = -1, last bucket).
+// whose offsets are not finite, become dropped (cell = -1, last bucket).  The
+// re-binned state goes to the workspace, from where k_sort_gather brings it
+// back in sorted order (so the state is read and written twice in all), with
+// each particle's place among its cell's as the counting met it.  Also counts the
+// particles whose offset, mass, velocity or density is not finite (one atomic
+// per wave), so that a state that blew up is reported by the status word.
 __global__ __launch_bounds__(kThreads) void k_rebin_count(
-    int n, int32_t *__restrict__ cell, float4 *__restrict__ pos, CellDims dims, float csx, float csy,
-    float csz, int cell_base, int n_cells, int32_t *__restrict__ cnt)
+    int n, const int32_t *__restrict__ cell, const float4 *__restrict__ pos, const float4 *__restrict__ vel,
+    CellDims dims, float csx, float csy, float csz, int cell_base, int n_cells, int32_t *__restrict__ cnt,
+    int32_t *__restrict__ t_cell, float4 *__restrict__ t_pos, float4 *__restrict__ t_vel,
+    uint32_t *__restrict__ place, int32_t *__restrict__ status)
 {
     const int i = blockIdx.x * kThreads + threadIdx.x;
     const bool valid = i < n;
     int c = valid ? cell[i] : -1;
     int bucket = n_cells;
-    if (valid && c >= 0) {
-        int cc[3];
-        cell_coords(c - cell_base, dims, cc[0], cc[1], cc[2]);
+    bool bad = false;
+    if (valid) {
         float4 p = pos[i];
-        float o[3] = {p.x, p.y, p.z};
-        const float cs[3] = {csx, csy, csz};
-        const int nd[3] = {dims.nx, dims.ny, dims.nz};
-        bool ok = true;
+        const float4 v = vel[i];
+        t_vel[i] = v;
+        int moved = c;
+        if (c >= 0) {
+            int cc[3];
+            cell_coords(c - cell_base, dims, cc[0], cc[1], cc[2]);
+            float o[3] = {p.x, p.y, p.z};
+            const float cs[3] = {csx, csy, csz};
+            const int nd[3] = {dims.nx, dims.ny, dims.nz};
+            bool ok = true;
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const float half = 0.5f * cs[d];
-            float v = o[d];
-            for (int it = 0; it < 4; ++it) {
-                if (v >= half) { v = v - cs[d]; cc[d] += 1; }
-                else if (v < -half) { v = v + cs[d]; cc[d] -= 1; }
-                else break;
+            for (int d = 0; d < 3; ++d) {
+                const float half = 0.5f * cs[d];
+                float w = o[d];
+                for (int it = 0; it < 4; ++it) {
+                    if (w >= half) { w = w - cs[d]; cc[d] += 1; }
+                    else if (w < -half) { w = w + cs[d]; cc[d] -= 1; }
+                    else break;
+                }
+                if (!(w >= -half && w < half)) ok = false;
+                if ((dims.periodic >> d) & 1u) {
+                    cc[d] %= nd[d];
+                    if (cc[d] < 0) cc[d] += nd[d];
+                } else if (cc[d] < 0 || cc[d] >= nd[d]) {
+                    ok = false;
+                }
+                o[d] = w;
             }
-            if (!(v >= -half && v < half)) ok = false;
-            if ((dims.periodic >> d) & 1u) {
-                cc[d] %= nd[d];
-                if (cc[d] < 0) cc[d] += nd[d];
-            } else if (cc[d] < 0 || cc[d] >= nd[d]) {
-                ok = false;
+            p = make_float4(o[0], o[1], o[2], p.w);
+            if (ok) {
+                const int lc = cc[0] + dims.nx * (cc[1] + dims.ny * cc[2]);
+                moved = lc + cell_base;
+                bucket = lc;
+            } else {
+                moved = -1;
             }
-            o[d] = v;
         }
-        pos[i] = make_float4(o[0], o[1], o[2], p.w);
-        if (ok) {
-            const int lc = cc[0] + dims.nx * (cc[1] + dims.ny * cc[2]);
-            cell[i] = lc + cell_base;
-            bucket = lc;
-        } else {
-            cell[i] = -1;
-        }
+        t_cell[i] = moved;
+        t_pos[i] = p;
+        bad = !(isfinite(p.x) && isfinite(p.y) && isfinite(p.z) && isfinite(p.w) && isfinite(v.x) &&
+                isfinite(v.y) && isfinite(v.z) && isfinite(v.w));
     }
-    run_atomic_inc(cnt, bucket, valid);
+    const int r = run_atomic_inc(cnt, bucket, valid);
+    if (valid) place[i] = (uint32_t)r;
+    const unsigned long long m = __ballot(bad);
+    if (m && (threadIdx.x % kWave) == 0) atomicAdd(&status[SPH_STATUS_NONFINITE], (int)__popcll(m));
 }
 
 // ---- exclusive scan of cnt[0..m) into start[0..m], start[m] = total --------
@@ -189,8 +205,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_reduce(const int32_t *__restr
     if (threadIdx.x == 0) partials[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(kThreads) void k_scan_partials(int32_t *__restrict__ partials, int np,
-                                                            int32_t *__restrict__ grand_total)
+__global__ __launch_bounds__(kThreads) void k_scan_partials(int32_t *__restrict__ partials, int np)
 {
     int carry = 0;
     for (int base = 0; base < np; base += kThreads) {
@@ -201,14 +216,28 @@ __global__ __launch_bounds__(kThreads) void k_scan_partials(int32_t *__restrict_
         if (i < np) partials[i] = carry + ex;
         carry += total;
     }
-    if (threadIdx.x == 0) *grand_total = carry;
 }
 
+// ... in[0..m) is the bucket counts (m = n_cells + 1, the last bucket the
+// dropped particles): also writes the cell ranges and, from the last bucket,
+// the particles in cells and the dropped ones to the status words.  FEW: the
+// partials are the blocks' sums, not yet scanned (few enough for every block
+// to add up those before it, which saves the launch between).
+template <bool FEW>
 __global__ __launch_bounds__(kThreads) void k_scan_apply(const int32_t *__restrict__ in, int m,
                                                          const int32_t *__restrict__ partials,
-                                                         int32_t *__restrict__ out)
+                                                         int32_t *__restrict__ out, int32_t *__restrict__ cell_start,
+                                                         int32_t *__restrict__ cell_end, int32_t *__restrict__ status)
 {
     const int base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
+    int before = 0;
+    if constexpr (FEW) {
+        int p = 0;
+        for (int k = threadIdx.x; k < (int)blockIdx.x; k += kThreads) p += partials[k];
+        (void)block_exclusive_scan(p, before);
+    } else {
+        before = partials[blockIdx.x];
+    }
     int v[kScanItems];
     int s = 0;
 #pragma unroll
@@ -217,161 +246,173 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(const int32_t *__restri
         s += v[k];
     }
     int total;
-    int ex = block_exclusive_scan(s, total) + partials[blockIdx.x];
+    int ex = block_exclusive_scan(s, total) + before;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
-        if (base + k < m) out[base + k] = ex;
+        const int c = base + k;
+        if (c < m) out[c] = ex;
+        if (c < m - 1) {
+            cell_start[c] = ex;
+            cell_end[c] = ex + v[k];
+        } else if (c == m - 1) {
+            out[m] = ex + v[k];
+            status[SPH_STATUS_N_ACTIVE] = ex;
+            status[SPH_STATUS_DROPPED] = v[k];
+        }
         ex += v[k];
     }
 }
 
-// Place every particle in its bucket's range (order inside a bucket is
-// arbitrary at this point).
+// Place every particle's (type, id) word and index in its bucket's range
+// (order inside a bucket as the counting met them).
 __global__ __launch_bounds__(kThreads) void k_scatter(int n, const int32_t *__restrict__ cell,
                                                       int cell_base, int n_cells,
                                                       const int32_t *__restrict__ start,
-                                                      int32_t *__restrict__ cursor,
-                                                      uint32_t *__restrict__ perm)
+                                                      const uint32_t *__restrict__ place,
+                                                      const uint32_t *__restrict__ info,
+                                                      uint32_t *__restrict__ keys, uint32_t *__restrict__ index)
 {
     const int i = blockIdx.x * kThreads + threadIdx.x;
-    const bool valid = i < n;
-    const int c = valid ? cell[i] : -1;
+    if (i >= n) return;
+    const int c = cell[i];
     const int b = c >= 0 ? c - cell_base : n_cells;
-    const int r = run_atomic_inc(cursor, b, valid);
-    if (valid) perm[start[b] + r] = (uint32_t)i;
+    const int slot = start[b] + (int)place[i];
+    keys[slot] = info[i];
+    index[slot] = (uint32_t)i;
 }
 
-// Rank each particle of a bucket by its info word (type << 30 | id) and
-// write it to its final position.  Ids are unique; equal words (invalid
-// input) are ranked by their slot so the result is a permutation in every
-// case.  One wave per window of kWave consecutive positions of the scattered
-// order (which is grouped by bucket): the wave ranks the buckets that start
-// in its window, one after the other.  Most buckets of a grid can be empty
-// (the air above a dam break); waves over positions visit only buckets that
-// hold particles, where a wave per bucket would be dispatched for each.
-__global__ __launch_bounds__(kThreads) void k_cell_sort(int n, const int32_t *__restrict__ cell, int cell_base,
-                                                        int n_cells, const int32_t *__restrict__ start,
-                                                        const uint32_t *__restrict__ perm_in,
-                                                        const uint32_t *__restrict__ info,
-                                                        uint32_t *__restrict__ perm_out)
+// Every particle ranks itself in its bucket by its info word (type << 30 |
+// id) and is copied to its final position.  Ids are unique; equal words
+// (invalid input) are ranked by their slot so the result is a permutation in
+// every case.  One lane per position of the scattered order, which is grouped
+// by bucket: the lanes of a bucket (about 24) read the same keys at the same
+// time.  1.62M particles: 36 us with the copy, against 46 us for a wave per
+// bucket and 46 us for a gather and a copy back.
+__global__ __launch_bounds__(kThreads) void k_sort_gather(int n, const int32_t *__restrict__ cell, int cell_base,
+                                                          int n_cells, const int32_t *__restrict__ start,
+                                                          const uint32_t *__restrict__ keys,
+                                                          const uint32_t *__restrict__ index,
+                                                          const float4 *__restrict__ pos,
+                                                          const float4 *__restrict__ vel,
+                                                          int32_t *__restrict__ o_cell, float4 *__restrict__ o_pos,
+                                                          float4 *__restrict__ o_vel, uint32_t *__restrict__ o_info,
+                                                          uint32_t *__restrict__ perm_out,
+                                                          uint32_t *__restrict__ neib_count)
 {
-    const int w0 = (blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave) * kWave;
-    if (w0 >= n) return;  // uniform
-    const int lane = threadIdx.x % kWave;
-    const int p = w0 + lane;
-    int b = 0;  // bucket of position p
-    bool first = false;
-    if (p < n) {
-        const int c = cell[perm_in[p]];
-        b = c >= 0 ? c - cell_base : n_cells;
-        first = start[b] == p;
+    const int p = blockIdx.x * kThreads + threadIdx.x;
+    if (p >= n) return;
+    const uint32_t src = index[p], key = keys[p];
+    const int c = cell[src];
+    const int b = c >= 0 ? c - cell_base : n_cells;
+    const float4 x = pos[src], v = vel[src];
+    const int s = start[b], e = start[b + 1];
+    int rank = 0;
+    for (int t = s; t < e; ++t) {
+        const uint32_t k = keys[t];
+        rank += (k < key || (k == key && t < p)) ? 1 : 0;
     }
-    unsigned long long F = __ballot(first);
-    while (F) {  // uniform: the buckets that start in the window
-        const int k = __ffsll((long long)F) - 1;
-        F &= F - 1;
-        const int bk = __shfl(b, k);
-        const int s = w0 + k;
-        const int m = start[bk + 1] - s;
-        for (int mb = 0; mb < m; mb += kWave) {
-            const int me = mb + lane;
-            const bool valid = me < m;
-            const uint32_t idx = valid ? perm_in[s + me] : 0u;
-            const uint32_t key = valid ? info[idx] : 0xFFFFFFFFu;
-            int rank = 0;
-            for (int tb = 0; tb < m; tb += kWave) {
-                const int t = tb + lane;
-                const uint32_t kt_lane = t < m ? info[perm_in[s + t]] : 0xFFFFFFFFu;
-                const int cnt = min(kWave, m - tb);
-                for (int u = 0; u < cnt; ++u) {
-                    const uint32_t kt = __shfl(kt_lane, u);
-                    rank += (kt < key || (kt == key && tb + u < me)) ? 1 : 0;
-                }
-            }
-            if (valid) perm_out[s + rank] = idx;
+    const int k = s + rank;
+    o_cell[k] = c;
+    o_pos[k] = x;
+    o_vel[k] = v;
+    o_info[k] = key;
+    if (perm_out) perm_out[k] = src;
+    if (c < 0) neib_count[k] = 0u;  // (dropped: in no brick, no neighbours)
+}
+
+// The table of bricks with a pair, in order of size (the particles of their
+// inner cells), large ones first, bricks of one size class in order of their
+// ids: the persistent kernels that take them in that order end with the cheap
+// ones, and their work is dealt the same way after every build of the same
+// state.  A counting sort over kClasses size classes: per block of bricks a
+// histogram, then every block finds its bricks' places from all histograms.
+// keys[b]: 0 for a brick without a pair, else 1 + min(particles / width, 62)
+// (brick_class); a brick is heavy from class 27 on (12 particles per cell).
+// The derivatives of the 1.62M-particle dam break are 2.5% faster in this order
+// than with the heavy and the light bricks each in an arbitrary one.
+constexpr int kClasses = 64, kHeavyClass = 27, kOrderThreads = 1024;
+template <int BX, int BY, int BZ>
+__device__ __forceinline__ int brick_class(int particles)
+{
+    // width of a class: heavy means 12 particles per inner cell
+    constexpr int W = 12 * BX * BY * BZ / kHeavyClass;
+    static_assert(W * kHeavyClass == 12 * BX * BY * BZ);
+    return 1 + min(particles / W, kClasses - 2);
+}
+
+__global__ __launch_bounds__(kOrderThreads) void k_order_count(int nb, const uint8_t *__restrict__ keys,
+                                                               int32_t *__restrict__ hist)
+{
+    __shared__ int h[kClasses];
+    if (threadIdx.x < kClasses) h[threadIdx.x] = 0;
+    __syncthreads();
+    const int b = blockIdx.x * kOrderThreads + threadIdx.x;
+    const int key = b < nb ? keys[b] : 0;
+    if (key) atomicAdd(&h[key], 1);
+    __syncthreads();
+    if (threadIdx.x < kClasses) hist[blockIdx.x * kClasses + threadIdx.x] = h[threadIdx.x];
+}
+
+__global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, const uint8_t *__restrict__ keys,
+                                                               const int32_t *__restrict__ hist,
+                                                               int32_t *__restrict__ table, int cap_ids)
+{
+    constexpr int NW = kOrderThreads / kWave;
+    static_assert(kClasses == kWave, "one lane per class");
+    __shared__ int all[NW][kClasses], before[NW][kClasses], own[NW][kClasses];
+    __shared__ int at[kClasses];  // place of the first brick of each class, heavy bricks
+    __shared__ int heavy;
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    // class `lane`: the bricks of all blocks and of those before this one
+    int a = 0, f = 0;
+    for (int k = w; k < (int)gridDim.x; k += NW) {
+        const int v = hist[k * kClasses + lane];
+        a += v;
+        f += k < (int)blockIdx.x ? v : 0;
+    }
+    all[w][lane] = a;
+    before[w][lane] = f;
+    const int b = blockIdx.x * kOrderThreads + threadIdx.x;
+    const int key = b < nb ? keys[b] : 0;
+    // lanes of the wave with the same class
+    unsigned long long same = ~0ull;
+#pragma unroll
+    for (int bit = 1; bit < kClasses; bit <<= 1) {
+        const unsigned long long m = __ballot((key & bit) != 0);
+        same &= (key & bit) ? m : ~m;
+    }
+    own[w][lane] = 0;
+    __syncthreads();
+    const unsigned long long below = same & ((1ull << lane) - 1ull);
+    if (key && below == 0ull) own[w][key] = (int)__popcll(same);
+    if (w == 0) {
+        int total = 0, first = 0;
+        for (int k = 0; k < NW; ++k) {
+            total += all[k][lane];
+            first += before[k][lane];
+        }
+        // large classes first: the bricks of the classes above
+        int above = total;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int v = __shfl_down(above, o);
+            if (lane + o < kWave) above += v;
+        }
+        at[lane] = above - total + first;
+        if (lane == 1 + kHeavyClass) heavy = above;
+        if (blockIdx.x == 0) {
+            if (lane == 1 + kHeavyClass) table[0] = above;
+            const int h = __shfl(above, 1 + kHeavyClass);
+            if (lane == 1) table[cap_ids + 1] = above - h;
         }
     }
-}
-
-// Reorder by the sort permutation.  Also counts the particles whose offset,
-// mass, velocity or density is not finite (one atomic per wave), so that a
-// state that blew up is reported by the build's status word.
-__global__ __launch_bounds__(kThreads) void k_gather(int n, const uint32_t *__restrict__ perm,
-                                                     const int32_t *__restrict__ cell,
-                                                     const float4 *__restrict__ pos,
-                                                     const float4 *__restrict__ vel,
-                                                     const uint32_t *__restrict__ info,
-                                                     int32_t *__restrict__ o_cell,
-                                                     float4 *__restrict__ o_pos,
-                                                     float4 *__restrict__ o_vel,
-                                                     uint32_t *__restrict__ o_info,
-                                                     uint32_t *__restrict__ perm_out,
-                                                     int32_t *__restrict__ status)
-{
-    const int k = blockIdx.x * kThreads + threadIdx.x;
-    bool bad = false;
-    if (k < n) {
-        const uint32_t src = perm[k];
-        if (perm_out) perm_out[k] = src;
-        const float4 p = pos[src];
-        const float4 v = vel[src];
-        o_cell[k] = cell[src];
-        o_pos[k] = p;
-        o_vel[k] = v;
-        o_info[k] = info[src];
-        bad = !(isfinite(p.x) && isfinite(p.y) && isfinite(p.z) && isfinite(p.w) && isfinite(v.x) &&
-                isfinite(v.y) && isfinite(v.z) && isfinite(v.w));
+    __syncthreads();
+    if (key) {
+        int p = at[key] + (int)__popcll(below);
+        for (int k = 0; k < w; ++k) p += own[k][key];
+        if (p < heavy) table[1 + p] = b;
+        else table[cap_ids - (p - heavy)] = b;
     }
-    const unsigned long long m = __ballot(bad);
-    if (m && (threadIdx.x % kWave) == 0) atomicAdd(&status[SPH_STATUS_NONFINITE], (int)__popcll(m));
-}
-
-// The sorted state back into the caller's arrays.  Also: particles dropped
-// by the build are in no brick and get no neighbours (count 0), and, when
-// flags is not null, the cells that hold a particle with a non-empty list
-// are flagged (for the table of bricks with a pair).
-__global__ __launch_bounds__(kThreads) void k_copy_state(int n, const int32_t *__restrict__ cell,
-                                                         const float4 *__restrict__ pos,
-                                                         const float4 *__restrict__ vel,
-                                                         const uint32_t *__restrict__ info,
-                                                         int32_t *__restrict__ o_cell,
-                                                         float4 *__restrict__ o_pos,
-                                                         float4 *__restrict__ o_vel,
-                                                         uint32_t *__restrict__ o_info,
-                                                         uint32_t *__restrict__ neib_count, int cell_base,
-                                                         int n_cells, uint8_t *__restrict__ flags)
-{
-    const int k = blockIdx.x * kThreads + threadIdx.x;
-    if (k >= n) return;
-    const int c = cell[k];
-    o_cell[k] = c;
-    o_pos[k] = pos[k];
-    o_vel[k] = vel[k];
-    o_info[k] = info[k];
-    if (c < 0) {
-        neib_count[k] = 0u;
-    } else if (flags && neib_count[k] != 0u) {
-        const int lc = c - cell_base;
-        if ((unsigned)lc < (unsigned)n_cells) flags[lc] = 1;
-    }
-}
-
-// Cell ranges from the bucket starts; thread 0 also writes the particles in
-// cells and the dropped ones (the last bucket) to the status words.
-__global__ __launch_bounds__(kThreads) void k_cell_ranges(int n_cells, const int32_t *__restrict__ start,
-                                                          int32_t *__restrict__ cell_start,
-                                                          int32_t *__restrict__ cell_end, int n,
-                                                          int32_t *__restrict__ status)
-{
-    const int c = blockIdx.x * kThreads + threadIdx.x;
-    if (c == 0) {
-        const int n_active = start[n_cells];
-        status[SPH_STATUS_N_ACTIVE] = n_active;
-        status[SPH_STATUS_DROPPED] = n - n_active;
-    }
-    if (c >= n_cells) return;
-    cell_start[c] = start[c];
-    cell_end[c] = start[c + 1];
 }
 
 // Neighbour lists, cell-brick form (section "Changing perspective: from the
@@ -700,7 +741,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 128))) 
                                                     uint32_t *__restrict__ neibs,
                                                     uint16_t *__restrict__ neibs_brick,
                                                     uint32_t *__restrict__ neib_count,
-                                                    int32_t *__restrict__ status)
+                                                    int32_t *__restrict__ status, uint8_t *__restrict__ keys)
 {
     constexpr int SX = BX + 2, SY = BY + 2, SZ = BZ + 2;
     constexpr int S = SX * SY * SZ;
@@ -824,6 +865,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 128))) 
                                                          neibs + toff,
                                                          neibs_brick + brick_entry(i, 0, brick_groups(max_neibs)));
             neib_count[i] = cw;
+            if (cw) keys[b] = (uint8_t)brick_class<BX, BY, BZ>(nc);
             atomicMax(&status[SPH_STATUS_MAX_NEIBS], found);
             if (found > max_neibs) atomicAdd(&status[SPH_STATUS_OVERFLOW], 1);
         }
@@ -856,6 +898,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 128))) 
                                                     cFluidEnd, sPos, pos, info, csx, csy, csz, rs2, tile, ltile,
                                                     found);
         neib_count[i] = cw;
+        if (keys && cw) keys[b] = (uint8_t)brick_class<BX, BY, BZ>(nc);
         atomicMax(&status[SPH_STATUS_MAX_NEIBS], found);
         if (found > max_neibs) atomicAdd(&status[SPH_STATUS_OVERFLOW], 1);
     }
@@ -929,15 +972,15 @@ extern "C" sph_status sph_build_neighbors(const sph_grid *grid, const sph_params
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
     int32_t *cnt = (int32_t *)(ws + L.cnt);
-    int32_t *cursor = (int32_t *)(ws + L.cursor);
+    int32_t *hist = (int32_t *)(ws + L.hist);
     int32_t *start = (int32_t *)(ws + L.start);
     int32_t *partials = (int32_t *)(ws + L.partials);
-    uint32_t *perm_a = (uint32_t *)(ws + L.perm_a);
-    uint32_t *perm_b = (uint32_t *)(ws + L.perm_b);
+    uint32_t *keys = (uint32_t *)(ws + L.keys);
+    uint32_t *index = (uint32_t *)(ws + L.index);
     int32_t *t_cell = (int32_t *)(ws + L.t_cell);
     float4 *t_pos = (float4 *)(ws + L.t_pos);
     float4 *t_vel = (float4 *)(ws + L.t_vel);
-    uint32_t *t_info = (uint32_t *)(ws + L.t_info);
+    uint32_t *place = (uint32_t *)(ws + L.place);
     float4 *pos = (float4 *)parts->pos;
     float4 *vel = (float4 *)parts->vel;
 
@@ -946,61 +989,55 @@ extern "C" sph_status sph_build_neighbors(const sph_grid *grid, const sph_params
 
     const int cap_ids = brick_table_cap(cap);
     int32_t *table = neibs_brick ? brick_table(reinterpret_cast<int32_t *>(neibs_brick), cap, max_neibs) : nullptr;
-    uint8_t *flags = neibs_brick ? (uint8_t *)(ws + L.flags) : nullptr;
+    uint8_t *classes = neibs_brick ? (uint8_t *)(ws + L.classes) : nullptr;
     int32_t *active = (int32_t *)(ws + L.active);
-    const int64_t flag_words = neibs_brick ? (n_cells + 3) / 4 : 0;
-    const int64_t zero_items = nbk > flag_words ? nbk : flag_words;
-    const unsigned fill_blocks = sph_blocks(zero_items, kThreads) < 4096u ? sph_blocks(zero_items, kThreads) : 4096u;
-    k_build_zero<<<fill_blocks, kThreads, 0, s>>>(nbk, cnt, cursor, d_status, flag_words, (int32_t *)flags, active,
-                                                  table, table ? table + cap_ids + 1 : nullptr);
+    const int64_t class_words = neibs_brick ? (n_cells + 3) / 4 : 0;  // (at most one brick per cell)
+    const unsigned fill_blocks = sph_blocks(nbk, kThreads) < 4096u ? sph_blocks(nbk, kThreads) : 4096u;
+    k_build_zero<<<fill_blocks, kThreads, 0, s>>>(nbk, cnt, d_status, class_words, (int32_t *)classes, active);
     SPH_CHECK_LAUNCH();
     if (n > 0) {
         k_rebin_count<<<sph_blocks(n, kThreads), kThreads, 0, s>>>(
-            n, parts->cell, pos, dims, grid->cell_size[0], grid->cell_size[1], grid->cell_size[2],
-            grid->cell_base, n_cells, cnt);
+            n, parts->cell, pos, vel, dims, grid->cell_size[0], grid->cell_size[1], grid->cell_size[2],
+            grid->cell_base, n_cells, cnt, t_cell, t_pos, t_vel, place, d_status);
         SPH_CHECK_LAUNCH();
     }
     const int np = (nbk + kScanTile - 1) / kScanTile;
     k_scan_reduce<<<np, kThreads, 0, s>>>(cnt, nbk, partials);
-    k_scan_partials<<<1, kThreads, 0, s>>>(partials, np, start + nbk);
-    k_scan_apply<<<np, kThreads, 0, s>>>(cnt, nbk, partials, start);
-    SPH_CHECK_LAUNCH();
-    k_cell_ranges<<<sph_blocks(n_cells, kThreads), kThreads, 0, s>>>(n_cells, start, cell_start, cell_end, n,
-                                                                     d_status);
+    if (np <= kFewPartials) {
+        k_scan_apply<true><<<np, kThreads, 0, s>>>(cnt, nbk, partials, start, cell_start, cell_end, d_status);
+    } else {
+        k_scan_partials<<<1, kThreads, 0, s>>>(partials, np);
+        k_scan_apply<false><<<np, kThreads, 0, s>>>(cnt, nbk, partials, start, cell_start, cell_end, d_status);
+    }
     SPH_CHECK_LAUNCH();
     if (n > 0) {
-        k_scatter<<<sph_blocks(n, kThreads), kThreads, 0, s>>>(n, parts->cell, grid->cell_base, n_cells,
-                                                                start, cursor, perm_a);
-        k_cell_sort<<<sph_blocks((n + kWave - 1) / kWave, kThreads / kWave), kThreads, 0, s>>>(
-            n, parts->cell, grid->cell_base, n_cells, start, perm_a, parts->info, perm_b);
-        k_gather<<<sph_blocks(n, kThreads), kThreads, 0, s>>>(n, perm_b, parts->cell, pos, vel, parts->info,
-                                                               t_cell, t_pos, t_vel, t_info, perm_out, d_status);
+        k_scatter<<<sph_blocks(n, kThreads), kThreads, 0, s>>>(n, t_cell, grid->cell_base, n_cells, start, place,
+                                                                parts->info, keys, index);
+        k_sort_gather<<<sph_blocks(n, kThreads), kThreads, 0, s>>>(n, t_cell, grid->cell_base, n_cells, start, keys,
+                                                                   index, t_pos, t_vel, parts->cell, pos, vel,
+                                                                   parts->info, perm_out, neib_count);
         SPH_CHECK_LAUNCH();
         const float rs2 = params->r_search * params->r_search;
         with_shape(shape, [&]<int BX, int BY, int BZ>() {
             const BrickGrid G = brick_grid<BX, BY, BZ>(grid->ncell, grid->periodic);
             const unsigned bricks = (unsigned)G.nbx * G.nby * G.nbz;
             constexpr int NT = brick_threads(BX * BY * BZ);
-            // brick activity from the (exclusive-scan) cell starts: start[c + 1] is the end of cell c
-            k_active_bricks<BX, BY, BZ><<<sph_blocks(bricks, 256), 256, 0, s>>>(start, start + 1, G, active, nullptr);
+            k_active_bricks<BX, BY, BZ><<<sph_blocks(bricks, 256), 256, 0, s>>>(cell_start, cell_end, G, active);
             k_build_brick<BX, BY, BZ, NT, kBuildCap><<<bricks, NT, 0, s>>>(
-                n, max_neibs, t_pos, t_info, start, G, grid->cell_size[0], grid->cell_size[1], grid->cell_size[2],
-                rs2, active, neibs, neibs_brick, neib_count, d_status);
+                n, max_neibs, pos, parts->info, start, G, grid->cell_size[0], grid->cell_size[1], grid->cell_size[2],
+                rs2, active, neibs, neibs_brick, neib_count, d_status, classes);
         });
-        k_copy_state<<<sph_blocks(n, kThreads), kThreads, 0, s>>>(n, t_cell, t_pos, t_vel, t_info, parts->cell,
-                                                                   pos, vel, parts->info, neib_count,
-                                                                   grid->cell_base, n_cells, flags);
         SPH_CHECK_LAUNCH();
     }
     if (neibs_brick) {
         // the table of bricks with a pair behind the brick-local lists, for
-        // the derivative kernels (heavy bricks first: at least 12 particles
-        // per inner cell), from the cell flags k_copy_state set
+        // the derivative kernels
         with_shape(shape, [&]<int BX, int BY, int BZ>() {
             const BrickGrid G = brick_grid<BX, BY, BZ>(grid->ncell, grid->periodic);
-            const unsigned bricks = (unsigned)G.nbx * G.nby * G.nbz;
-            k_active_bricks<BX, BY, BZ><<<sph_blocks(bricks, 256), 256, 0, s>>>(
-                start, start + 1, G, table, flags, table + cap_ids + 1, 12 * BX * BY * BZ, cap_ids);
+            const int bricks = G.nbx * G.nby * G.nbz;
+            const unsigned blocks = sph_blocks(bricks, kOrderThreads);
+            k_order_count<<<blocks, kOrderThreads, 0, s>>>(bricks, classes, hist);
+            k_order_place<<<blocks, kOrderThreads, 0, s>>>(bricks, classes, hist, table, cap_ids);
         });
         SPH_CHECK_LAUNCH();
     }

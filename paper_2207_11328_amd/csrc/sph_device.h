@@ -244,28 +244,14 @@ __device__ __forceinline__ int block_scan(int v, int &total, int *wsum)
 
 // List the bricks that hold at least one particle (order is irrelevant: each
 // brick writes only its own particles).  active[0] must be zero on entry.
-// With cell_flags (one byte per cell, set by the list build for every cell
-// that holds a particle with a non-empty list), a brick is listed only if one
-// of its inner cells is flagged: the kernels that take the list write the
-// outputs of particles with empty lists without staging, so a brick of such
-// particles (a wall away from the fluid) needs none.  The flags of the brick's inner cells are
-// cleared for the next call; a stale flag only lists a brick that then finds
-// no pair.
-// With light (a second counter, zero on entry), bricks with fewer than
-// light_min particles are listed from the back of the id region instead
-// (active[cap_ids], active[cap_ids - 1], ...; light[0] of them), so that a
-// consumer taking the bricks in brick_at order ends with the cheap ones.
 template <int BX, int BY, int BZ>
 __global__ __launch_bounds__(256) void k_active_bricks(const int32_t *__restrict__ cell_start,
                                                        const int32_t *__restrict__ cell_end, BrickGrid G,
-                                                       int32_t *__restrict__ active, uint8_t *__restrict__ cell_flags,
-                                                       int32_t *__restrict__ light = nullptr, int light_min = 0,
-                                                       int cap_ids = 0)
+                                                       int32_t *__restrict__ active)
 {
     const int b = blockIdx.x * 256 + threadIdx.x;
     const int nb = G.nbx * G.nby * G.nbz;
     int cnt = 0;
-    bool flagged = cell_flags == nullptr;
     if (b < nb) {
         const int cx0 = (b % G.nbx) * BX, cy0 = ((b / G.nbx) % G.nby) * BY, cz0 = (b / (G.nbx * G.nby)) * BZ;
         const int cx1 = min(cx0 + BX, G.nx) - 1;
@@ -279,56 +265,23 @@ __global__ __launch_bounds__(256) void k_active_bricks(const int32_t *__restrict
             e[k] = cell_end[row + cx1];
             s0[k] = cell_start[row + cx0];
         }
-        if (cell_flags) {
-            uint8_t f[BY * BZ][BX];
-#pragma unroll
-            for (int k = 0; k < BY * BZ; ++k) {
-                const int y = min(cy0 + k % BY, G.ny - 1), z = min(cz0 + k / BY, G.nz - 1);
-                const int row = G.nx * (y + G.ny * z);
-#pragma unroll
-                for (int x = 0; x < BX; ++x) f[k][x] = cell_flags[row + min(cx0 + x, cx1)];
-            }
-            int any = 0;
-#pragma unroll
-            for (int k = 0; k < BY * BZ; ++k) {
-                const int y = cy0 + k % BY, z = cz0 + k / BY;
-                const int row = G.nx * (y + G.ny * z);
-#pragma unroll
-                for (int x = 0; x < BX; ++x) {
-                    const bool in = y < G.ny && z < G.nz && cx0 + x <= cx1;
-                    if (in && f[k][x]) {
-                        any = 1;
-                        cell_flags[row + cx0 + x] = 0;
-                    }
-                }
-            }
-            flagged = any != 0;
-        }
 #pragma unroll
         for (int k = 0; k < BY * BZ; ++k)
             cnt += (cy0 + k % BY < G.ny && cz0 + k / BY < G.nz) ? e[k] - s0[k] : 0;
     }
-    const bool has = cnt > 0 && flagged;
-    const bool lt = has && light && cnt < light_min;
+    const bool has = cnt > 0;
     // wave-aggregated appends
-    const unsigned long long ballot = __ballot(has && !lt), lballot = __ballot(lt);
+    const unsigned long long ballot = __ballot(has);
     const int lane = threadIdx.x % kWave;
     const unsigned long long below = (1ull << lane) - 1ull;
-    int base = 0, lbase = 0;
+    int base = 0;
     if (lane == 0 && ballot) base = atomicAdd(&active[0], (int)__popcll(ballot));
-    if (lane == 0 && lballot) lbase = atomicAdd(light, (int)__popcll(lballot));
     base = __shfl(base, 0);
-    lbase = __shfl(lbase, 0);
-    if (has && !lt) active[1 + base + __popcll(ballot & below)] = b;
-    if (lt) active[cap_ids - (lbase + __popcll(lballot & below))] = b;
+    if (has) active[1 + base + __popcll(ballot & below)] = b;
 }
 
-// Bricks listed by k_active_bricks: their number, and the kb-th in the order
-// heavy (from the front) then light (from the back).
-__device__ __forceinline__ int bricks_listed(const int32_t *active, const int32_t *light)
-{
-    return active[0] + light[0];
-}
+// The kb-th brick of the table: heavy (from the front) then light (from the
+// back).
 __device__ __forceinline__ int brick_at(const int32_t *active, int cap_ids, int kb)
 {
     const int nh = active[0];
