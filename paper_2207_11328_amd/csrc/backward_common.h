@@ -11,6 +11,7 @@ struct BackConst {
     float csx, csy, csz;
     float rho0, inv_rho0, B, c0;
     float lim2, inv_h, inv_h2, fcoeff;
+    float neg_inv_2h, minus_8c, c12_h;  // Wendland in t = 1 - r/(2h): F = -8 c t^3, F'/r = 12 c t^2/(h r)
     float alpha_h, h, eps_h2, four_nu, k_four_nu, inv_c0;
     float diff;  // 2 delta h c0 (density diffusion)
     int max_neibs;
@@ -48,9 +49,9 @@ struct BackArgs {
     const int32_t *cell_start, *cell_end;
     const int32_t *table;  // bricks with a pair (brick_table layout), from the build
     int cap_ids;           // ids of the table
-    int32_t *next;         // brick counter and finished workgroups of the persistent workgroups (zeroed before)
+    int32_t *next;         // item counter and finished workgroups of the persistent workgroups (zeroed before)
     float4 *gpos, *gvel;
-    double *partial;  // per-block (gather) or per-brick parameter partials
+    double *partial;  // per-block (gather) or per-item (brick form) parameter partials
     double *grad_params;  // (brick form) the last workgroup to finish sums the partials into it
     int accumulate;
     bool bricks;

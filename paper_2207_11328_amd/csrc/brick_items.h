@@ -38,20 +38,27 @@ namespace sph {
 // 15.5k particles (27 bricks with a pair) takes 18.0 us in rows against 30.0
 // with whole bricks, the 169k-particle dam break (120) 35.8 us in halves
 // against 51.4 (cubic spline, Landrini-Morris, Morris viscosity, diffusion).
-template <int BY>
-__device__ __forceinline__ int brick_parts(int n, int wgs)
+// PAIRS: the time of a whole brick's pairs, LEAST: the parts below which no
+// item would fit in LDS, limit: the most items (there are slots for).
+template <int BY, int PAIRS, int LEAST>
+__device__ __forceinline__ int brick_parts(int n, int wgs, int limit)
 {
-    const int c1 = ((n + wgs - 1) / wgs) * 42;
-    int best = 1, cost = c1;
+    int best = 1, cost = ((n + wgs - 1) / wgs) * (10 + PAIRS);
     if constexpr (BY % 2 == 0 && BY > 2) {
-        const int c2 = ((2 * n + wgs - 1) / wgs) * (8 + 32 / 2);
-        if (c2 < cost) {
+        const int c2 = ((2 * n + wgs - 1) / wgs) * (8 + PAIRS / 2);
+        if (LEAST == 2 || c2 < cost) {
             best = 2;
             cost = c2;
         }
     }
-    const int c = ((BY * n + wgs - 1) / wgs) * (7 + 32 / BY);
-    return c < cost ? BY : best;
+    if (((BY * n + wgs - 1) / wgs) * (7 + PAIRS / BY) < cost) best = BY;
+    return best * n <= limit ? best : 1;
+}
+
+template <int BY, int PAIRS, int LEAST>
+__device__ __forceinline__ int item_parts(int n_listed, const BrickGrid &G)
+{
+    return brick_parts<BY, PAIRS, LEAST>(n_listed, gridDim.x, G.nx * G.ny * G.nz);
 }
 
 // Descriptor of an item.
@@ -103,7 +110,7 @@ __device__ __forceinline__ int lanes_scan(int v, int lane)
 // The next item into Q, by one wave: the rows left of item prev, else the next
 // part of a brick from the counter.  CAP: staged particles that fit in LDS;
 // NT: centrals that fit in the table.
-template <int BX, int BY, int BZ, int NT, int CAP>
+template <int BX, int BY, int BZ, int NT, int CAP, int PAIRS, int LEAST>
 __device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const BrickItem &prev, bool first, int lane,
                                              const int32_t *__restrict__ table, int cap_ids,
                                              int32_t *__restrict__ next, const int32_t *__restrict__ cell_start,
@@ -124,7 +131,7 @@ __device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const Br
         // counter (zeroed before the launch)
         const int heavy = table[0], n_listed = heavy + table[cap_ids + 1];
         const int guess = first ? table[1 + min((int)blockIdx.x, cap_ids - 1)] : 0;  // (sent for with the counts)
-        const int parts = brick_parts<BY>(n_listed, gridDim.x), items = n_listed * parts;
+        const int parts = item_parts<BY, PAIRS, LEAST>(n_listed, G), items = n_listed * parts;
         item = items;
         if (first) {
             item = blockIdx.x;
@@ -300,6 +307,132 @@ struct TableMaker {
         const int p = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)before));
         if (len > 0) T.cen[p] = entry | (uint32_t)len << kCenCountShift;
+    }
+};
+
+// ---- reading a brick's lists and staged particles ----------------------------
+
+// LDS by address (a 32-bit offset in the workgroup's LDS).
+typedef float vf4 __attribute__((ext_vector_type(4)));
+typedef float vf2 __attribute__((ext_vector_type(2)));
+template <typename T>
+using Lds = __attribute__((address_space(3))) T;
+template <typename T>
+__device__ __forceinline__ uint32_t lds_address(const T *p)
+{
+    return (uint32_t)(uintptr_t)(Lds<const T> *)p;
+}
+__device__ __forceinline__ float4 lds_float4(uint32_t a, int index)
+{
+    const vf4 v = ((Lds<const vf4> *)(uintptr_t)a)[index];
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float2 lds_float2(uint32_t a)
+{
+    const vf2 v = *(Lds<const vf2> *)(uintptr_t)a;
+    return make_float2(v.x, v.y);
+}
+
+// base + scale x (the 16-bit slot in half `hi` of w): one instruction, the
+// unpacking included.
+__device__ __forceinline__ uint32_t slot_address(uint32_t w, int hi, int scale, uint32_t base)
+{
+    uint32_t a;
+    if (scale == 16) {
+        if (hi) asm("v_mad_u32_u16 %0, %1, 16, %2 op_sel:[1,0,0,0]" : "=v"(a) : "v"(w), "s"(base));
+        else asm("v_mad_u32_u16 %0, %1, 16, %2" : "=v"(a) : "v"(w), "s"(base));
+    } else {
+        if (hi) asm("v_mad_u32_u16 %0, %1, 8, %2 op_sel:[1,0,0,0]" : "=v"(a) : "v"(w), "s"(base));
+        else asm("v_mad_u32_u16 %0, %1, 8, %2" : "=v"(a) : "v"(w), "s"(base));
+    }
+    return a;
+}
+
+// Lanes per central, and the entries one of them takes at a time.
+constexpr int kLanes = 4, kEntries = kBrickGroup;
+typedef uint32_t Entries __attribute__((ext_vector_type(4)));
+// group e of a brick-local list, lg its group 0
+__device__ __forceinline__ Entries list_entries(const uint4 *lg, int e)
+{
+    return load_at((const Entries *)lg, e * kWave);
+}
+// Two slots of a list relative to the first staged one, kept inside the staged
+// range (a stale list gives wrong numbers but no access past it).
+__device__ __forceinline__ uint32_t staged_slots(uint32_t w, uint32_t lo2, uint32_t max2)
+{
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    const us2 d = __builtin_elementwise_sub_sat(__builtin_bit_cast(us2, w), __builtin_bit_cast(us2, lo2));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(d, __builtin_bit_cast(us2, max2)));
+}
+
+// The sum of a value over the lanes of a central, in all of them.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lanes_sum(float v)
+{
+    v += dpp<0xB1>(v);  // quad lanes 1, 0, 3, 2
+    v += dpp<0x4E>(v);  // quad lanes 2, 3, 0, 1
+    return v;
+}
+
+// The brick-local list of particle i (brick_entry(i, 0, groups)): group g at
+// [g * kWave].
+__device__ __forceinline__ const uint4 *list_groups(const uint16_t *__restrict__ neibs_brick, int i, uint32_t groups)
+{
+    const uint32_t u = (uint32_t)i;
+    return (const uint4 *)((const char *)neibs_brick + (uint64_t)(u / kWave) * (groups * (kWave * 16u)) +
+                           (u % kWave) * 16u);
+}
+
+// Staged rows of cells of an item (SX x-consecutive cells: one contiguous LDS
+// range and, away from a periodic seam, one contiguous global range): wave w
+// takes rows w and w + NW.
+template <int BX, int BY, int BZ, int NW>
+struct StagedRows {
+    using St = Staging<BX, BY, BZ>;
+    static constexpr int SX = St::SX, SZ = St::SZ, ROWS = 2;
+    static_assert(St::SY * SZ <= ROWS * NW, "two rows per wave hold every row");
+    int row[ROWS], slot[ROWS], len[ROWS];  // row, its first slot (from s_lo), its particles
+
+    __device__ __forceinline__ void locate(const BrickScans<BX, BY, BZ> &B, int wave)
+    {
+        const bool staged = __builtin_amdgcn_readfirstlane(B.d.item) >= 0 && __builtin_amdgcn_readfirstlane(B.d.lds);
+        const int R0 = __builtin_amdgcn_readfirstlane(B.d.ya * SZ), R1 = __builtin_amdgcn_readfirstlane((B.d.yb + 2) * SZ);
+#pragma unroll
+        for (int k = 0; k < ROWS; ++k) {
+            row[k] = min(R0 + wave + k * NW, R1 - 1);
+            const int b0 = __builtin_amdgcn_readfirstlane(B.base[row[k] * SX]);
+            slot[k] = b0 - __builtin_amdgcn_readfirstlane(B.d.s_lo);
+            const int l = __builtin_amdgcn_readfirstlane(B.base[row[k] * SX + SX]) - b0;
+            len[k] = staged && R0 + wave + k * NW < R1 ? l : 0;
+        }
+    }
+    // Index of particle t of row k, and its cell along x from the brick's
+    // centre cell (t past the row's end: particle 0).
+    __device__ __forceinline__ int particle(const BrickScans<BX, BY, BZ> &B, int k, int t, int &cx) const
+    {
+        const int *base = B.base + row[k] * SX, *delta = B.delta + row[k] * SX;
+        const int s = base[0] + t;
+        int d = delta[0];
+        cx = -2;
+#pragma unroll
+        for (int m = 1; m < SX; ++m) {
+            const bool past = s >= base[m];
+            cx += past ? 1 : 0;
+            d = past ? delta[m] : d;
+        }
+        return t < len[k] ? s - d : 0;
+    }
+    // Position of a particle of row k relative to the centre cell of the whole
+    // brick (cx along x).
+    __device__ __forceinline__ float4 brick_relative(const float4 &p, int k, int cx, float csx, float csy, float csz,
+                                                     float w) const
+    {
+        return make_float4(fmaf((float)cx, csx, p.x), fmaf((float)(row[k] / SZ - 2), csy, p.y),
+                           fmaf((float)(row[k] % SZ - 2), csz, p.z), w);
     }
 };
 

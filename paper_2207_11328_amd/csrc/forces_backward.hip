@@ -8,7 +8,6 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
-#include <algorithm>
 
 #include "backward_common.h"
 
@@ -28,17 +27,13 @@ __global__ __launch_bounds__(kThreads) void k_eos_grad(int n, const float4 *__re
     if (i < n) aux[i] = eos_grad_terms(vel[i].w, C);
 }
 
-// Brick form: clears what the brick kernel counts and sums into, its two
-// counters (next) and the nbp per-brick parameter partials.
-__global__ __launch_bounds__(kThreads) void k_back_clear(int32_t *__restrict__ next, double *__restrict__ bpartial,
-                                                         int nbp)
+// Brick form: clears the brick kernel's two counters.
+__global__ void k_back_clear(int32_t *__restrict__ next)
 {
-    const int i = blockIdx.x * kThreads + threadIdx.x;
-    for (int k = i; k < nbp; k += gridDim.x * kThreads) bpartial[k] = 0.0;
-    if (i < 2) next[i] = 0;
+    if (threadIdx.x < 2) next[threadIdx.x] = 0;
 }
 
-// Sum of the per-block (or per-brick) parameter partials in a fixed order:
+// Gather form: sum of the per-block parameter partials in a fixed order:
 // thread t adds partials t, t + 1024, ... (four running sums, combined in a
 // fixed order), then a fixed tree over the threads.
 constexpr int kReduceThreads = 1024;
@@ -60,8 +55,8 @@ __global__ __launch_bounds__(kThreads) void k_unpermute(int n, const uint32_t *_
 
 size_t aux_bytes(int64_t cap) { return (size_t)((16 * cap + 255) & ~(int64_t)255); }
 size_t partial_bytes(int64_t cap) { return (size_t)(3 * 8 * ((cap + kThreads - 1) / kThreads) + 256); }
-// per-brick parameter partials (at most one brick per cell) and the brick
-// counter
+// parameter partials of the brick form's items (at most as many as cells) and
+// its counters
 size_t brick_bytes(int64_t n_cells) { return (size_t)(3 * 8 * (n_cells + 1) + 256); }
 
 }  // namespace
@@ -113,6 +108,9 @@ extern "C" sph_status sph_forces_backward(const sph_grid *grid, const sph_params
     C.inv_h = (float)(1.0 / h);
     C.inv_h2 = (float)(1.0 / (h * h));
     C.fcoeff = (float)kernel_coeff(p->kernel, h);
+    C.neg_inv_2h = -0.5f * C.inv_h;
+    C.minus_8c = -8.0f * C.fcoeff;
+    C.c12_h = 12.0f * C.fcoeff * C.inv_h;
     C.alpha_h = (float)((double)p->alpha * h);
     C.h = p->h;
     C.eps_h2 = (float)((double)p->eps_visc * h * h);
@@ -135,16 +133,8 @@ extern "C" sph_status sph_forces_backward(const sph_grid *grid, const sph_params
     const int model = model_of(p);
     int n_partials = 0;
     if (n > 0) {
-        // bricks of the grid (one parameter partial each)
-        int n_bricks = 0;
-        with_shape(shape, [&]<int BX, int BY, int BZ>() {
-            const BrickGrid G = brick_grid<BX, BY, BZ>(grid->ncell, grid->periodic);
-            n_bricks = G.nbx * G.nby * G.nbz;
-        });
         if (bricks) {
-            const int nbp = 3 * n_bricks;
-            const unsigned cb = (unsigned)std::min(std::max((nbp + kThreads - 1) / kThreads, 1), 256);
-            k_back_clear<<<cb, kThreads, 0, s>>>(next, bpartial, nbp);
+            k_back_clear<<<1, kWave, 0, s>>>(next);
         } else {
             k_eos_grad<<<nblocks, kThreads, 0, s>>>(n, (const float4 *)parts->vel, aux, C);
         }

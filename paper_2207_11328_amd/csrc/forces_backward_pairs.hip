@@ -36,6 +36,7 @@
 #include <math.h>
 
 #include "backward_common.h"
+#include "brick_items.h"
 
 #ifndef SPH_KERNEL_KIND
 #error "compile with SPH_KERNEL_KIND set to one of the SPH_KERNEL_* values"
@@ -54,34 +55,49 @@ struct BackAcc {
 
 // aux: xi = (p or P, c, dp/drho or dP/drho, dc/drho) of the central; xj = (p
 // or P, c) of the neighbour.  pair_fluid: both are fluid (density diffusion).
+// in: 1 inside the list, 0 past its end.
 // MASKED: a pair outside the support or past the list has F and F'/r set to
 // zero and is accumulated anyway (every term is a finite factor times one of
 // them, so it adds +-0; the LDS loop only stages real particles, so every
 // factor is finite); otherwise a branch skips it.  The LDS loop takes the
 // masked form except with density diffusion, whose longer pair body spills
-// when it runs for every slot.
+// when it runs for every slot.  For the Wendland kernel the mask is the clamp
+// to [0, 1] of t = in - r/(2h), which is 1 - q/2 inside the list: F = -8 c t^3
+// and F'/r = 12 c t^2/(h r) vanish with it.
 template <int MODEL, bool MASKED>
 __device__ __forceinline__ void pair_adjoint_core(BackAcc &G, float xx, float xy, float xz, float mi,
                                                   const float4 &vi, const float4 &xi, const float4 &gi, float mj,
-                                                  const float4 &vj, const float2 &xj, const float4 &gj, bool valid,
+                                                  const float4 &vj, const float2 &xj, const float4 &gj, float in,
                                                   bool pair_fluid, const BackConst &C)
 {
     constexpr int KER = model_kernel(MODEL);
+    // (the Wendland masked form has no decision on r^2: fused, and kept off
+    // zero, so that a slot past the list that holds the central itself gives
+    // zeros and not 0 x inf; the others round it as the list predicate does)
+    constexpr bool CLAMPED = MASKED && KER == SPH_KERNEL_WENDLAND;
     float r2;
-    {
+    if constexpr (CLAMPED) {
+        r2 = fmaxf(fmaf(xx, xx, fmaf(xy, xy, xz * xz)), 1e-30f);
+    } else {
 #pragma clang fp contract(off)
         r2 = (xx * xx + xy * xy) + xz * xz;
     }
-    bool inter = valid && (r2 < C.lim2);
+    bool inter = in > 0.0f && r2 < C.lim2;
     if constexpr (KER == SPH_KERNEL_QUADRATIC) inter = inter && r2 > 0.0f;  // its F is unbounded at r = 0
     // 1/r from one reciprocal square root, r = r^2/r
     const float inv_r = __builtin_amdgcn_rsqf(r2);
     const float r = r2 * inv_r;
     float F, Fp_r;  // F and F'(r)/r
-    kernel_F_dF<KER>(C.fcoeff, r, r2, inv_r, C.inv_h, C.inv_h2, F, Fp_r);
-    if (MASKED) {
-        F = inter ? F : 0.0f;
-        Fp_r = inter ? Fp_r : 0.0f;
+    if constexpr (CLAMPED) {
+        const float t = __builtin_amdgcn_fmed3f(fmaf(r, C.neg_inv_2h, in), 0.0f, 1.0f), t2 = t * t;
+        F = t2 * (t * C.minus_8c);
+        Fp_r = t2 * (C.c12_h * inv_r);
+    } else {
+        kernel_F_dF<KER>(C.fcoeff, r, r2, inv_r, C.inv_h, C.inv_h2, F, Fp_r);
+        if (MASKED) {
+            F = inter ? F : 0.0f;
+            Fp_r = inter ? Fp_r : 0.0f;
+        }
     }
     const float ux = vi.x - vj.x, uy = vi.y - vj.y, uz = vi.z - vj.z;
     const float w = fmaf(ux, xx, fmaf(uy, xy, uz * xz));
@@ -93,15 +109,16 @@ __device__ __forceinline__ void pair_adjoint_core(BackAcc &G, float xx, float xy
     const float inv_rs = dd * inv_rsd;
     const float inv_d = rs * inv_rsd;
     const float csum = xi.y + xj.y;
-    // Pi = -alpha h min(w, 0)/d (c_i + c_j)/rs = A B with A = -alpha h min(w, 0)/d
-    // (zero for w >= 0, and so are Pi and its rho_i derivative) and B = csum/rs
-    const float mwd = fminf(w, 0.0f) * inv_d;
+    // Pi = -alpha h min(w, 0)/d (c_i + c_j)/rs = -alpha h (m/d) B with m =
+    // min(w, 0) (zero for w >= 0, and so are Pi and its derivatives) and B =
+    // csum/rs; act/d: 1/d for w < 0, else 0
+    const float act_d = w < 0.0f ? inv_d : 0.0f;
+    const float mwd = w * act_d;
     const float B = csum * inv_rs;
-    const float A = -C.alpha_h * mwd;
-    const float Pi = A * B;
-    const float actK = w < 0.0f ? -C.alpha_h * B : 0.0f;
-    // dPi/drho_i = A (dc_i/drho_i - B)/rs
-    const float dPi_dri = A * (xi.w - B) * inv_rs;
+    const float mB = mwd * B;
+    const float Pi = -C.alpha_h * mB;
+    // dPi/drho_i = -alpha h (m/d) (dc_i/drho_i - B)/rs
+    const float dPi_dri = -C.alpha_h * mwd * (xi.w - B) * inv_rs;
     // 1/(rho_i rho_j), 1/rho_i and 1/rho_j from one reciprocal (Landrini-Morris;
     // the density diffusion alone takes them in its branch)
     [[maybe_unused]] float inv_rr = 0.0f, iri = 0.0f, irj = 0.0f;
@@ -137,8 +154,8 @@ __device__ __forceinline__ void pair_adjoint_core(BackAcc &G, float xx, float xy
     }
     // d/do_i = ka da + kx x + ku u, d/du_i = ku x (+ the laminar terms)
     const float t = w * inv_d;
-    const float cu = F * actK * inv_d;
-    const float cx = fmaf(-2.0f * t, cu, S * Fp_r);  // S F'/r - 2 F actK w/d^2
+    const float cu = F * (-C.alpha_h * B * act_d);
+    const float cx = fmaf(-2.0f * t, cu, S * Fp_r);  // S F'/r - 2 F act K w/d^2
     float kx = fmaf(-dA, cx, sD * w * Fp_r);
     float ku = fmaf(-dA, cu, sD * F);
     float ka = -S * F;
@@ -161,8 +178,8 @@ __device__ __forceinline__ void pair_adjoint_core(BackAcc &G, float xx, float xy
     if constexpr (MODEL & kLandrini) gr = fmaf(w * F, fmaf(gi.w * mj, inv_rj, -gj.w * mi * wj * inv_ri), gr);
     // parameters (central role)
     const float AmF = fmaf(gi.x, xx, fmaf(gi.y, xy, gi.z * xz)) * (-mj * F);
-    float ga = AmF * (-C.h * mwd * B);
-    float gc = AmF * fmaf(2.0f, Sp, Pi) * C.inv_c0;
+    const float ga = AmF * mB;                 // (times -h: scale_parameters)
+    float gc = AmF * fmaf(2.0f, Sp, Pi);       // (times 1/c0)
     float gn = 0.0f;
     if constexpr (model_visc(MODEL) == kMorris) gn = fmaf(gi.x, ux, fmaf(gi.y, uy, gi.z * uz)) * 4.0f * mj * F * inv_rs;
     if constexpr (model_visc(MODEL) == kMonaghanK)
@@ -185,7 +202,7 @@ __device__ __forceinline__ void pair_adjoint_core(BackAcc &G, float xx, float xy
             const float dr = vi.w - vj.w;
             kx = fmaf(C.diff * Gd_r * dr, w1 - w2, kx);
             gr = fmaf(C.diff * Gd, w1 - w2 * vj.w * iri, gr);
-            gc = fmaf(w1 * C.diff * dr * Gd, C.inv_c0, gc);
+            gc = fmaf(w1 * C.diff * dr, Gd, gc);
         }
     }
     if (MASKED || inter) {
@@ -208,6 +225,13 @@ __device__ __forceinline__ void pair_adjoint_core(BackAcc &G, float xx, float xy
     }
 }
 
+// The common factors of the parameter sums, applied once per central.
+__device__ __forceinline__ void scale_parameters(BackAcc &G, const BackConst &C)
+{
+    G.galpha *= -C.h;
+    G.gc0 *= C.inv_c0;
+}
+
 template <int MODEL>
 __device__ __forceinline__ void pair_adjoint(BackAcc &G, uint32_t e, const float4 &pi, const float4 &vi,
                                              const float4 &xi, const float4 &gi, const float4 &pj,
@@ -217,8 +241,8 @@ __device__ __forceinline__ void pair_adjoint(BackAcc &G, uint32_t e, const float
     const float xx = fmaf(entry_k(e, 0), C.csx, pi.x - pj.x);
     const float xy = fmaf(entry_k(e, 1), C.csy, pi.y - pj.y);
     const float xz = fmaf(entry_k(e, 2), C.csz, pi.z - pj.z);
-    pair_adjoint_core<MODEL, false>(G, xx, xy, xz, pi.w, vi, xi, gi, pj.w, vj, make_float2(xj.x, xj.y), gj, valid,
-                            pair_fluid, C);
+    pair_adjoint_core<MODEL, false>(G, xx, xy, xz, pi.w, vi, xi, gi, pj.w, vj, make_float2(xj.x, xj.y), gj,
+                                       valid ? 1.0f : 0.0f, pair_fluid, C);
 }
 
 template <int MODEL>
@@ -280,6 +304,7 @@ __global__ __launch_bounds__(kThreads) void k_forces_backward(
         gvel[i] = vo;
     }
     // parameter derivatives: per-block partial sums in double, fixed order
+    scale_parameters(G, C);
     double a = nt > 0 ? (double)G.galpha : 0.0, c = nt > 0 ? (double)G.gc0 : 0.0,
            v = nt > 0 ? (double)G.gnu : 0.0;
     if (i >= n) a = c = v = 0.0;
@@ -301,108 +326,152 @@ __global__ __launch_bounds__(kThreads) void k_forces_backward(
     }
 }
 
-// Output of one particle's adjoint (overwrite or accumulate; grad_pos.w is
-// left as it is).
-__device__ __forceinline__ void store_adjoint(int i, int nt, const BackAcc &G, float4 *__restrict__ gpos,
-                                              float4 *__restrict__ gvel, int accumulate)
-{
-    float4 po = make_float4(G.ox, G.oy, G.oz, 0.0f);
-    float4 vo = make_float4(G.ux, G.uy, G.uz, G.r);
-    if (nt == 0) po = vo = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    const float4 p0 = gpos[i];
-    if (accumulate) {
-        const float4 v0 = gvel[i];
-        po = make_float4(p0.x + po.x, p0.y + po.y, p0.z + po.z, p0.w);
-        vo = make_float4(v0.x + vo.x, v0.y + vo.y, v0.z + vo.z, v0.w + vo.w);
-    } else {
-        po.w = p0.w;
-    }
-    gpos[i] = po;
-    gvel[i] = vo;
-}
-
 // ---------------------------------------------------------------------------
 // Cell-brick form of the adjoint (the cell perspective of section "Changing
-// perspective: from the particle to the cell", as in sph_forces).  A brick of
-// cells is processed in its lower and its upper half along y: the staging
-// order puts y outermost, so the staged cells of a half (its inner rows and
-// one halo row on each side) are one contiguous range of staging slots, and
-// the brick-local list entries of its particles index into that range.  Per
-// staged particle 56 bytes go to LDS (brick-relative position and mass,
-// velocity and density, P/rho^2 and c, the upstream adjoint), which holds the
-// halo of a half brick at the lattice density; a half that does not fit reads
-// the global lists and arrays as k_forces_backward does.  The sums per pair
-// are those of k_forces_backward; the separation is taken from brick-relative
-// positions (rounding differs from the gather kernel at the ulp level).
+// perspective: from the particle to the cell", as in sph_forces).  The work
+// items are those of the derivative kernel (brick_items.h); per staged
+// particle 56 bytes go to LDS (brick-relative position and mass, velocity and
+// density, P/rho^2 and c, the upstream adjoint), which holds the halo of half
+// a 3 x 4 x 3 brick at the lattice density, so its items are halves.  A run
+// that does not fit even as a single row reads the global lists and arrays as
+// k_forces_backward does.  The sums per pair are those of k_forces_backward;
+// the separation is taken from brick-relative positions (rounding differs from
+// the gather kernel at the ulp level).
+//
+// What bounds it is VALU issue: 92 instructions per pair (99 before the masks
+// went into the clamp, r^2 was fused and the parameter sums' common factors
+// left the loop), four lanes per central.  1.62M-particle dam break 382 -> 305
+// us, the 169k one with Morris viscosity 90 -> 51 us (its 120 bricks were one
+// item each, two halves one after the other).
 #ifndef SPH_BACK_RING
 #define SPH_BACK_RING 2
 #endif
-constexpr int kBackBrickThreads = 1024;
-constexpr int kBackBrickCap = 2880;
+constexpr int kBackThreads = 1024;
+constexpr int kBackCap = 2624;
+constexpr int kBackPairTime = 86;  // of a whole brick, in half microseconds (brick_parts)
 
-// Pairs of one central's brick-local list, read from LDS, shared by two
-// lanes: lane h of the pair takes the groups of 8 entries h, h + 2, h + 4, ...
-// (list groups requested two iterations ahead, staged data R pairs ahead).
-template <int MODEL>
-__device__ __forceinline__ void brick_adjoint_lds(BackAcc &G, const uint4 *lg, int h, int nt, int ntw, int s_lo,
-                                                  int span, const float4 *__restrict__ sP,
-                                                  const float4 *__restrict__ sV, const float2 *__restrict__ sX,
-                                                  const float4 *__restrict__ sG, const float4 &pi, const float4 &vi,
-                                                  const float4 &xi, const float4 &gi, const BackConst &C)
+// The staged arrays of a run.
+template <int CAP>
+struct StagedBack {
+    float4 P[CAP];  // brick-relative offset, mass
+    float4 V[CAP];  // velocity, density
+    float4 G[CAP];  // upstream adjoint
+    float2 X[CAP];  // equation-of-state terms
+};
+
+// Pairs of one central's brick-local list, read from LDS, shared by kLanes
+// lanes as in the derivative kernel (which says why the two runs of entries
+// take turns).
+template <int MODEL, int CAP>
+__device__ __forceinline__ void brick_adjoint_lds(BackAcc &G, const uint4 *lg, Entries ea, Entries eb, int h, int nt,
+                                                  uint32_t lo2, uint32_t max2, const StagedBack<CAP> &L,
+                                                  const float4 &pi, const float4 &vi, const float4 &xi,
+                                                  const float4 &gi, const BackConst &C)
 {
     // pairs of staged data in flight; one for the longest pair bodies
     // (Landrini-Morris with density diffusion and a laminar term), which
     // would otherwise exceed the 128 registers of a 1024-lane workgroup
     constexpr bool kHeaviest = (MODEL & kLandrini) && (MODEL & kDiffusion) && model_visc(MODEL) != 0;
     constexpr int R = kHeaviest ? 1 : SPH_BACK_RING;
-    const int lastg = max(nt - 1, 0) / kBrickGroup;
-    const uint32_t smax = (uint32_t)(span - 1);
+    const int runs = (nt + kEntries - 1) / kEntries;
+    const uint32_t baseP = lds_address(L.P), baseG = lds_address(L.G), baseX = lds_address(L.X);
     float4 P[R], V[R], Gj[R];
     float2 X[R];
-    auto fetch = [&](uint32_t slot, int r) {
-        const uint32_t sl = min(slot - (uint32_t)s_lo, smax);  // stays inside the staged range
-        P[r] = sP[sl];
-        V[r] = sV[sl];
-        X[r] = sX[sl];
-        Gj[r] = sG[sl];
+    auto fetch = [&](const Entries &e, int s) {
+        const uint32_t w = staged_slots(e[s >> 1], lo2, max2), a = slot_address(w, s & 1, 16, baseP);
+        const int r = s % R;
+        P[r] = lds_float4(a, 0);
+        V[r] = lds_float4(a, CAP);
+        Gj[r] = lds_float4(slot_address(w, s & 1, 16, baseG), 0);
+        X[r] = lds_float2(slot_address(w, s & 1, 8, baseX));
     };
-    uint4 gc = lg[min(h, lastg) * kWave];
-    uint4 gn = lg[min(h + 2, lastg) * kWave];
 #pragma unroll
-    for (int r = 0; r < R; ++r) fetch(group_entry(gc, r), r);
-    for (int k = 0; k < ntw; k += 2 * kBrickGroup) {
-        const int g0 = k / kBrickGroup + h;  // this lane's group
-        const uint4 gnn = lg[min(g0 + 4, lastg) * kWave];
-        const int rem = nt - g0 * kBrickGroup;  // entries of the list from this group on
+    for (int s = 0; s < R; ++s) fetch(ea, s);
+    float rem = (float)(nt - h * kEntries);  // entries of the list from this lane's run on
+    int g = h;
+    auto run = [&](Entries &e, const Entries &f) {
 #pragma unroll
-        for (int s = 0; s < kBrickGroup; ++s) {
-            const int r = s % R;
+        for (int s = 0; s < kEntries; ++s) {
+            const int r = s % R, s2 = s + R;
             // staged w = +-m_j, negative for boundary particles
-            pair_adjoint_core<MODEL, !(MODEL & kDiffusion)>(G, pi.x - P[r].x, pi.y - P[r].y, pi.z - P[r].z, fabsf(pi.w), vi, xi, gi,
-                                    fabsf(P[r].w), V[r], X[r], Gj[r], s < rem,
-                                    pi.w > 0.0f && P[r].w > 0.0f, C);
-            const int s2 = s + R;
-            fetch(s2 < kBrickGroup ? group_entry(gc, s2) : group_entry(gn, s2 - kBrickGroup), r);
+            pair_adjoint_core<MODEL, !(MODEL & kDiffusion)>(
+                G, pi.x - P[r].x, pi.y - P[r].y, pi.z - P[r].z, fabsf(pi.w), vi, xi, gi, fabsf(P[r].w), V[r], X[r],
+                Gj[r], __builtin_amdgcn_fmed3f(rem - (float)s, 0.0f, 1.0f), pi.w > 0.0f && P[r].w > 0.0f, C);
+            if (s2 < kEntries)
+                fetch(e, s2);
+            else
+                fetch(f, s2 - kEntries);
+            if (s2 == kEntries - 1) e = list_entries(lg, min(g + 2 * kLanes, runs - 1));
         }
-        gc = gn;
-        gn = gnn;
+        g += kLanes;
+        rem -= (float)(kLanes * kEntries);
+    };
+    while (g < runs) {
+        run(ea, eb);
+        if (g >= runs) break;
+        run(eb, ea);
     }
 }
 
-__device__ __forceinline__ void add_partner(BackAcc &A)
+// One particle of a staged row on its way to LDS.
+struct BackChunk {
+    float4 p, v, g;
+    int cx;  // cell along x from the brick's centre cell
+    uint32_t info;
+};
+template <int MODEL, typename Rows, typename Scans>
+__device__ __forceinline__ BackChunk load_chunk(const Rows &rows, const Scans &B, int k, int t,
+                                                const float4 *__restrict__ pos, const float4 *__restrict__ vel,
+                                                const float4 *__restrict__ gforce, const uint32_t *__restrict__ info)
 {
-    A.ox += __shfl_xor(A.ox, 1);
-    A.oy += __shfl_xor(A.oy, 1);
-    A.oz += __shfl_xor(A.oz, 1);
-    A.ux += __shfl_xor(A.ux, 1);
-    A.uy += __shfl_xor(A.uy, 1);
-    A.uz += __shfl_xor(A.uz, 1);
-    A.r += __shfl_xor(A.r, 1);
-    A.galpha += __shfl_xor(A.galpha, 1);
-    A.gc0 += __shfl_xor(A.gc0, 1);
-    A.gnu += __shfl_xor(A.gnu, 1);
+    BackChunk q;
+    const int j = rows.particle(B, k, t, q.cx);
+    q.p = load_at(pos, j);
+    q.v = load_at(vel, j);
+    q.g = load_at(gforce, j);
+    q.info = (MODEL & kDiffusion) ? load_at(info, j) : 0u;
+    return q;
+}
+template <int MODEL, typename Rows, int CAP>
+__device__ __forceinline__ void store_chunk(StagedBack<CAP> &L, const Rows &rows, const BackChunk &q, int k, int t,
+                                            const BackConst &C)
+{
+    if (t >= rows.len[k]) return;
+    const int l = rows.slot[k] + t;
+    // mass negated for boundary particles when the diffusion needs the type
+    L.P[l] = rows.brick_relative(q.p, k, q.cx, C.csx, C.csy, C.csz,
+                                 (MODEL & kDiffusion) && ptype(q.info) == kBoundary ? -q.p.w : q.p.w);
+    L.V[l] = q.v;
+    L.G[l] = q.g;
+    // equation-of-state terms (P/rho^2 or P, c) from the staged density
+    const float4 x = eos_grad_terms(q.v.w, C);
+    L.X[l] = make_float2(x.x, x.y);
 }
 
+// Output of one particle's adjoint by two lanes, h = 0 the position's and h =
+// 1 the velocity's and density's (overwrite or accumulate; grad_pos.w is left
+// as it is).
+__device__ __forceinline__ void store_adjoint(int i, int h, const BackAcc &A, float4 *__restrict__ gpos,
+                                              float4 *__restrict__ gvel, int accumulate)
+{
+    if (h == 0) {
+        const float4 p = load_at(gpos, i);
+        store_at(gpos, i, accumulate ? make_float4(p.x + A.ox, p.y + A.oy, p.z + A.oz, p.w)
+                                     : make_float4(A.ox, A.oy, A.oz, p.w));
+    } else if (h == 1) {
+        float4 v = make_float4(A.ux, A.uy, A.uz, A.r);
+        if (accumulate) {
+            const float4 v0 = load_at(gvel, i);
+            v = make_float4(v0.x + v.x, v0.y + v.y, v0.z + v.z, v0.w + v.w);
+        }
+        store_at(gvel, i, v);
+    }
+}
+
+// One resident workgroup per CU takes the items; the order of their stages is
+// that of k_forces_brick.  The parameter derivatives are summed in double in a
+// fixed order: over the centrals of a group by its wave, over the groups of an
+// item, over the items in the order of the build's table.
 template <int MODEL, int BX, int BY, int BZ, int NT, int CAP>
 __global__ __launch_bounds__(NT) void k_forces_backward_brick(
     int n, const float4 *__restrict__ pos, const float4 *__restrict__ vel,
@@ -413,258 +482,196 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
     float4 *__restrict__ gpos, float4 *__restrict__ gvel, double *__restrict__ partial,
     double *__restrict__ grad_params, int accumulate, BackConst C, BrickGrid G)
 {
-    using St = Staging<BX, BY, BZ>;
-    constexpr int SX = St::SX, SZ = St::SZ, S = St::S, NI = St::NI;
-    constexpr int ROW = SX * SZ;       // staged cells per y row
-    constexpr int IROW = BX * BZ;      // inner cells per y row
-    constexpr int HALF = BY / 2;       // inner y rows of the lower half
-    static_assert(S <= NT, "one thread per staged cell");
-    __shared__ float4 sP[CAP];
-    __shared__ float4 sV[CAP];
-    __shared__ float2 sX[CAP];
-    __shared__ float4 sG[CAP];
-    __shared__ int cBase[S + 1];
-    __shared__ int cDelta[S];
-    __shared__ int iBase[NI + 1];
-    __shared__ int iStart[NI];
-    __shared__ int wsum[NT / kWave];
-    __shared__ double red[3][NT / kWave];
-
-    __shared__ int sNext;
+    constexpr int NW = NT / kWave, LEAST = BY == 4 ? 2 : 1;
+    // a wave takes QG consecutive centrals of the table at a time
+    constexpr int QG = kWave / kLanes, MAXG = NT / QG;
+    static_assert(MAXG == kWave, "one lane per group in the sum over groups");
+    __shared__ StagedBack<CAP> L;
+    __shared__ BrickScans<BX, BY, BZ> Q[3];  // this item's, the next one's and the one after
+    __shared__ CentralTable<NT> T[2];        // this item's and the next one's
+    __shared__ double par[3][MAXG];          // parameter sums of each group
+    __shared__ double red[3][NW];
+    __shared__ int sGroup;  // groups of centrals claimed in the item
     __shared__ int sLast;
-    // One resident workgroup per CU takes the bricks with a pair one at a time
-    // from the counter `next`, heavy ones first (brick_at order; no workgroup
-    // for an empty brick; costs even out across CUs, cheap bricks come last).
-    const int n_listed = table[0] + table[cap_ids + 1];
-    for (;;) {
-        // the thread index is re-read per brick (an empty asm hides that it is the
-        // same), so nothing derived from it is kept live across the pair loop
+    using Rows = StagedRows<BX, BY, BZ, NW>;
+    constexpr int SUB = 2;        // chunks of kWave particles of a row carried to the next item
+    constexpr int PREP = NW - 1;  // the wave that prepares items
+    const int M = C.max_neibs;
+    BackChunk chunk[Rows::ROWS][SUB];
+    auto load_chunks = [&](const BrickScans<BX, BY, BZ> &N, int wave, int lane) {
+        // (always loads, so that no chunk is kept from one item to the next)
+        Rows rows;
+        rows.locate(N, wave);
+#pragma unroll
+        for (int k = 0; k < Rows::ROWS; ++k)
+#pragma unroll
+            for (int u = 0; u < SUB; ++u)
+                chunk[k][u] = load_chunk<MODEL>(rows, N, k, u * kWave + lane, pos, vel, gforce, info);
+    };
+    // The first item (prepared, staging loads under way, table made) and the
+    // second (prepared).  Meanwhile particles with an empty list (in no table
+    // of centrals; also those the build dropped) get a zero adjoint when the
+    // call overwrites (grad_pos.w is kept): no other lane writes them.
+    {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+        if (threadIdx.x == 0) Q[2].d = BrickItem{};
+        __syncthreads();
+        if (wave == PREP)
+            prepare_item<BX, BY, BZ, NT, CAP, kBackPairTime, LEAST>(Q[0], Q[2].d, true, lane, table, cap_ids, next,
+                                                                    cell_start, cell_end, G);
+        else if (!accumulate)
+            for (int i = blockIdx.x * (PREP * kWave) + threadIdx.x; i < n; i += gridDim.x * (PREP * kWave))
+                if (count[i] == 0u) {
+                    gpos[i] = make_float4(0.0f, 0.0f, 0.0f, gpos[i].w);
+                    gvel[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                }
+        __syncthreads();
+        TableMaker<BX, BY, BZ, NT> maker;
+        maker.request(Q[0], wave, lane, count);
+        load_chunks(Q[0], wave, lane);
+        maker.tally(T[0], wave, lane, M);
+        __syncthreads();
+        maker.place(T[0], wave, lane);
+        if (wave == PREP)
+            prepare_item<BX, BY, BZ, NT, CAP, kBackPairTime, LEAST>(Q[1], Q[0].d, false, lane, table, cap_ids, next,
+                                                                    cell_start, cell_end, G);
+        __syncthreads();
+    }
+    int cur = 0;
+    double item_sum = 0.0;  // (waves 0 .. 2) over the runs of the current item
+    for (int k = 0;; ++k) {
+        const int nxt = cur == 2 ? 0 : cur + 1, far = nxt == 2 ? 0 : nxt + 1;
+        // the thread index is re-read per item (an empty asm hides that it is
+        // the same), so nothing derived from it is kept live across the pair loop
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        if (tid == 0) sNext = atomicAdd(next, 1);
+        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+        const BrickScans<BX, BY, BZ> &B = Q[cur];
+        const CentralTable<NT> &D = T[k & 1];
+        CentralTable<NT> &DN = T[(k & 1) ^ 1];
+        if (__builtin_amdgcn_readfirstlane(B.d.item) < 0) break;
+        const int s_lo = __builtin_amdgcn_readfirstlane(B.d.s_lo), span = __builtin_amdgcn_readfirstlane(B.d.span);
+        const bool use_lds = __builtin_amdgcn_readfirstlane(B.d.lds) != 0;
+        const int nc = __builtin_amdgcn_readfirstlane(use_lds ? D.used : B.d.nc);
+        TableMaker<BX, BY, BZ, NT> maker;
+        maker.request(Q[nxt], wave, lane, count);
+        const int h = lane % kLanes;
+        const uint32_t lo2 = (uint32_t)s_lo * 0x10001u, max2 = (uint32_t)(span - 1) * 0x10001u;
+        int g = wave;
+        if (tid == 0) sGroup = NW;  // read after the staging barrier
+        if (tid < 3 * MAXG) (&par[0][0])[tid] = 0.0;
+        if (use_lds) {
+            // the item's particles into LDS: the chunks requested at the end of
+            // the last item, then what is left of rows longer than those
+            Rows rows;
+            rows.locate(B, wave);
+#pragma unroll
+            for (int r = 0; r < Rows::ROWS; ++r)
+#pragma unroll
+                for (int u = 0; u < SUB; ++u) store_chunk<MODEL>(L, rows, chunk[r][u], r, u * kWave + lane, C);
+#pragma unroll
+            for (int r = 0; r < Rows::ROWS; ++r)
+                for (int t = SUB * kWave + lane; t - lane < rows.len[r]; t += kWave)
+                    store_chunk<MODEL>(L, rows, load_chunk<MODEL>(rows, B, r, t, pos, vel, gforce, info), r, t, C);
+        }
+        maker.tally(DN, wave, lane, M);
         __syncthreads();
-        const int kb = sNext;
-        if (kb >= n_listed) break;  // uniform
-        const int b = brick_at(table, cap_ids, kb);
-        const int cx0 = (b % G.nbx) * BX, cy0 = ((b / G.nbx) % G.nby) * BY, cz0 = (b / (G.nbx * G.nby)) * BZ;
-
-        // 1. staged cell ranges and LDS bases, inner cells and their centrals
-        int st = 0, cnt = 0;
-        if (tid < S) {
-            int gx = cx0 - 1 + St::sx_of(tid), gy = cy0 - 1 + St::sy_of(tid), gz = cz0 - 1 + St::sz_of(tid);
-            const bool ok = wrap_axis(gx, G.nx, G.periodic & 1u) && wrap_axis(gy, G.ny, (G.periodic >> 1) & 1u) &&
-                            wrap_axis(gz, G.nz, (G.periodic >> 2) & 1u);
-            if (ok) {
-                const int lin = gx + G.nx * (gy + G.ny * gz);
-                st = cell_start[lin];
-                cnt = cell_end[lin] - st;
-            }
+        if (wave == PREP) {
+            // (few instructions in a long chain of latencies: it goes first)
+            __builtin_amdgcn_s_setprio(3);
+            prepare_item<BX, BY, BZ, NT, CAP, kBackPairTime, LEAST>(Q[far], Q[nxt].d, false, lane, table, cap_ids,
+                                                                    next, cell_start, cell_end, G);
+            __builtin_amdgcn_s_setprio(0);
         }
-        int total;
-        const int ex = block_scan<NT>(cnt, total, wsum);
-        if (tid < S) {
-            cBase[tid] = ex;
-            cDelta[tid] = ex - st;
-        }
-        if (tid == 0) cBase[S] = total;
-        __syncthreads();
-        int icnt = 0, ist = 0;
-        if (tid < NI && cx0 + St::ix_of(tid) < G.nx && cy0 + St::iy_of(tid) < G.ny && cz0 + St::iz_of(tid) < G.nz) {
-            const int t = St::inner(tid);
-            icnt = cBase[t + 1] - cBase[t];
-            ist = cBase[t] - cDelta[t];
-        }
-        int nc;
-        const int iex = block_scan<NT>(icnt, nc, wsum);
-        if (tid < NI) {
-            iBase[tid] = iex;
-            iStart[tid] = ist;
-        }
-        if (tid == 0) iBase[NI] = nc;
-        __syncthreads();
-
-        const int M = C.max_neibs;
-        const int groups = brick_groups(M);
-        const uint32_t jmax = (uint32_t)(n - 1);
-        if (tid % kWave == 0) {  // this wave's parameter sums of the brick (only its lane 0 touches them)
-            red[0][tid / kWave] = 0.0;
-            red[1][tid / kWave] = 0.0;
-            red[2][tid / kWave] = 0.0;
-        }
-        for (int half = 0; half < 2; ++half) {
-            // inner rows [y0, y1), staged rows [y0, y1 + 2)
-            const int y0 = half ? HALF : 0, y1 = half ? BY : HALF;
-            const int s_lo = cBase[y0 * ROW];
-            const int s_hi = cBase[(y1 + 2) * ROW];
-            const int q_lo = iBase[y0 * IROW];
-            const int q_hi = iBase[y1 * IROW];
-            const int span = s_hi - s_lo;
-            const bool use_lds = span <= CAP;
-            if (use_lds && q_hi > q_lo) {
-                // stage the half.  Wave w takes the staged rows R0 + w, R0 + w +
-                // NW, ... (SX x-consecutive cells: contiguous in LDS) and walks
-                // them as one range in chunks of 64 particles, the loads of SB
-                // chunks issued before their LDS stores so that their
-                // latencies overlap; lanes past the range load particle 0
-                constexpr int NW = NT / kWave, RPW = ((BY - HALF + 2) * SZ + NW - 1) / NW, SB = 4;
-                const int wave = tid / kWave, lane = tid % kWave;
-                const int R0 = y0 * SZ, R1 = (y1 + 2) * SZ;
-                int dlt[RPW], off[RPW + 1], e[RPW][SX - 1];
-                off[0] = 0;
-#pragma unroll
-                for (int k = 0; k < RPW; ++k) {
-                    const int r = R0 + wave + k * NW, rr = min(r, R1 - 1);
-                    const int b0 = cBase[rr * SX];
-                    dlt[k] = b0 - off[k];
-                    off[k + 1] = off[k] + (r < R1 ? cBase[rr * SX + SX] - b0 : 0);
-#pragma unroll
-                    for (int m = 0; m < SX - 1; ++m) e[k][m] = cBase[rr * SX + 1 + m];
+        while (g * QG < nc) {  // wave-uniform
+            const int q = g * QG + lane / kLanes;
+            BackAcc A = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+            int i, nt;
+            if (use_lds) {
+                const uint32_t e = D.cen[min(q, nc - 1)];
+                const int si = (int)(e & kCenSlotMask);
+                nt = q < nc ? (int)(e >> kCenCountShift) : 0;
+                i = min(si + B.row_shift[e >> kCenRowShift & 15u], n - 1);
+                if (nt > 0) {
+                    const uint4 *lg = list_groups(neibs_brick, i, brick_groups(M));
+                    const int last = (nt - 1) / kEntries;
+                    const Entries ea = list_entries(lg, min(h, last)), eb = list_entries(lg, min(h + kLanes, last));
+                    const float4 vi = L.V[si];
+                    brick_adjoint_lds<MODEL, CAP>(A, lg, ea, eb, h, nt, lo2, max2, L, L.P[si], vi,
+                                                  eos_grad_terms(vi.w, C), L.G[si], C);
                 }
-                const int L = off[RPW];
-                for (int tb = 0; tb < L; tb += SB * kWave) {
-                    int slot[SB], cc[SB], rw[SB];
-                    float4 p[SB], v[SB], g[SB];
-                    bool bnd[SB];
-#pragma unroll
-                    for (int u = 0; u < SB; ++u) {
-                        const int t = tb + u * kWave + lane;
-                        int k = 0;
-#pragma unroll
-                        for (int m = 1; m < RPW; ++m) k += t >= off[m] ? 1 : 0;
-                        int d = dlt[0], ee[SX - 1];
-#pragma unroll
-                        for (int m = 0; m < SX - 1; ++m) ee[m] = e[0][m];
-#pragma unroll
-                        for (int q = 1; q < RPW; ++q)
-                            if (k == q) {
-                                d = dlt[q];
-#pragma unroll
-                                for (int m = 0; m < SX - 1; ++m) ee[m] = e[q][m];
-                            }
-                        const int s2 = t + d;
-                        int c = 0;
-#pragma unroll
-                        for (int m = 0; m < SX - 1; ++m) c += s2 >= ee[m] ? 1 : 0;
-                        const int r = min(R0 + wave + k * NW, R1 - 1);
-                        slot[u] = t < L ? s2 : -1;
-                        cc[u] = c;
-                        rw[u] = r;
-                        const int j = t < L ? s2 - cDelta[r * SX + c] : 0;
-                        p[u] = pos[j];
-                        v[u] = vel[j];
-                        g[u] = gforce[j];
-                        // mass negated for boundary particles when the diffusion needs the type
-                        bnd[u] = (MODEL & kDiffusion) ? ptype(info[j]) == kBoundary : false;
-                    }
-#pragma unroll
-                    for (int u = 0; u < SB; ++u) {
-                        if (slot[u] >= 0) {
-                            const float sx = (float)(cc[u] - 2), sy = (float)(rw[u] / SZ - 2),
-                                        sz = (float)(rw[u] % SZ - 2);
-                            const int l = slot[u] - s_lo;
-                            sP[l] = make_float4(fmaf(sx, C.csx, p[u].x), fmaf(sy, C.csy, p[u].y),
-                                                fmaf(sz, C.csz, p[u].z), bnd[u] ? -p[u].w : p[u].w);
-                            sV[l] = v[u];
-                            // equation-of-state terms (P/rho^2 or P, c) from the staged density
-                            const float4 x = eos_grad_terms(v[u].w, C);
-                            sX[l] = make_float2(x.x, x.y);
-                            sG[l] = g[u];
-                        }
-                    }
-                }
-            }
-            __syncthreads();
-            // two lanes per central particle of the half (lane pairs 2q', 2q'+1)
-            const int h = tid & 1;
-            if (q_hi == q_lo) continue;  // uniform
-            for (int q0 = q_lo; q0 < q_hi; q0 += NT / 2) {
-                const int q = q0 + tid / 2;
-                const bool act = q < q_hi;
-                int u;
-                {
-                    int lo = 0, hi = NI - 1;
-                    const int qq = act ? q : q_hi - 1;
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (iBase[mid] <= qq) lo = mid;
-                        else hi = mid - 1;
-                    }
-                    u = lo;
-                }
-                const int i = iStart[u] + ((act ? q : q_hi - 1) - iBase[u]);
-                const uint32_t cntw = act ? count[i] : 0u;
-                const int nf = min((int)(cntw & 0xFFFFu), M);
-                const int nt = min(nf + (int)(cntw >> 16), M);
+            } else {
+                // more particles than LDS holds: the global lists and arrays, the
+                // lanes of a central taking every kLanes-th entry
+                i = item_central(B, min(q, nc - 1));
+                const uint32_t cw = q < nc ? count[i] : 0u;
+                const int nf = min((int)(cw & 0xFFFFu), M);
+                nt = min(nf + (int)(cw >> 16), M);
                 const int ntw = __builtin_amdgcn_readfirstlane(wave_max(nt));
-                BackAcc A = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                if (ntw > 0) {
-                    if (use_lds) {
-                        const int si = i + cDelta[St::inner(u)] - s_lo;
-                        const uint4 *lg = (const uint4 *)(neibs_brick + brick_entry(i, 0, groups));
-                        const float4 vi = sV[si];
-                        brick_adjoint_lds<MODEL>(A, lg, h, nt, ntw, s_lo, span, sP, sV, sX, sG, sP[si], vi,
-                                                eos_grad_terms(vi.w, C), sG[si], C);
-                    } else {
-                        // the lane pair splits the list by parity of the entry
-                        const uint32_t *tile = neibs + (size_t)(i / kWave) * (kWave * M) + (i % kWave);
-                        const float4 pi = pos[i], vi = vel[i], gi = gforce[i];
-                        const float4 xi = eos_grad_terms(vi.w, C);
-                        const bool central_fluid = (MODEL & kDiffusion) ? ptype(info[i]) != kBoundary : true;
-                        const int last = max(nt - 1, 0);
-                        for (int k = h; k < ntw; k += 2) {
-                            const uint32_t e = tile[list_slot(k, nf, last, M) * kWave];
-                            const uint32_t j = min(e & kIndexMask, jmax);
-                            const float4 vj = vel[j];
-                            pair_adjoint<MODEL>(A, e, pi, vi, xi, gi, pos[j], vj, eos_grad_terms(vj.w, C),
-                                               gforce[j], k < nt, central_fluid && k < nf, C);
-                        }
-                    }
+                const uint32_t *tile = neibs + (size_t)(i / kWave) * (kWave * M) + (i % kWave);
+                const float4 pi = pos[i], vi = vel[i], gi = gforce[i];
+                const float4 xi = eos_grad_terms(vi.w, C);
+                const bool central_fluid = (MODEL & kDiffusion) ? ptype(info[i]) != kBoundary : true;
+                const int last = max(nt - 1, 0);
+                for (int t = h; t < ntw; t += kLanes) {
+                    const uint32_t e = tile[list_slot(t, nf, last, M) * kWave];
+                    const uint32_t j = min(e & kIndexMask, (uint32_t)(n - 1));
+                    const float4 vj = vel[j];
+                    pair_adjoint<MODEL>(A, e, pi, vi, xi, gi, pos[j], vj, eos_grad_terms(vj.w, C), gforce[j], t < nt,
+                                        central_fluid && t < nf, C);
                 }
-                add_partner(A);
-                const bool own = act && h == 0 && nt > 0;
-                // (a particle with an empty list is written after the last brick)
-                if (own) store_adjoint(i, nt, A, gpos, gvel, accumulate);
-                // parameter sums: per wave and group of centrals, in double,
-                // added to the wave's LDS slot in a fixed order (no per-lane
-                // double kept across the loop: registers are the pair loop's)
-                const double ga = wave_sum(own ? (double)A.galpha : 0.0);
-                const double gc = wave_sum(own ? (double)A.gc0 : 0.0);
-                const double gn = wave_sum(own ? (double)A.gnu : 0.0);
-                if (tid % kWave == 0) {
-                    red[0][tid / kWave] += ga;
-                    red[1][tid / kWave] += gc;
-                    red[2][tid / kWave] += gn;
-                }
+                if (nt == 0) A = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             }
-            __syncthreads();  // the next half reuses LDS
+            A.ox = lanes_sum(A.ox);
+            A.oy = lanes_sum(A.oy);
+            A.oz = lanes_sum(A.oz);
+            A.ux = lanes_sum(A.ux);
+            A.uy = lanes_sum(A.uy);
+            A.uz = lanes_sum(A.uz);
+            A.r = lanes_sum(A.r);
+            A.galpha = lanes_sum(A.galpha);
+            A.gc0 = lanes_sum(A.gc0);
+            A.gnu = lanes_sum(A.gnu);
+            if (nt > 0) store_adjoint(i, h, A, gpos, gvel, accumulate);
+            scale_parameters(A, C);
+            // parameter sums: lane h of every central takes one of the three,
+            // summed in double over the wave's centrals
+            double s = (double)(h == 0 ? A.galpha : h == 1 ? A.gc0 : A.gnu);
+#pragma unroll
+            for (int o = kLanes; o < kWave; o <<= 1) s += __shfl_xor(s, o);
+            if (use_lds) {
+                if (lane < 3) par[lane][g] = s;
+                int c = 0;
+                if (lane == 0) c = atomicAdd(&sGroup, 1);
+                g = __builtin_amdgcn_readfirstlane(c);
+            } else {
+                // (such an item may have more groups than slots: dealt to the
+                // waves in turn, each adds up its own)
+                if (lane < 3) par[lane][wave] += s;
+                g += NW;
+            }
         }
-        // parameter partial sums of the brick, fixed order, stored by brick id
-        if (tid < 3) {
-            double sum = 0.0;
-            for (int k = 0; k < NT / kWave; ++k) sum += red[tid][k];
-            partial[3 * (size_t)b + tid] = sum;
+        // (in the time that waves without a group wait for the others)
+        maker.place(DN, wave, lane);
+        load_chunks(Q[nxt], wave, lane);
+        __syncthreads();  // the next item reuses the LDS
+        if (wave < 3) {  // (the same wave clears par[wave] for the next item)
+            const double v = wave_sum(par[wave][lane]);
+            item_sum += v;
+            if (lane == 0 && B.d.yb == B.d.yend) partial[3 * (size_t)B.d.item + wave] = item_sum;
+            if (B.d.yb == B.d.yend) item_sum = 0.0;
         }
-        __syncthreads();  // the next brick reuses the LDS
+        cur = nxt;
     }
-    // Particles with an empty list (none of their bricks' pairs; also those
-    // the build dropped) get a zero adjoint when the call overwrites
-    // (grad_pos.w is kept), by all workgroups as they run out of bricks: no
-    // other lane writes them.
-    if (!accumulate)
-        for (int k = blockIdx.x * NT + threadIdx.x; k < n; k += gridDim.x * NT)
-            if (count[k] == 0u) {
-                gpos[k] = make_float4(0.0f, 0.0f, 0.0f, gpos[k].w);
-                gvel[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            }
-    // The last workgroup to finish sums the partials of every brick of the
-    // grid (bricks without a pair hold the zero written before the launch)
-    // in a fixed order: each workgroup makes its partials visible device-wide
-    // before it counts itself finished (next[1]), and the last one takes that
-    // count's view of memory before it reads them.
+    // The last workgroup to finish sums the partials of all items in a fixed
+    // order: each workgroup makes its partials visible device-wide before it
+    // counts itself finished (next[1]), and the last one takes that count's
+    // view of memory before it reads them.
     // (the thread index is hidden from the compiler here as in the loop, so
     // that nothing derived from it is computed before the loop and kept live)
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
+    __syncthreads();
     if (tid == 0) {
         __threadfence();
         sLast = atomicAdd(&next[1], 1) == (int)gridDim.x - 1;
@@ -672,26 +679,24 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
     __syncthreads();
     if (sLast) {  // uniform
         __threadfence();
-        sum_partials<NT>(tid, G.nbx * G.nby * G.nbz, partial, grad_params, accumulate, red);
+        const int n_listed = table[0] + table[cap_ids + 1];
+        sum_partials<NT>(tid, n_listed * item_parts<BY, kBackPairTime, LEAST>(n_listed, G), partial, grad_params,
+                         accumulate, red);
     }
 }
 
 template <int MODEL>
-void launch_backward_brick(const BackArgs &a, const BackConst &C, hipStream_t s, int &n_bricks)
+void launch_backward_brick(const BackArgs &a, const BackConst &C, hipStream_t s)
 {
     with_shape(a.shape, [&]<int BX, int BY, int BZ>() {
         const BrickGrid G = brick_grid<BX, BY, BZ>(a.grid->ncell, a.grid->periodic);
         const unsigned blocks = (unsigned)G.nbx * G.nby * G.nbz;
-        n_bricks = (int)blocks;
-        // (the brick counters and the per-brick parameter partials were
-        // cleared before the launch; the table of bricks with a pair is the
-        // build's)
-        const unsigned wgs = blocks < (unsigned)sph_device_cus() ? blocks : (unsigned)sph_device_cus();
-        k_forces_backward_brick<MODEL, BX, BY, BZ, kBackBrickThreads, kBackBrickCap>
-            <<<wgs, kBackBrickThreads, 0, s>>>(a.n, a.pos, a.vel, a.gforce, a.neibs, a.neibs_brick,
-                                              a.count, a.cell_start, a.cell_end, a.table, a.cap_ids, a.next, a.info,
-                                              a.gpos,
-                                              a.gvel, a.partial, a.grad_params, a.accumulate, C, G);
+        // (the counters were cleared before the launch; the table of bricks
+        // with a pair is the build's)
+        k_forces_backward_brick<MODEL, BX, BY, BZ, kBackThreads, kBackCap>
+            <<<brick_workgroups(blocks, BY), kBackThreads, 0, s>>>(
+                a.n, a.pos, a.vel, a.gforce, a.neibs, a.neibs_brick, a.count, a.cell_start, a.cell_end, a.table,
+                a.cap_ids, a.next, a.info, a.gpos, a.gvel, a.partial, a.grad_params, a.accumulate, C, G);
     });
 }
 
@@ -706,9 +711,10 @@ bool sph::SPH_BACK_FN(SPH_KERNEL_KIND)(int model, const BackArgs &a, const BackC
     if (model < 0 || model_kernel(model) != SPH_KERNEL_KIND) return false;
     return with_model<SPH_KERNEL_KIND>(model & kModelLowBits, [&]<int M>() {
         if (a.bricks) {
-            // cell ranges and brick-local lists of the last build: LDS bricks,
-            // one partial per brick of the grid
-            launch_backward_brick<M>(a, C, s, n_partials);
+            // cell ranges and brick-local lists of the last build: LDS bricks
+            // (the kernel sums its own partials)
+            launch_backward_brick<M>(a, C, s);
+            n_partials = 0;
         } else {
             const unsigned blocks = sph_blocks(a.n, kThreads);
             n_partials = (int)blocks;

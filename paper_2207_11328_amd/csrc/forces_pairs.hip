@@ -272,6 +272,7 @@ __global__ __launch_bounds__(kThreads) void k_forces(int n, const float4 *__rest
 #define SPH_BRICK_RING 2
 #endif
 constexpr int kRing = SPH_BRICK_RING;
+constexpr int kPairTime = 32;  // of a whole brick, in half microseconds (brick_parts)
 static_assert(kBrickGroup % kRing == 0, "ring must divide the group");
 
 // The staged arrays of a brick.  P and V are read with one address register
@@ -282,59 +283,6 @@ struct Staged {
     float4 V[CAP];  // velocity, density
     float2 A[CAP];  // equation-of-state terms
 };
-
-// LDS by address (a 32-bit offset in the workgroup's LDS).
-typedef float vf4 __attribute__((ext_vector_type(4)));
-typedef float vf2 __attribute__((ext_vector_type(2)));
-template <typename T>
-using Lds = __attribute__((address_space(3))) T;
-template <typename T>
-__device__ __forceinline__ uint32_t lds_address(const T *p)
-{
-    return (uint32_t)(uintptr_t)(Lds<const T> *)p;
-}
-__device__ __forceinline__ float4 lds_float4(uint32_t a, int index)
-{
-    const vf4 v = ((Lds<const vf4> *)(uintptr_t)a)[index];
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ float2 lds_float2(uint32_t a)
-{
-    const vf2 v = *(Lds<const vf2> *)(uintptr_t)a;
-    return make_float2(v.x, v.y);
-}
-
-// base + scale x (the 16-bit slot in half `hi` of w): one instruction, the
-// unpacking included.
-__device__ __forceinline__ uint32_t slot_address(uint32_t w, int hi, int scale, uint32_t base)
-{
-    uint32_t a;
-    if (scale == 16) {
-        if (hi) asm("v_mad_u32_u16 %0, %1, 16, %2 op_sel:[1,0,0,0]" : "=v"(a) : "v"(w), "s"(base));
-        else asm("v_mad_u32_u16 %0, %1, 16, %2" : "=v"(a) : "v"(w), "s"(base));
-    } else {
-        if (hi) asm("v_mad_u32_u16 %0, %1, 8, %2 op_sel:[1,0,0,0]" : "=v"(a) : "v"(w), "s"(base));
-        else asm("v_mad_u32_u16 %0, %1, 8, %2" : "=v"(a) : "v"(w), "s"(base));
-    }
-    return a;
-}
-
-// Lanes per central, and the entries one of them takes at a time.
-constexpr int kLanes = 4, kEntries = kBrickGroup;
-typedef uint32_t Entries __attribute__((ext_vector_type(4)));
-// group e of a brick-local list, lg its group 0
-__device__ __forceinline__ Entries list_entries(const uint4 *lg, int e)
-{
-    return load_at((const Entries *)lg, e * kWave);
-}
-// Two slots of a list relative to the first staged one, kept inside the staged
-// range (a stale list gives wrong numbers but no access past it).
-__device__ __forceinline__ uint32_t staged_slots(uint32_t w, uint32_t lo2, uint32_t max2)
-{
-    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-    const us2 d = __builtin_elementwise_sub_sat(__builtin_bit_cast(us2, w), __builtin_bit_cast(us2, lo2));
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(d, __builtin_bit_cast(us2, max2)));
-}
 
 // Lane h of a central's kLanes lanes takes the runs of kEntries entries h, h +
 // kLanes, ... of its list; ea and eb are its first two.  The two take turns:
@@ -385,19 +333,6 @@ __device__ __forceinline__ void brick_pairs_lds(PairAcc &A, const uint4 *lg, Ent
     }
 }
 
-// The sum of a value over the lanes of a central, in all of them.
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float lanes_sum(float v)
-{
-    v += dpp<0xB1>(v);  // quad lanes 1, 0, 3, 2
-    v += dpp<0x4E>(v);  // quad lanes 2, 3, 0, 1
-    return v;
-}
-
 // One particle of a staged row on its way to LDS.
 struct Chunk {
     float4 p, v;
@@ -406,79 +341,34 @@ struct Chunk {
     uint32_t info;
 };
 
-// Staged rows of cells of an item (SX x-consecutive cells: one contiguous LDS
-// range and, away from a periodic seam, one contiguous global range): wave w
-// takes rows w and w + NW.
-template <int BX, int BY, int BZ, int NW>
-struct StagedRows {
-    using St = Staging<BX, BY, BZ>;
-    static constexpr int SX = St::SX, SZ = St::SZ, ROWS = 2;
-    static_assert(St::SY * SZ <= ROWS * NW, "two rows per wave hold every row");
-    int row[ROWS], slot[ROWS], len[ROWS];  // row, its first slot (from s_lo), its particles
-
-    __device__ __forceinline__ void locate(const BrickScans<BX, BY, BZ> &B, int wave)
-    {
-        const bool staged = __builtin_amdgcn_readfirstlane(B.d.item) >= 0 && __builtin_amdgcn_readfirstlane(B.d.lds);
-        const int R0 = __builtin_amdgcn_readfirstlane(B.d.ya * SZ), R1 = __builtin_amdgcn_readfirstlane((B.d.yb + 2) * SZ);
-#pragma unroll
-        for (int k = 0; k < ROWS; ++k) {
-            row[k] = min(R0 + wave + k * NW, R1 - 1);
-            const int b0 = __builtin_amdgcn_readfirstlane(B.base[row[k] * SX]);
-            slot[k] = b0 - __builtin_amdgcn_readfirstlane(B.d.s_lo);
-            const int l = __builtin_amdgcn_readfirstlane(B.base[row[k] * SX + SX]) - b0;
-            len[k] = staged && R0 + wave + k * NW < R1 ? l : 0;
-        }
-    }
-    // particle t of row k (t past its end: particle 0; loads stay
-    // unconditional, so the chunks stay in registers)
-    template <int MODEL>
-    __device__ __forceinline__ Chunk load(const BrickScans<BX, BY, BZ> &B, int k, int t, const float4 *__restrict__ pos,
-                                          const float4 *__restrict__ vel, const int32_t *__restrict__ cell,
-                                          const uint32_t *__restrict__ info, const ForceConst &C) const
-    {
-        const int *base = B.base + row[k] * SX, *delta = B.delta + row[k] * SX;
-        const int s = base[0] + t;
-        int c = -2, d = delta[0];
-#pragma unroll
-        for (int m = 1; m < SX; ++m) {
-            const bool past = s >= base[m];
-            c += past ? 1 : 0;
-            d = past ? delta[m] : d;
-        }
-        const int j = t < len[k] ? s - d : 0;
-        Chunk q;
-        q.p = load_at(pos, j);
-        q.v = load_at(vel, j);
-        q.ah = alpha_h_of(j, cell, C);
-        q.cx = c;
-        q.info = (MODEL & kDiffusion) ? load_at(info, j) : 0u;
-        return q;
-    }
-    template <int MODEL, int CAP>
-    __device__ __forceinline__ void store(Staged<CAP> &L, const Chunk &q, int k, int t, const ForceConst &C) const
-    {
-        if (t >= len[k]) return;
-        const int l = slot[k] + t;
-        // positions relative to the centre cell of the whole brick
-        const float sx = (float)q.cx, sy = (float)(row[k] / SZ - 2), sz = (float)(row[k] % SZ - 2);
-        // w = m x kernel coefficient, negated for boundary particles when the
-        // density diffusion needs the type
-        const float mf = q.p.w * C.fcoeff_brick;
-        L.P[l] = make_float4(fmaf(sx, C.csx, q.p.x), fmaf(sy, C.csy, q.p.y), fmaf(sz, C.csz, q.p.z),
-                             (MODEL & kDiffusion) && ptype(q.info) == kBoundary ? -mf : mf);
-        L.V[l] = q.v;
-        // equation-of-state terms from the staged density
-        L.A[l] = eos_terms<(MODEL & kLandrini) != 0>(q.v.w, q.ah, C);
-    }
-};
-
-// The brick-local list of particle i (brick_entry(i, 0, groups)): group g at
-// [g * kWave].
-__device__ __forceinline__ const uint4 *list_groups(const uint16_t *__restrict__ neibs_brick, int i, uint32_t groups)
+template <int MODEL, typename Rows, typename Scans>
+__device__ __forceinline__ Chunk load_chunk(const Rows &rows, const Scans &B, int k, int t,
+                                            const float4 *__restrict__ pos, const float4 *__restrict__ vel,
+                                            const int32_t *__restrict__ cell, const uint32_t *__restrict__ info,
+                                            const ForceConst &C)
 {
-    const uint32_t u = (uint32_t)i;
-    return (const uint4 *)((const char *)neibs_brick + (uint64_t)(u / kWave) * (groups * (kWave * 16u)) +
-                           (u % kWave) * 16u);
+    Chunk q;
+    const int j = rows.particle(B, k, t, q.cx);
+    q.p = load_at(pos, j);
+    q.v = load_at(vel, j);
+    q.ah = alpha_h_of(j, cell, C);
+    q.info = (MODEL & kDiffusion) ? load_at(info, j) : 0u;
+    return q;
+}
+template <int MODEL, typename Rows, int CAP>
+__device__ __forceinline__ void store_chunk(Staged<CAP> &L, const Rows &rows, const Chunk &q, int k, int t,
+                                            const ForceConst &C)
+{
+    if (t >= rows.len[k]) return;
+    const int l = rows.slot[k] + t;
+    // w = m x kernel coefficient, negated for boundary particles when the
+    // density diffusion needs the type
+    const float mf = q.p.w * C.fcoeff_brick;
+    L.P[l] = rows.brick_relative(q.p, k, q.cx, C.csx, C.csy, C.csz,
+                                 (MODEL & kDiffusion) && ptype(q.info) == kBoundary ? -mf : mf);
+    L.V[l] = q.v;
+    // equation-of-state terms from the staged density
+    L.A[l] = eos_terms<(MODEL & kLandrini) != 0>(q.v.w, q.ah, C);
 }
 
 // Particles with an empty list (in no table of centrals; also those the build
@@ -562,7 +452,7 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         for (int k = 0; k < Rows::ROWS; ++k)
 #pragma unroll
             for (int u = 0; u < SUB; ++u)
-                chunk[k][u] = rows.template load<MODEL>(N, k, u * kWave + lane, pos, vel, cell, info, C);
+                chunk[k][u] = load_chunk<MODEL>(rows, N, k, u * kWave + lane, pos, vel, cell, info, C);
     };
     // The first item (prepared, staging loads under way, table made) and the second (prepared)
     {
@@ -570,7 +460,7 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         if (threadIdx.x == 0) Q[2].d = BrickItem{};
         __syncthreads();
         if (wave == PREP)
-            prepare_item<BX, BY, BZ, NT, CAP>(Q[0], Q[2].d, true, lane, table, cap_ids, next, cell_start, cell_end, G);
+            prepare_item<BX, BY, BZ, NT, CAP, kPairTime, 1>(Q[0], Q[2].d, true, lane, table, cap_ids, next, cell_start, cell_end, G);
         else
             empty_lists<PREP * kWave>(n, count, vel, out, tau, K);
         __syncthreads();
@@ -581,7 +471,7 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         __syncthreads();
         maker.place(T[0], wave, lane);
         if (wave == PREP)
-            prepare_item<BX, BY, BZ, NT, CAP>(Q[1], Q[0].d, false, lane, table, cap_ids, next, cell_start, cell_end, G);
+            prepare_item<BX, BY, BZ, NT, CAP, kPairTime, 1>(Q[1], Q[0].d, false, lane, table, cap_ids, next, cell_start, cell_end, G);
         __syncthreads();
     }
     int cur = 0;
@@ -656,11 +546,11 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
 #pragma unroll
             for (int r = 0; r < Rows::ROWS; ++r)
 #pragma unroll
-                for (int u = 0; u < SUB; ++u) rows.template store<MODEL>(L, chunk[r][u], r, u * kWave + lane, C);
+                for (int u = 0; u < SUB; ++u) store_chunk<MODEL>(L, rows, chunk[r][u], r, u * kWave + lane, C);
 #pragma unroll
             for (int r = 0; r < Rows::ROWS; ++r)
                 for (int t = SUB * kWave + lane; t - lane < rows.len[r]; t += kWave)
-                    rows.template store<MODEL>(L, rows.template load<MODEL>(B, r, t, pos, vel, cell, info, C), r, t, C);
+                    store_chunk<MODEL>(L, rows, load_chunk<MODEL>(rows, B, r, t, pos, vel, cell, info, C), r, t, C);
         }
         maker.tally(DN, wave, lane, M);
         __syncthreads();
@@ -672,7 +562,7 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         if (wave == PREP) {
             // (few instructions in a long chain of latencies: it goes first)
             __builtin_amdgcn_s_setprio(3);
-            prepare_item<BX, BY, BZ, NT, CAP>(Q[far], Q[nxt].d, false, lane, table, cap_ids, next, cell_start, cell_end,
+            prepare_item<BX, BY, BZ, NT, CAP, kPairTime, 1>(Q[far], Q[nxt].d, false, lane, table, cap_ids, next, cell_start, cell_end,
                                               G);
             __builtin_amdgcn_s_setprio(0);
         }

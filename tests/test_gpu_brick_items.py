@@ -69,3 +69,44 @@ def test_few_bricks(n, brick):
     ob = compare_build(sc, sim, max_neibs=256)
     _, (acc, drho, sa, sd, _ni) = oracle_forces_of(sc, ob)
     check_forces(f[:n].cpu().numpy(), acc, drho, sa, sd, label="few bricks %d" % n, allowance=edge_allowance(sc, ob))
+
+
+@pytest.mark.parametrize("brick", SHAPES, ids=["x".join(map(str, b)) for b in SHAPES])
+def test_crowded_bricks_adjoint(brick):
+    """The adjoint on the crowded cloud (its LDS holds fewer particles, so
+    more bricks are cut or left to the global lists), parameter sums included;
+    its own checks repeat the call bit for bit."""
+    from test_gpu_adjoint import _backward_parity
+    sc = S.random_cloud(n=17500, box=(0.4, 0.4, 0.4), dp=0.02, seed=21, boundary_frac=0.2, u_sigma=0.2, alpha=0.2)
+    _backward_parity(sc, 416, True, brick, "crowded")
+
+
+@pytest.mark.parametrize("n", [2, 65, 700])
+def test_few_bricks_adjoint(n):
+    from test_gpu_adjoint import _backward_parity
+    box = (0.12, 0.12, 0.12) if n < 100 else (0.2, 0.27, 0.16)
+    sc = S.random_cloud(n=n, box=box, dp=0.02, seed=300 + n, boundary_frac=0.2, u_sigma=0.2, alpha=0.2)
+    _backward_parity(sc, 256, True, None, "few bricks %d" % n)
+
+
+def test_adjoint_same_after_every_build():
+    """The table of bricks, and with it the order in which the parameter
+    partials are summed, is the same after every build of a state."""
+    from paper_2207_11328_amd import abi
+    sc = S.dam_break_64k()
+    got = []
+    for _ in range(2):
+        sim = make_sim(sc)
+        for _ in range(2):
+            sim.build()
+            gf = torch.sin(torch.arange(4 * sim.capacity, device=sim.device, dtype=torch.float32)).view(-1, 4)
+            gp, gv = torch.zeros_like(sim.pos), torch.zeros_like(sim.vel)
+            par = torch.zeros(3, dtype=torch.float64, device=sim.device)
+            ws = torch.zeros(abi.sph_forces_backward_workspace_bytes(sim.capacity, sim.n_cells), dtype=torch.uint8,
+                             device=sim.device)
+            abi.sph_forces_backward(sim.g, sim.p, sim.parts, sim.neibs, sim.neib_count, sim.max_neibs, gf, gp, gv,
+                                    par, False, ws, None, *sim.brick_args())
+            torch_sync()
+            got.append((gp, gv, par))
+    for g in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], g))
