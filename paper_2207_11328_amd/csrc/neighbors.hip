@@ -417,365 +417,497 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, const uin
 
 // Neighbour lists, cell-brick form (section "Changing perspective: from the
 // particle to the cell": a group of work-items per cell, neighbour data shared
-// through on-chip memory).  A workgroup owns a brick of BX x BY x BZ cells and
-// stages the offsets and type words of the particles of the brick and its
-// one-cell halo in LDS (16 bytes per particle).  Each lane then takes one
-// central particle and scans the 27 cells of its Moore neighbourhood (z, y, x
-// from -1 to +1), each cell in sorted order, reading candidates from LDS;
-// lanes of the same cell read the same candidate at the same time (an LDS
-// broadcast).  Fluid entries fill the list from the front and boundary
-// entries from the back, in scan order, until M entries are written.
+// through on-chip memory).  A workgroup owns a brick of BX x BY x BZ cells, or
+// a run of its rows; its work items are the fluid and the boundary centrals of
+// each inner cell (inside a cell fluid particles precede boundary ones, so
+// boundary centrals, which take no boundary neighbours, have the fluid prefix
+// of each cell as candidates).  A wave takes items from a counter.
 //
-// Inside a cell fluid particles precede boundary ones, so the exclusion of
-// boundary-boundary pairs is a shorter candidate range for a boundary centre
-// (the fluid prefix of each cell, from a per-cell table) rather than a test per
-// candidate, and the candidate loop has no data-dependent branch: one
-// predicated store per listed pair.  A brick whose halo does not fit in LDS
-// runs the same loop on global memory.
+// For its item a wave lists the candidates: the particles of the 27 cells of
+// the Moore neighbourhood (z, y, x from -1 to +1), each cell in sorted order.
+// The distances of 16 centrals to 16 candidates are a 16 x 4 by 4 x 16 product
+// in float32,
+//   |o_i|^2 - r_s^2 + |p_j|^2 - 2 o_i . p_j,
+// with the offset o_i and the candidate's position p_j = o_j + d cs in the
+// frame of the central's cell: one matrix instruction instead of 11 vector
+// ones per 64 pairs, and the hit is the sign of the result.  The list predicate
+// is a float32 expression of its own (predicate_r2), so a result within a slack
+// of zero decides nothing: that pair is evaluated with the predicate itself.
+// Both differ from the real r^2 - r_s^2 by rounding: with u = 2^-24,
+// S = |cs|^2, |o|^2 <= S/4 and |p|^2 <= 9/4 S,
+//   shift of p (1/2 ulp of it, twice)                    6 u S
+//   |p|^2, |o|^2 - r_s^2 (3 roundings each)              9 u S
+//   four products and sums of at most 4 S                32 u S
+//   the predicate: x to 2.5 u |cs|, its square and sum   8 u S
+// less than 64 u S together; kSlack = 128 u S.  Where an offset leaves its
+// cell, or is not finite, the predicate decides every pair of the item.
 //
-// Optionally the same lists are also written in brick-local form for the
-// derivative kernels: entry k is the neighbour's slot in the staging order of
-// the central particle's brick (cells of the brick and its halo in the
-// Staging order, particles of a cell in sorted order), uint16, in scan order with
-// fluid and boundary neighbours interleaved as found (entries 0 .. nf+nb-1),
-// stored in groups of 8 per particle (brick_entry).
-// The staged word of a particle (w of its float4 in LDS): its type in the
-// type bits, its staged cell in bits kCellShift.., and for a central the
-// number of neighbours found so far in the low bits (kFoundMask; the count is
-// below the brick's staged particles, fewer than kBuildCap).
-constexpr uint32_t kFoundMask = 0xFFFFu;
-constexpr int kCellShift = 16;
-constexpr uint32_t kCellMask = 0xFFu;
+// Lanes 16 g .. 16 g + 15 take quarter g of the candidate list, each lane for
+// one central: row 4 g + r of the candidate operand is candidate g Q + 4 t + r
+// in tile t, so the four results of a lane are consecutive candidates of its
+// quarter, and their signs are shifted into its hit words.  A central's entries
+// are then the hits of its four lanes one after the other: after a count over
+// the four, each lane writes its own to LDS in scan order, and from there the
+// four lanes write both lists in rows of 16 centrals.  Two groups of centrals
+// share a candidate operand.  Fluid entries fill the split list from the front
+// and boundary entries from the back, in scan order, until M entries are
+// written.
+//
+// The brick-local form of the same lists is for the derivative kernels: entry k
+// is the neighbour's slot in the staging order of the central particle's brick
+// (cells of the brick and its halo in the Staging order, particles of a cell in
+// sorted order), uint16, in scan order with fluid and boundary neighbours
+// interleaved as found (entries 0 .. nf+nb-1), stored in groups of 8 per
+// particle (brick_entry).
+//
+// Bound by VALU issue and the latencies between the steps: of the 545 us that
+// the scan of the 1.62M-particle dam break takes (92 neighbours a particle, 0.9 GB of
+// lists), the vector ALU issues for 330; the lists alone would take 175 at the
+// rate of a large copy.  Taking away in turn the writing of the lists, the
+// collecting of entries, the products and the positions leaves 450, 335, 215
+// and 180 us.  Before, a wave took one central and 64 candidates at a time from
+// a brick staged in LDS, with a ballot per central: 721 us (still-water tank of
+// 15.5k particles, 27 bricks: 141, now 45; 169k dam break: 180, now 98).
+//
+// Candidates are listed kList at a time and their positions laid out by
+// component kTilesPage tiles at a time.  Rows of a quarter are kRow apart: the
+// 64 operands of a tile (16 candidates by 4 components) then lie in 64 places
+// of distinct banks, two passes of 32.  Entries are collected kWindow at a time
+// (kOut apart per central) in the memory of the positions.
+constexpr int kList = 640, kWords = kList / 4 / 32, kTilesPage = 16, kRow = 4 * kTilesPage + 4;
+constexpr int kWindow = 128, kOut = kWindow + 8;
+constexpr float kSlack = 0x1p-17f;
+constexpr uint32_t kNoCandidate = ~0u;  // (no image code has all bits set in a field)
+typedef float vf4 __attribute__((ext_vector_type(4)));
 
-// The split j-list of one central particle written from its brick-local
-// list (w entries, already in global memory, in scan order), entry k of the
-// lanes of a wave in one store.  The staged word of each entry's particle
-// holds its staged cell t (kCellShift); the cell gives the particle index
-// (slot - cDelta[t]) and, from the offset t - tc to the central's cell, the
-// image code (sCode[t - tc + S - 1]).  Returns n_fluid | n_boundary << 16.
-template <int BX, int BY, int BZ>
-__device__ __forceinline__ uint32_t brick_jlists(int tc, int M, int w, const int *cDelta, const uint32_t *sCode,
-                                                 const float4 *sPos, uint32_t *tile, const uint16_t *ltile)
+template <int BX, int BY, int BZ, int NW>
+struct ScanTables {
+    static constexpr int S = Staging<BX, BY, BZ>::S, NI = Staging<BX, BY, BZ>::NI;
+    struct Wave {
+        int4 cell[27];  // of the neighbour cells with candidates: slot of a candidate - its place,
+                        // end of the fluid prefix, image code - delta
+        alignas(16) union {
+            float page[4][4 * kRow];  // x, y, z, |p|^2
+            uint16_t out[16][kOut];   // places of a central's neighbours, times 4
+        };
+        // by place: entry of the split list, slot; [kList]: 0, for the rest of a group
+        uint32_t code[kList + 4];
+        uint16_t slot[kList + 8];
+        alignas(8) uint32_t marks[kList / 32];  // first candidates of a cell, then boundary candidates
+    } wave[NW];
+    float4 shift[64];  // by the image code: the shift d cs of a candidate
+    int base[S + 1], delta[S];  // first slot of each staged cell, slot - particle index
+    int fluid_end[S];           // end of the fluid prefix of each staged cell (slot)
+    int first[NI + 1];          // first central of each inner cell
+    int wsum[NW];
+    int item;                 // work items taken
+    int most, over;             // most neighbours found, centrals with more than max_neibs
+};
+
+// Orders the LDS accesses of the lanes of a wave.
+__device__ __forceinline__ void wave_fence()
 {
-    constexpr int S = Staging<BX, BY, BZ>::S;
-    uint32_t *tf = tile, *tb = tile + (size_t)(M - 1) * kWave;
-    const uint4 *lg = (const uint4 *)ltile;
-    uint4 grp = make_uint4(0u, 0u, 0u, 0u);
-    const uint32_t *code = sCode + (S - 1 - tc);
-    for (int e = 0; e < w; ++e) {
-        if ((e & (kBrickGroup - 1)) == 0) grp = lg[(size_t)(e / kBrickGroup) * kWave];
-        const int word = e >> 1 & 3;
-        const uint32_t pair = word == 0 ? grp.x : word == 1 ? grp.y : word == 2 ? grp.z : grp.w;
-        const int sl = (int)(pair >> ((e & 1) * 16) & 0xFFFFu);
-        const uint32_t ws = __float_as_uint(sPos[sl].w);
-        const int t = (int)(ws >> kCellShift & kCellMask);
-        const bool nb_boundary = ptype(ws) == kBoundary;
-        *(nb_boundary ? tb : tf) = (uint32_t)(sl - cDelta[t]) | code[t];
-        tf += nb_boundary ? 0 : kWave;
-        tb -= nb_boundary ? kWave : 0;
-    }
-    const int wf = (int)((tf - tile) / kWave), wb = w - wf;
-    return (uint32_t)wf | (uint32_t)wb << 16;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-template <int BX, int BY, int BZ, bool LDS>
-__device__ __forceinline__ uint32_t brick_scan(int i, int tc, int M, const float4 &pi, bool central_boundary,
-                                               const int *cBase, const int *cDelta, const int *cFluidEnd,
-                                               const float4 *sPos, const float4 *__restrict__ gpos,
-                                               const uint32_t *__restrict__ ginfo, float csx, float csy, float csz,
-                                               float rs2, uint32_t *tile, uint16_t *ltile, int &total_found)
+struct ScanArgs {
+    const float4 *__restrict__ pos;
+    float csx, csy, csz, rs2;
+    int M;
+    uint32_t *__restrict__ neibs;
+    uint16_t *__restrict__ neibs_brick;
+    uint32_t *__restrict__ neib_count;
+};
+
+// The lists of the centrals of one work item (bound: the boundary centrals) of
+// staged cell tc: centrals slots q_begin .. q_begin + nq - 1.
+template <int BX, int BY, int BZ, int NW>
+__device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const ScanArgs &A, int tc, bool bound,
+                                          int q_begin, int nq, int &most, int &over)
 {
-    // Each neighbour cell is scanned in chunks of up to 64 candidates in two
-    // phases: the predicate alone, one bit per hit in a 64-bit mask, then the
-    // hits in slot order, written as before.  Only about one candidate in six
-    // is a hit, so the writing work runs per hit instead of per candidate.
-    int found = 0, w = 0;
-    // write positions: the next fluid slot from the front, the next boundary
-    // slot from the back; the brick-local entries of the current group of 8
-    // are collected in registers and stored as one 16-byte group when it is
-    // full (groups are kWave x 8 entries apart), the last one at the end.
-    // (With the brick staged in LDS and brick-local lists asked for, the
-    // cell form of the scan runs instead.)
-    uint32_t *tf = tile, *tb = tile + (size_t)(M - 1) * kWave;
-    uint4 *lg = (uint4 *)ltile;
-    uint4 grp = make_uint4(0u, 0u, 0u, 0u);
-    for (int dz = -1; dz <= 1; ++dz) {
-        const float t2z = cell_shift(-dz, csz);
-        for (int dy = -1; dy <= 1; ++dy) {
-            const float t2y = cell_shift(-dy, csy);
-            for (int dx = -1; dx <= 1; ++dx) {
-                const float t2x = cell_shift(-dx, csx);
-                const int t = tc + Staging<BX, BY, BZ>::step(dx, dy, dz);
-                const int s0 = cBase[t];
-                const int s1 = central_boundary ? cFluidEnd[t] : cBase[t + 1];
-                const int delta = cDelta[t];
-                const uint32_t code = pack_neib(0u, -dx, -dy, -dz);
-                // the central itself can only be met in its own cell (the 27
-                // cells are distinct grid cells), at slot i + delta there
-                const int self_sl = (dx | dy | dz) == 0 ? i + delta : -1;
-                for (int c0 = s0; c0 < s1; c0 += 64) {
-                    const int m = min(s1 - c0, 64);
-                    // hit bits of the chunk, candidates 0..31 and 32..63 in a
-                    // 32-bit word each (the bit of candidate k is uniform)
-                    uint32_t hlo = 0u, hhi = 0u;
-                    // two candidates in flight per lane (the LDS read latency)
-#pragma unroll 2
-                    for (int k = 0; k < min(m, 32); ++k) {
-                        const int sl = c0 + k;
-                        const float4 pj = LDS ? sPos[sl] : gpos[sl - delta];
-                        const float r2 = predicate_r2(pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, t2x, t2y, t2z);
-                        hlo = r2 < rs2 ? hlo | 1u << k : hlo;
+    using St = Staging<BX, BY, BZ>;
+    // (opaque: what follows from the lane is computed for each item, not kept in registers across them)
+    unsigned lane_bits = threadIdx.x;
+    asm volatile("" : "+v"(lane_bits));
+    const int lane = lane_bits % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int quarter = lane / 16, m = lane % 16, M = A.M, G = brick_groups(M);
+    auto &W = T.wave[wave];
+    const float slack = kSlack * (A.csx * A.csx + A.csy * A.csy + A.csz * A.csz);
+    const float farthest = slack * (0.2505f / kSlack);  // the |o|^2 up to which the slack holds
+    const int to_index = __builtin_amdgcn_readfirstlane(-T.delta[tc]);
+
+    auto of_quarter = [&](int v, int q) { return __builtin_amdgcn_ds_bpermute(4 * (16 * q + m), v); };
+
+    // candidate ranges of the 27 cells, lane k < 27 (k = 9 (dz+1) + 3 (dy+1) + dx+1);
+    // tables of those that have any, in order
+    int beg = 0, len = 0;
+    const int dx = lane % 3 - 1, dy = (lane / 3) % 3 - 1, dz = lane / 9 - 1;
+    const int t_cell = lane < 27 ? tc + St::step(dx, dy, dz) : tc;
+    if (lane < 27) {
+        beg = T.base[t_cell];
+        len = (bound ? T.fluid_end[t_cell] : T.base[t_cell + 1]) - beg;
+    }
+    int inc = len;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+        const int v = __builtin_amdgcn_ds_bpermute(4 * (lane - o), inc);
+        if (lane >= o) inc += v;
+    }
+    const int ex = inc - len;
+    const int n_cand = __builtin_amdgcn_readlane(inc, 26);
+    const int self0 = __builtin_amdgcn_readlane(ex, 13) - __builtin_amdgcn_readlane(beg, 13);  // place - slot
+    const uint64_t some = __builtin_amdgcn_ballot_w64(len > 0);
+    if (len > 0) {
+        const int r = (int)__popcll(some & ((1ull << lane) - 1ull));
+        W.cell[r] = make_int4(beg - ex, T.fluid_end[t_cell], (int)(pack_neib(0u, -dx, -dy, -dz) - (uint32_t)T.delta[t_cell]), 0);
+    }
+    if (lane == 0) W.code[kList] = W.slot[kList] = 0;
+    wave_fence();
+    bool mixed = false;  // boundary particles among the candidates
+
+    for (int q0 = 0; q0 < nq; q0 += 32) {  // uniform: two groups of 16 centrals
+        const bool two = nq - q0 > 16;
+        // this lane's central of each group: its index, operand, counts of
+        // neighbours found and of fluid ones kept
+        int index[2], found[2] = {0, 0}, fluid[2] = {0, 0};
+        float bop[2], c_init[2];
+        bool has[2], odd = false;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int q = q0 + 16 * c + m;
+            has[c] = q < nq;
+            index[c] = q_begin + min(q, nq - 1) + to_index;
+            const float4 o = A.pos[index[c]];
+            bop[c] = quarter == 0 ? -2.0f * o.x : quarter == 1 ? -2.0f * o.y : quarter == 2 ? -2.0f * o.z : 1.0f;
+            odd |= !(fmaf(o.x, o.x, fmaf(o.y, o.y, o.z * o.z)) <= farthest);
+            c_init[c] = fmaf(o.x, o.x, fmaf(o.y, o.y, fmaf(o.z, o.z, -A.rs2)));
+        }
+        for (int pg = 0; pg < n_cand; pg += kList) {  // uniform
+            const int np = min(n_cand - pg, kList);
+            const int tiles = 4 * ((np + 63) / 64), Q = 4 * tiles;  // of a quarter: Q candidates
+            if (q0 == 0 || n_cand > kList) {
+                // 1. the list: a mark at the first candidate of each cell but
+                //    the first; a candidate's cell is the count of marks up to it
+                if (lane < kList / 32) W.marks[lane] = 0u;
+                wave_fence();
+                const int mark = ex - pg;
+                if (len > 0 && mark > 0 && mark < kList) atomicOr(&W.marks[mark >> 5], 1u << (mark & 31));
+                wave_fence();
+                const uint32_t marks = lane < kList / 32 ? W.marks[lane] : 0u;
+                int before = (int)__popcll(__builtin_amdgcn_ballot_w64(len > 0 && mark <= 0)) - 1;
+                for (int ch = 0; ch < Q / 16; ++ch) {  // uniform
+                    const uint32_t lo = __builtin_amdgcn_readlane(marks, 2 * ch);
+                    const uint32_t hi = __builtin_amdgcn_readlane(marks, 2 * ch + 1);
+                    const uint64_t mm = ((uint64_t)hi << 32 | lo) >> 1;
+                    const int k = __builtin_amdgcn_mbcnt_hi((uint32_t)(mm >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mm, before + (int)(lo & 1u)));
+                    before += __popc(lo) + __popc(hi);
+                    const int f = 64 * ch + lane;
+                    const int4 c = W.cell[k];
+                    const int sl = f + pg + c.x;
+                    const uint64_t b = __builtin_amdgcn_ballot_w64(f < np && sl >= c.y);
+                    mixed |= b != 0;
+                    W.code[f] = (uint32_t)(sl + c.z);
+                    W.slot[f] = (uint16_t)sl;
+                    if (lane == 0) *(uint64_t *)&W.marks[2 * ch] = b;
+                }
+                wave_fence();
+            }
+            // 2. hit words
+            uint32_t w[2][kWords];
+            const float *mine = &W.page[quarter][m / 4 * kRow + m % 4];
+#pragma unroll
+            for (int k = 0; k < kWords; ++k) {
+                w[0][k] = 0u;
+                w[1][k] = 0u;
+                if (8 * k >= tiles) continue;  // uniform
+                if (k % 2 == 0) {
+                    // the positions of the next kTilesPage tiles
+                    const int f0 = 32 * k + lane;
+                    float4 p[4];
+                    uint32_t code[4];
+                    wave_fence();
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int f = g * Q + f0;
+                        code[g] = f0 < Q && f < np ? W.code[f] : kNoCandidate;
+                        p[g] = code[g] != kNoCandidate ? A.pos[code[g] & kIndexMask] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                     }
-#pragma unroll 2
-                    for (int k = 32; k < m; ++k) {
-                        const int sl = c0 + k;
-                        const float4 pj = LDS ? sPos[sl] : gpos[sl - delta];
-                        const float r2 = predicate_r2(pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, t2x, t2y, t2z);
-                        hhi = r2 < rs2 ? hhi | 1u << (k - 32) : hhi;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        odd |= !(fmaf(p[g].x, p[g].x, fmaf(p[g].y, p[g].y, p[g].z * p[g].z)) <= farthest);
+                        const float4 d = T.shift[code[g] >> 26];
+                        const float x = p[g].x + d.x, y = p[g].y + d.y, z = p[g].z + d.z;
+                        W.page[0][g * kRow + lane] = x;
+                        W.page[1][g * kRow + lane] = y;
+                        W.page[2][g * kRow + lane] = z;
+                        W.page[3][g * kRow + lane] = code[g] != kNoCandidate ? fmaf(x, x, fmaf(y, y, z * z)) : 1e30f;
                     }
-                    uint64_t hits = (uint64_t)hhi << 32 | hlo;
-                    const int sk = self_sl - c0;
-                    if ((unsigned)sk < 64u) hits &= ~(1ull << sk);
-                    found += __popcll(hits);
-                    while (hits) {
-                        const int k = __ffsll((long long)hits) - 1;
-                        hits &= hits - 1;
-                        if (w < M) {
-                            const int sl = c0 + k;
-                            const int j = sl - delta;
-                            {
-                                const uint32_t inf = LDS ? __float_as_uint(sPos[sl].w) : ginfo[j];
-                                const bool nb_boundary = ptype(inf) == kBoundary;
-                                *(nb_boundary ? tb : tf) = (uint32_t)j | code;
-                                tf += nb_boundary ? 0 : kWave;
-                                tb -= nb_boundary ? kWave : 0;
-                            }
-                            if (ltile) {
-                                const int e = w & (kBrickGroup - 1);
-                                const uint32_t v = (uint32_t)min(sl, 0xFFFF) << ((e & 1) * 16);
-                                grp.x |= (e >> 1) == 0 ? v : 0u;
-                                grp.y |= (e >> 1) == 1 ? v : 0u;
-                                grp.z |= (e >> 1) == 2 ? v : 0u;
-                                grp.w |= (e >> 1) == 3 ? v : 0u;
-                                if (e == kBrickGroup - 1) {
-                                    lg[(size_t)(w / kBrickGroup) * kWave] = grp;
-                                    grp = make_uint4(0u, 0u, 0u, 0u);
-                                }
-                            }
-                            ++w;
+                    odd = __builtin_amdgcn_ballot_w64(odd) != 0;
+                    wave_fence();
+                }
+                constexpr int kHalf = 4 * kTilesPage / 2;  // candidates of a quarter in a word
+                const float *word = mine + (k % 2) * kHalf;
+                float least[2] = {1e30f, 1e30f};
+                const int part = min(tiles - 8 * k, 8);  // 4 or 8
+#pragma unroll 1
+                for (int b = 0; b < part; b += 4) {      // uniform
+                    float aop[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) aop[t] = word[4 * (b + t)];
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        if (c == 1 && !two) continue;  // uniform
+                        const vf4 c4 = {c_init[c], c_init[c], c_init[c], c_init[c]};
+                        vf4 r[4];  // (all four under way before the first is read)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            r[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop[t], bop[c], c4, 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                w[c][k] = __builtin_amdgcn_alignbit(w[c][k], __float_as_uint(r[t][e]), 31);
+                            least[c] = fminf(fminf(least[c], fabsf(r[t].x)), fabsf(r[t].y));
+                            least[c] = fminf(fminf(least[c], fabsf(r[t].z)), fabsf(r[t].w));
                         }
                     }
                 }
-            }
-        }
-    }
-    if (ltile && (w & (kBrickGroup - 1)) != 0) lg[(size_t)(w / kBrickGroup) * kWave] = grp;
-    const int wf = (int)((tf - tile) / kWave), wb = w - wf;
-    total_found = found;
-    return (uint32_t)wf | (uint32_t)wb << 16;
-}
-
-// Scan of the list build, cell form (brick staged in LDS, brick-local lists
-// asked for).  The work items are the kItemParts parts of each inner cell's
-// central particles (consecutive runs); a wave takes items from a counter.  For its item, the
-// wave lays the candidates of the cell's 27 neighbour cells, in scan order
-// (cells z, y, x from -1 to +1, each in slot order; only the fluid prefix of
-// each cell when the item's centrals are boundary particles), out over its
-// lanes in chunks of 64, one candidate per lane with its cell shift, and
-// tests every central of the item against each chunk: every lane busy on the
-// same central, no divergent trip counts.  The hits of a chunk are a ballot;
-// a hit's place in the central's list is the count of hits before it
-// (mbcnt), so the entries come out in scan order and the first max_neibs
-// found are kept, as in the lane-per-central form.  The brick-local entries
-// go straight to global memory (the groups of one central fill within the
-// item); the number found is kept in the low 30 bits of the central's staged
-// type word (its type bits stay: other waves read them); a candidate past
-// the cell set points at a dummy staged particle far away.
-constexpr int kItemChunks = 6;                 // candidate chunks held in registers per pass
-constexpr int kItemParts = 1;                  // work items per inner cell (its centrals split evenly)
-
-// Tests of one central (LDS slot si, position pi) against the nch candidate
-// chunks of the item; found: entries so far.  MASK_B: the central is a
-// boundary particle among fluid candidates (boundary candidates are skipped).
-// The hit mask of a chunk is formed from ballots of plain compares combined on
-// the scalar unit (a ballot of a combined lane predicate would first be turned
-// into a vector of 0/1 and compared again); a hit's entry is stored at its
-// byte offset from the central's (uniform) group base.
-template <bool MASK_B>
-__device__ __forceinline__ int scan_central(int found, uint32_t si, const float4 &pi, int nch, const int *sa,
-                                            const float *tx, const float *ty, const float *tz, const float4 *sPos,
-                                            float rs2, int M, uint16_t *__restrict__ lt)
-{
 #pragma unroll
-    for (int c = 0; c < kItemChunks; ++c) {
-        if (c < nch) {  // uniform (scalar)
-            const uint32_t slot = (uint32_t)sa[c];
-            const float4 pj = sPos[slot];
-            const float r2 = predicate_r2(pi.x, pi.y, pi.z, pj.x, pj.y, pj.z, tx[c], ty[c], tz[c]);
-            const bool in = r2 < rs2, other = slot != si;
-            unsigned long long H = __builtin_amdgcn_ballot_w64(in) & __builtin_amdgcn_ballot_w64(other);
-            bool fluid = true;
-            if constexpr (MASK_B) {
-                fluid = ptype(__float_as_uint(pj.w)) != kBoundary;
-                H &= __builtin_amdgcn_ballot_w64(fluid);
+                for (int c = 0; c < 2; ++c) {
+                    if (c == 1 && !two) continue;  // uniform
+                    if (__builtin_amdgcn_ballot_w64(odd || (has[c] && least[c] < slack))) {  // uniform, rare
+                        // the candidates of the word that are that near
+                        const vf4 c4 = {c_init[c], c_init[c], c_init[c], c_init[c]};
+                        uint32_t near = 0u;
+#pragma unroll 1
+                        for (int t = 0; t < part; ++t) {
+                            const vf4 r = __builtin_amdgcn_mfma_f32_16x16x4f32(word[4 * t], bop[c], c4, 0, 0, 0);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                near = __builtin_amdgcn_alignbit(near, __float_as_uint(fabsf(r[e]) - slack), 31);
+                        }
+                        if (odd) {  // uniform: all there are
+                            const int there = min(max(np - (quarter * Q + 32 * k), 0), 4 * part);
+                            near = (uint32_t)(((1ull << there) - 1ull) << (4 * part - there));
+                        }
+                        if (!has[c]) near = 0u;
+                        const float4 o = A.pos[index[c]];
+                        auto listed = [&](uint32_t bit) {
+                            const uint32_t e = W.code[quarter * Q + 32 * k + 4 * part - __ffs((int)bit)];
+                            const float4 d = T.shift[e >> 26], p = A.pos[e & kIndexMask];
+                            return predicate_r2(o.x, o.y, o.z, p.x, p.y, p.z, -d.x, -d.y, -d.z) < A.rs2 ? bit : 0u;
+                        };
+                        while (near) {  // two at a time
+                            const uint32_t b0 = near & (0u - near), rest = near ^ b0, b1 = rest ? rest & (0u - rest) : b0;
+                            near = rest & ~b1;
+                            const uint32_t h0 = listed(b0), h1 = listed(b1);
+                            w[c][k] = (w[c][k] & ~(b0 | b1)) | h0 | h1;
+                        }
+                    }
+                    if (part == 4) w[c][k] <<= 16;  // (the first candidate of a word is its top bit)
+                }
             }
-            if (H) {  // uniform
-                const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(H >> 32),
-                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)H, (uint32_t)found));
-                // brick_entry layout: group pos / 8 at 1024-byte stride, entry pos % 8
-                const uint32_t boff = ((pos >> 3) << 10) | ((pos & 7u) << 1);
-                if (in && other && fluid && pos < (uint32_t)M)
-                    *reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lt) + boff) = (uint16_t)slot;
-                found += (int)__popcll(H);
+            // 3. entries
+#pragma unroll 1
+            for (int c = 0; c < (two ? 2 : 1); ++c) {  // uniform
+                const int i = c ? index[1] : index[0];
+                // the central itself is no neighbour (its place in this
+                // quarter; a boundary central is not among its candidates)
+                const int self = bound ? -1 : i - to_index + self0 - pg - quarter * Q;
+                uint32_t hits[kWords];
+                int mine_n = 0;
+#pragma unroll
+                for (int k = 0; k < kWords; ++k) {
+                    hits[k] = c ? w[1][k] : w[0][k];
+                    if (self >= 0 && self < Q && self >> 5 == k) hits[k] &= ~(0x80000000u >> (self & 31));
+                    if (!(c ? has[1] : has[0])) hits[k] = 0u;
+                    mine_n += __popc(hits[k]);
+                }
+                const int n0 = of_quarter(mine_n, 0), n1 = of_quarter(mine_n, 1), n2 = of_quarter(mine_n, 2),
+                          n3 = of_quarter(mine_n, 3);
+                const int f0 = c ? found[1] : found[0], f1 = f0 + n0 + n1 + n2 + n3;
+                const int from = f0 + (quarter > 0 ? n0 : 0) + (quarter > 1 ? n1 : 0) + (quarter > 2 ? n2 : 0);
+                int fluid_c = c ? fluid[1] : fluid[0];
+                const int kept = min(f1, M);  // entries f0 .. kept - 1 are written
+                uint32_t *tile = A.neibs + (size_t)(i / kWave) * kWave * M + (i % kWave);
+                uint4 *lt = A.neibs_brick ? (uint4 *)(A.neibs_brick + brick_entry(i, 0, G)) : nullptr;
+                // windows of kWindow entries (one, but for long lists)
+                for (int win = f0 & ~(kBrickGroup - 1); __builtin_amdgcn_ballot_w64(win < kept); win += kWindow) {
+                    wave_fence();
+                    uint16_t *out = &W.out[m][0];
+                    if (!__builtin_amdgcn_ballot_w64(f1 - win > kWindow || from < win)) {  // uniform: all in this one
+                        uint16_t *to = out + (from - win);
+#pragma unroll
+                        for (int k = 0; k < kWords; ++k) {
+                            const int place = 4 * (quarter * Q + 32 * k);
+                            for (uint32_t left = __brev(hits[k]); left; left &= left - 1u)
+                                *to++ = (uint16_t)(place + 4 * __builtin_ctz(left));
+                        }
+                    } else {
+                        int at = from - win;
+#pragma unroll 1
+                        for (int f = 0; f < 32 * kWords; ++f) {
+                            uint32_t h = hits[0];
+#pragma unroll
+                            for (int k = 1; k < kWords; ++k) h = f >> 5 == k ? hits[k] : h;
+                            if (!(h << (f & 31) >> 31)) continue;
+                            if ((unsigned)at < (unsigned)kWindow) out[at] = (uint16_t)(4 * (quarter * Q + f));
+                            ++at;
+                        }
+                    }
+                    wave_fence();
+                    // the rest of the last group
+                    const int end = kept - win;
+                    if (end >= 0 && end < kWindow) {
+                        for (int e = end + quarter; e < ((end + kBrickGroup - 1) & ~(kBrickGroup - 1)); e += 4)
+                            out[e] = 4 * kList;
+                    }
+                    wave_fence();
+                    const bool plain = !mixed && pg == 0;  // uniform: fluid entries from the first
+                    if (plain) fluid_c = kept;
+                    const char *codes = (const char *)W.code, *slots = (const char *)W.slot;
+#pragma unroll 1
+                    for (int g0 = 0; g0 < kWindow; g0 += 4 * kBrickGroup) {
+                        if (!__builtin_amdgcn_ballot_w64(win + g0 < kept)) break;  // uniform
+                        const int e0 = win + g0 + quarter * kBrickGroup;  // this lane's group of entries
+                        const int lo = max(f0 - e0, 0), hi = min(kept - e0, kBrickGroup);  // those of it to write
+                        const uint4 grp = *(const uint4 *)(out + g0 + quarter * kBrickGroup);
+                        const uint32_t pairs[4] = {grp.x, grp.y, grp.z, grp.w};
+                        if (plain) {
+                            if (hi > 0) {
+                                uint32_t e[kBrickGroup], v[kBrickGroup / 2];
+#pragma unroll
+                                for (int x = 0; x < kBrickGroup; ++x)
+                                    e[x] = *(const uint32_t *)(codes + (x & 1 ? pairs[x / 2] >> 16 : pairs[x / 2] & 0xFFFFu));
+                                if (lt) {
+#pragma unroll
+                                    for (int x = 0; x < kBrickGroup / 2; ++x)
+                                        v[x] = *(const uint16_t *)(slots + ((pairs[x] & 0xFFFFu) >> 1)) |
+                                               (uint32_t) * (const uint16_t *)(slots + (pairs[x] >> 17)) << 16;
+                                    lt[(size_t)(e0 / kBrickGroup) * kWave] = make_uint4(v[0], v[1], v[2], v[3]);
+                                }
+                                uint32_t *to = tile + (size_t)e0 * kWave;
+                                if (__builtin_amdgcn_ballot_w64(hi < kBrickGroup)) {  // uniform
+#pragma unroll
+                                    for (int x = 0; x < kBrickGroup; ++x)
+                                        if (x < hi) to[x * kWave] = e[x];
+                                } else {
+#pragma unroll
+                                    for (int x = 0; x < kBrickGroup; ++x) to[x * kWave] = e[x];
+                                }
+                            }
+                            continue;
+                        }
+                        uint32_t e[kBrickGroup], v[kBrickGroup / 2] = {}, b_bits = 0u;
+#pragma unroll
+                        for (int x = 0; x < kBrickGroup; ++x) {
+                            const bool in = x >= lo && x < hi;
+                            const uint32_t pl = in ? (x & 1 ? pairs[x / 2] >> 16 : pairs[x / 2] & 0xFFFFu) : 4u * kList;
+                            e[x] = *(const uint32_t *)(codes + pl);
+                            v[x / 2] |= (uint32_t) * (const uint16_t *)(slots + pl / 2) << (x % 2 * 16);
+                            b_bits |= (in ? W.marks[pl / 128] >> (pl / 4 % 32) & 1u : 0u) << x;
+                        }
+                        // boundary entries and entries of the quarters before this one
+                        const int nb = __popc(b_bits), nn = max(hi - lo, 0);
+                        const int both = nn << 16 | nb;
+                        const int s0 = of_quarter(both, 0), s1 = of_quarter(both, 1), s2 = of_quarter(both, 2),
+                                  s3 = of_quarter(both, 3);
+                        const int pre = (quarter > 0 ? s0 : 0) + (quarter > 1 ? s1 : 0) + (quarter > 2 ? s2 : 0);
+                        const int sum = s0 + s1 + s2 + s3;
+                        int fl = fluid_c + (pre >> 16) - (pre & 0xFFFF);             // fluid entries before
+                        int bo = e0 + lo - fl;                                       // boundary entries before
+                        fluid_c += (sum >> 16) - (sum & 0xFFFF);
+                        if (hi > lo) {
+                            if (lt) {
+                                uint4 *to = lt + (size_t)(e0 / kBrickGroup) * kWave;
+                                if (lo == 0) {
+                                    *to = make_uint4(v[0], v[1], v[2], v[3]);
+                                } else {  // the group's first entries are from the page before
+#pragma unroll
+                                    for (int x = 1; x < kBrickGroup; ++x)
+                                        if (x >= lo) ((uint16_t *)to)[x] = (uint16_t)(v[x / 2] >> (x % 2 * 16));
+                                }
+                            }
+#pragma unroll
+                            for (int x = 0; x < kBrickGroup; ++x) {
+                                if (x < lo || x >= hi) continue;
+                                const bool b = b_bits >> x & 1u;
+                                tile[(size_t)(b ? M - 1 - bo : fl) * kWave] = e[x];
+                                bo += b ? 1 : 0;
+                                fl += b ? 0 : 1;
+                            }
+                        }
+                    }
+                }
+                if (c) {
+                    found[1] = f1;
+                    fluid[1] = fluid_c;
+                } else {
+                    found[0] = f1;
+                    fluid[0] = fluid_c;
+                }
             }
         }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (!has[c] || quarter != 0) continue;
+            const int kept = min(found[c], M);
+            A.neib_count[index[c]] = (uint32_t)fluid[c] | (uint32_t)(kept - fluid[c]) << 16;
+            most = max(most, found[c]);
+            over += found[c] > M;
+        }
     }
-    return found;
 }
 
-template <int BX, int BY, int BZ>
-__device__ __forceinline__ void brick_scan_items(int M, int *sItem, const int *cBase, const int *cDelta,
-                                                 const int *cFluidEnd, const int *iBase, const int *iStart,
-                                                 float4 *sPos, int dummy_slot, float csx, float csy, float csz,
-                                                 float rs2, uint16_t *__restrict__ neibs_brick)
+// Workgroups of 4 waves, four to a CU (128 VGPRs, 33 KB of LDS), so that the
+// ranges of one are read while the others scan.
+constexpr int kBuildThreads = 256, kBuildResident = 4;
+
+// The inner cells per workgroup for n bricks of NI cells: a multiple of the 4
+// waves that share them, 12, or fewer while two rounds of workgroups take them
+// all.  The whole build, by cells per workgroup: 1.62M-particle dam break, 3464
+// bricks of 36 cells with a particle: 736 us (36), 671 (18), 641 (12), 687 (9), 719
+// (6); 169k dam break, 672 bricks of 18 cells, ten steps with a build: 826
+// (18), 777 (9), 759 (6), 758 (3); tank of 27 bricks: 575 (9), 548 (6), 525 (4), 522 (3).
+template <int NI>
+__device__ __forceinline__ int scan_cells(int n, int resident)
+{
+    int cells = 12;
+    if (n * ((NI + 7) / 8) <= 2 * resident) cells = 8;
+    if (n * ((NI + 3) / 4) <= 2 * resident) cells = 4;
+    return cells;
+}
+
+// One workgroup per part of a brick.
+template <int BX, int BY, int BZ, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kBuildResident))) void k_build_brick(
+    ScanArgs A, const uint32_t *__restrict__ info, const int32_t *__restrict__ start, BrickGrid G,
+    const int32_t *__restrict__ active, int resident, int32_t *__restrict__ status,
+    uint8_t *__restrict__ keys)
 {
     using St = Staging<BX, BY, BZ>;
-    constexpr int NI = St::NI;
-    const int lane = threadIdx.x % kWave;
-    const int G = brick_groups(M);
-    for (;;) {
-        int item = 0;
-        if (lane == 0) item = atomicAdd(sItem, 1);
-        item = __builtin_amdgcn_readfirstlane(__shfl(item, 0));
-        if (item >= kItemParts * NI) break;  // uniform
-        const int u = item / kItemParts, part = item % kItemParts;
-        const int n_u = iBase[u + 1] - iBase[u];
-        const int qa = part * n_u / kItemParts, qb = (part + 1) * n_u / kItemParts;
-        if (qa >= qb) continue;  // uniform
-        const int tc = St::inner(u);
-        const int i0 = iStart[u];
-        const int sdel = cDelta[tc];
-        // centrals are fluid first: a boundary one first means all are
-        const bool fluid_only = ptype(__float_as_uint(sPos[i0 + qa + sdel].w)) == kBoundary;
-        // candidate ranges of the 27 cells, lane k < 27 (k = 9 (dz+1) + 3 (dy+1) + dx+1)
-        int beg = 0, len = 0;
-        if (lane < 27) {
-            const int t = tc + St::step(lane % 3 - 1, (lane / 3) % 3 - 1, lane / 9 - 1);
-            beg = cBase[t];
-            len = (fluid_only ? cFluidEnd[t] : cBase[t + 1]) - beg;
-        }
-        // inclusive scan over lanes 0..26; the lane id is read afresh (opaque
-        // to the compiler) so that the shuffle addresses are not kept live
-        // across the whole item loop
-        int incl = len, me;
-        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0" : "=v"(me));
-#pragma unroll
-        for (int o = 1; o < 32; o <<= 1) {
-            const int v = __builtin_amdgcn_ds_bpermute((me - o) << 2, incl);
-            if (me >= o) incl += v;
-        }
-        const int ex = incl - len;
-        const int ncand = __builtin_amdgcn_readfirstlane(__shfl(incl, 26));
-        if (ncand == 0) {  // uniform: no candidate (boundary centrals far from the fluid)
-            for (int q = qa + lane; q < qb; q += kWave) {
-                uint32_t *wq = reinterpret_cast<uint32_t *>(&sPos[i0 + q + sdel]) + 3;
-                *wq &= ~kFoundMask;
-            }
-            continue;
-        }
-        for (int pg = 0; pg < ncand; pg += kItemChunks * kWave) {
-            int sa[kItemChunks];
-            float tx[kItemChunks], ty[kItemChunks], tz[kItemChunks];
-#pragma unroll
-            for (int c = 0; c < kItemChunks; ++c) {
-                const int idx = pg + c * kWave + lane;
-                int lo = 0, hi = 26;  // the last cell k with ex_k <= idx
-#pragma unroll
-                for (int st = 0; st < 5; ++st) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (__shfl(ex, mid) <= idx) lo = mid;
-                    else hi = mid - 1;
-                }
-                const int b = __shfl(beg, lo), e = __shfl(ex, lo);
-                sa[c] = idx < ncand ? b + (idx - e) : dummy_slot;
-                // k_d = c_i - c_j = -(d) for the neighbour cell at offset d
-                tx[c] = cell_shift(1 - lo % 3, csx);
-                ty[c] = cell_shift(1 - (lo / 3) % 3, csy);
-                tz[c] = cell_shift(1 - lo / 9, csz);
-            }
-            const int nch = min(kItemChunks, (ncand - pg + kWave - 1) / kWave);
-            const bool last_page = pg + kItemChunks * kWave >= ncand;
-            for (int q = qa; q < qb; ++q) {  // uniform
-                const int i = __builtin_amdgcn_readfirstlane(i0 + q), si = i + sdel;
-                const float4 pi = sPos[si];
-                const uint32_t wi = __builtin_amdgcn_readfirstlane(__float_as_uint(pi.w));
-                int found = pg == 0 ? 0 : (int)(wi & kFoundMask);
-                uint16_t *lt = neibs_brick + brick_entry(i, 0, G);
-                // a boundary central among fluid ones takes fluid neighbours only
-                if (!fluid_only && ptype(wi) == kBoundary)
-                    found = scan_central<true>(found, si, pi, nch, sa, tx, ty, tz, sPos, rs2, M, lt);
-                else
-                    found = scan_central<false>(found, si, pi, nch, sa, tx, ty, tz, sPos, rs2, M, lt);
-                if (last_page) {
-                    // zero the rest of the last group, so the lists are the same bytes
-                    // whatever the array held
-                    const int w = min(found, M);
-                    const int wend = min((w + kBrickGroup - 1) & ~(kBrickGroup - 1), G * kBrickGroup);
-                    const int e = w + lane;
-                    if (e < wend) lt[((e >> 3) << 9) | (e & 7)] = 0;
-                }
-                if (lane == 0)
-                    reinterpret_cast<uint32_t *>(&sPos[si])[3] =
-                        (wi & ~kFoundMask) | (uint32_t)min(found, (int)kFoundMask);
-            }
-        }
-    }
-}
-
-template <int BX, int BY, int BZ, int NT, int CAP>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 128))) void k_build_brick(int n, int max_neibs, const float4 *__restrict__ pos,
-                                                    const uint32_t *__restrict__ info,
-                                                    const int32_t *__restrict__ start, BrickGrid G, float csx,
-                                                    float csy, float csz, float rs2,
-                                                    const int32_t *__restrict__ active,
-                                                    uint32_t *__restrict__ neibs,
-                                                    uint16_t *__restrict__ neibs_brick,
-                                                    uint32_t *__restrict__ neib_count,
-                                                    int32_t *__restrict__ status, uint8_t *__restrict__ keys)
-{
-    constexpr int SX = BX + 2, SY = BY + 2, SZ = BZ + 2;
-    constexpr int S = SX * SY * SZ;
-    constexpr int NI = BX * BY * BZ;
+    constexpr int SX = St::SX, SZ = St::SZ, S = St::S, NI = St::NI, IROW = BX * BZ;
     static_assert(S <= NT && NI <= NT, "one thread per cell");
-    __shared__ float4 sPos[CAP];  // xyz offset, w = type/id word
-    __shared__ int cBase[S + 1];
-    __shared__ int cDelta[S];
-    __shared__ int cFluidEnd[S];  // end of the fluid prefix of each staged cell (slot)
-    __shared__ int iBase[NI + 1];
-    __shared__ int iStart[NI];
-    __shared__ int wsum[NT / kWave];
-    __shared__ int sItem;  // work items taken (cell form of the scan)
-    // image code of the neighbour cell at staged offset d = t - tc from the
-    // central's cell, at index d + S - 1 (offsets that are no neighbour: 0)
-    __shared__ uint32_t sCode[2 * S - 1];
-    static_assert(S - 1 <= (int)kCellMask, "the staged cell fits its field of the staged word");
+    __shared__ ScanTables<BX, BY, BZ, NT / kWave> T;
 
     const int tid = threadIdx.x;
-    if ((int)blockIdx.x >= active[0]) return;
-    for (int k = tid; k < 2 * S - 1; k += NT) {  // (read after the staging barrier)
-        // d = dx + SX (dz + SZ dy) with dx, dy, dz in {-1, 0, 1}, d + S - 1 = k
-        const int e = k - (S - 1) + 1 + SX + SX * SZ;
-        const int ex = e % SX, ez = (e / SX) % SZ, ey = e / (SX * SZ);
-        const bool nb = e >= 0 && ex <= 2 && ez <= 2 && ey <= 2;
-        sCode[k] = nb ? pack_neib(0u, 1 - ex, 1 - ey, 1 - ez) : 0u;
-    }
-    const int b = active[1 + blockIdx.x];
+    const int cells = scan_cells<NI>(active[0], resident), parts = (NI + cells - 1) / cells;
+    if ((int)blockIdx.x >= active[0] * parts) return;
+    const int b = active[1 + blockIdx.x / parts];
     const int cx0 = (b % G.nbx) * BX, cy0 = ((b / G.nbx) % G.nby) * BY, cz0 = (b / (G.nbx * G.nby)) * BZ;
 
-    // 1. ranges of the staged cells and their LDS bases
+    if (tid < 64) {
+        auto offset = [](int bits) { return (float)(-((bits & 3) - (bits & 2) * 2)); };
+        T.shift[tid] = make_float4(offset(tid) * A.csx, offset(tid >> 2) * A.csy, offset(tid >> 4) * A.csz, 0.0f);
+    }
+
+    // ranges of the staged cells and their slots in the brick's staging order
     int st = 0, cnt = 0;
     if (tid < S) {
-        using St = Staging<BX, BY, BZ>;
         int gx = cx0 - 1 + St::sx_of(tid), gy = cy0 - 1 + St::sy_of(tid), gz = cz0 - 1 + St::sz_of(tid);
         const bool ok = wrap_axis(gx, G.nx, G.periodic & 1u) && wrap_axis(gy, G.ny, (G.periodic >> 1) & 1u) &&
                         wrap_axis(gz, G.nz, (G.periodic >> 2) & 1u);
@@ -786,126 +918,67 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 128))) 
         }
     }
     int total;
-    const int ex = block_scan<NT>(cnt, total, wsum);
+    const int ex = block_scan<NT>(cnt, total, T.wsum);
     if (tid < S) {
-        cBase[tid] = ex;
-        cDelta[tid] = ex - st;
-        cFluidEnd[tid] = ex + cnt;  // lowered below where the cell holds boundary particles
+        T.base[tid] = ex;
+        T.delta[tid] = ex - st;
+        T.fluid_end[tid] = ex + cnt;  // lowered below where the cell holds boundary particles
     }
-    if (tid == 0) cBase[S] = total;
+    if (tid == 0) {
+        T.base[S] = total;
+        T.item = T.most = T.over = 0;
+    }
     __syncthreads();
-    int icnt = 0, ist = 0;
+    int icnt = 0;
     // inner cells past the grid edge hold no centrals (on a periodic axis the
     // staged copy would be the wrapped cell, owned by another brick)
-    using St = Staging<BX, BY, BZ>;
     if (tid < NI && cx0 + St::ix_of(tid) < G.nx && cy0 + St::iy_of(tid) < G.ny && cz0 + St::iz_of(tid) < G.nz) {
         const int t = St::inner(tid);
-        icnt = cBase[t + 1] - cBase[t];
-        ist = cBase[t] - cDelta[t];
+        icnt = T.base[t + 1] - T.base[t];
     }
     int nc;
-    const int iex = block_scan<NT>(icnt, nc, wsum);
-    if (tid < NI) {
-        iBase[tid] = iex;
-        iStart[tid] = ist;
-    }
-    if (tid == 0) iBase[NI] = nc;
-    if (nc == 0) return;  // uniform: no particle in the brick
-    // (one staged slot past the brick is the cell form's dummy candidate)
-    const bool use_lds = total < CAP;
-    // the cell form of the scan needs the brick-local lists (the j-lists are
-    // written from them)
-    const bool cells = use_lds && neibs_brick != nullptr;
+    const int iex = block_scan<NT>(icnt, nc, T.wsum);
+    if (tid < NI) T.first[tid] = iex;
+    if (tid == 0) T.first[NI] = nc;
 
-    // 2. stage the brick and its halo (slot -> cell by binary search) and mark
-    //    the first boundary particle of each cell
-    for (int s2 = tid; s2 < total; s2 += NT) {
-        int lo = 0, hi = S - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (cBase[mid] <= s2) lo = mid;
-            else hi = mid - 1;
-        }
-        const int j = s2 - cDelta[lo];
-        const uint32_t inf = info[j];
-        if (use_lds) {
-            float4 p = pos[j];
-            p.w = __uint_as_float((inf & ~((1u << kTypeShift) - 1u)) | (uint32_t)lo << kCellShift);
-            sPos[s2] = p;
-        }
-        if (ptype(inf) == kBoundary && (s2 == cBase[lo] || ptype(info[j - 1]) != kBoundary)) cFluidEnd[lo] = s2;
-    }
-    if (cells && tid == 0) {
-        sPos[total] = make_float4(1e18f, 1e18f, 1e18f, 0.0f);  // no central is within r_s of it
-        sItem = 0;
+    // the part's inner cells; the fluid prefix of the cells of their rows and
+    // the halo of these, half a wave per cell
+    const int u0 = (int)blockIdx.x % parts * cells, u1 = min(u0 + cells, NI);
+    const int t_end = ((u1 - 1) / IROW + 3) * SX * SZ;
+#pragma unroll 4
+    for (int t = u0 / IROW * SX * SZ + tid / 32; t < t_end; t += NT / 32) {
+        const int s0 = T.base[t], s1 = T.base[t + 1], delta = T.delta[t];
+        for (int s2 = s0 + tid % 32; s2 < s1; s2 += 32)
+            if (ptype(info[s2 - delta]) == kBoundary) atomicMin(&T.fluid_end[t], s2);
     }
     __syncthreads();
 
-    if (cells) {
-        // 3a. the cell form of the scan: brick-local lists and counts found
-        brick_scan_items<BX, BY, BZ>(max_neibs, &sItem, cBase, cDelta, cFluidEnd, iBase, iStart, sPos, total, csx,
-                                     csy, csz, rs2, neibs_brick);
-        __syncthreads();
-        // 3b. one lane per central: its j-list from its brick-local list
-        for (int q0 = 0; q0 < nc; q0 += NT) {
-            const int q = q0 + tid;
-            if (q >= nc) break;
-            int lo = 0, hi = NI - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (iBase[mid] <= q) lo = mid;
-                else hi = mid - 1;
-            }
-            const int u = lo;
-            const int i = iStart[u] + (q - iBase[u]);
-            const int tc = St::inner(u);
-            const int found = (int)(__float_as_uint(sPos[i + cDelta[tc]].w) & kFoundMask);
-            const size_t toff = (size_t)(i / kWave) * kWave * max_neibs + (i % kWave);
-            const uint32_t cw = brick_jlists<BX, BY, BZ>(tc, max_neibs, min(found, max_neibs), cDelta, sCode, sPos,
-                                                         neibs + toff,
-                                                         neibs_brick + brick_entry(i, 0, brick_groups(max_neibs)));
-            neib_count[i] = cw;
-            if (cw) keys[b] = (uint8_t)brick_class<BX, BY, BZ>(nc);
-            atomicMax(&status[SPH_STATUS_MAX_NEIBS], found);
-            if (found > max_neibs) atomicAdd(&status[SPH_STATUS_OVERFLOW], 1);
-        }
-        return;
+    int most = 0, over = 0;
+    for (;;) {
+        int item = 0;
+        if (tid % kWave == 0) item = atomicAdd(&T.item, 1);
+        item = __builtin_amdgcn_readfirstlane(item);
+        if (item >= 2 * (u1 - u0)) break;  // uniform
+        const int u = u0 + item / 2, tc = St::inner(u);
+        const bool bound = item & 1;  // the cell's boundary centrals
+        const int all = __builtin_amdgcn_readfirstlane(T.first[u + 1] - T.first[u]);
+        if (all == 0) continue;  // uniform
+        const int c0 = __builtin_amdgcn_readfirstlane(T.base[tc]), cf = __builtin_amdgcn_readfirstlane(T.fluid_end[tc]);
+        const int nq = bound ? c0 + all - cf : cf - c0;
+        if (nq > 0) scan_item(T, A, tc, bound, bound ? cf : c0, nq, most, over);
     }
 
-    // 3. one lane per central particle of the brick
-    for (int q0 = 0; q0 < nc; q0 += NT) {
-        const int q = q0 + tid;
-        if (q >= nc) break;
-        int lo = 0, hi = NI - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (iBase[mid] <= q) lo = mid;
-            else hi = mid - 1;
-        }
-        const int u = lo;
-        const int i = iStart[u] + (q - iBase[u]);
-        const int tc = St::inner(u);
-        const float4 pi = pos[i];
-        const bool central_boundary = ptype(info[i]) == kBoundary;
-        const size_t toff = (size_t)(i / kWave) * kWave * max_neibs + (i % kWave);
-        uint32_t *tile = neibs + toff;
-        uint16_t *ltile = neibs_brick ? neibs_brick + brick_entry(i, 0, brick_groups(max_neibs)) : nullptr;
-        int found;
-        const uint32_t cw =
-            use_lds ? brick_scan<BX, BY, BZ, true>(i, tc, max_neibs, pi, central_boundary, cBase, cDelta, cFluidEnd,
-                                                   sPos, pos, info, csx, csy, csz, rs2, tile, ltile, found)
-                    : brick_scan<BX, BY, BZ, false>(i, tc, max_neibs, pi, central_boundary, cBase, cDelta,
-                                                    cFluidEnd, sPos, pos, info, csx, csy, csz, rs2, tile, ltile,
-                                                    found);
-        neib_count[i] = cw;
-        if (keys && cw) keys[b] = (uint8_t)brick_class<BX, BY, BZ>(nc);
-        atomicMax(&status[SPH_STATUS_MAX_NEIBS], found);
-        if (found > max_neibs) atomicAdd(&status[SPH_STATUS_OVERFLOW], 1);
+    // the workgroup's share of the status, and the brick's class where it has
+    // a pair (one atomic a workgroup: all of them are to the same word)
+    if (most) atomicMax(&T.most, most);
+    if (over) atomicAdd(&T.over, over);
+    __syncthreads();
+    if (tid == 0) {
+        if (T.most) atomicMax(&status[SPH_STATUS_MAX_NEIBS], T.most);
+        if (T.over) atomicAdd(&status[SPH_STATUS_OVERFLOW], T.over);
+        if (keys && T.most) keys[b] = (uint8_t)brick_class<BX, BY, BZ>(nc);
     }
 }
-
-constexpr int kBuildCap = 4800;  // 75 KB of LDS for the halo: two workgroups per CU
-static_assert(kBuildCap <= (int)kFoundMask, "a central's count of found neighbours fits its field");
 
 bool grid_ok(const sph_grid *g, float r_search)
 {
@@ -1021,11 +1094,16 @@ extern "C" sph_status sph_build_neighbors(const sph_grid *grid, const sph_params
         with_shape(shape, [&]<int BX, int BY, int BZ>() {
             const BrickGrid G = brick_grid<BX, BY, BZ>(grid->ncell, grid->periodic);
             const unsigned bricks = (unsigned)G.nbx * G.nby * G.nbz;
-            constexpr int NT = brick_threads(BX * BY * BZ);
+            // a workgroup per part of a brick: which bricks have work, and so
+            // the parts, is known on the device
+            constexpr int NI = BX * BY * BZ;
+            const int resident = kBuildResident * sph_device_cus();
+            const int items = max((int)bricks * ((NI + 11) / 12), min((int)bricks * ((NI + 3) / 4), 2 * resident));
             k_active_bricks<BX, BY, BZ><<<sph_blocks(bricks, 256), 256, 0, s>>>(cell_start, cell_end, G, active);
-            k_build_brick<BX, BY, BZ, NT, kBuildCap><<<bricks, NT, 0, s>>>(
-                n, max_neibs, pos, parts->info, start, G, grid->cell_size[0], grid->cell_size[1], grid->cell_size[2],
-                rs2, active, neibs, neibs_brick, neib_count, d_status, classes);
+            k_build_brick<BX, BY, BZ, kBuildThreads><<<items, kBuildThreads, 0, s>>>(
+                ScanArgs{pos, grid->cell_size[0], grid->cell_size[1], grid->cell_size[2], rs2, max_neibs, neibs,
+                         neibs_brick, neib_count},
+                parts->info, start, G, active, resident, d_status, classes);
         });
         SPH_CHECK_LAUNCH();
     }

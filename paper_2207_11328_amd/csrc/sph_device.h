@@ -49,12 +49,6 @@ __device__ __forceinline__ float predicate_r2(float oix, float oiy, float oiz, f
     return s + zz;
 }
 
-// k * cs for k in {-1, 0, 1}, exact.
-__device__ __forceinline__ float cell_shift(int k, float cs)
-{
-    return k == 0 ? 0.0f : (k > 0 ? cs : -cs);
-}
-
 // Neighbour entry: sorted index plus k_d = c_i,d - c_j,d in {-1, 0, 1} per
 // axis as two's-complement 2-bit fields at bits 26, 28, 30.
 __device__ __forceinline__ uint32_t pack_neib(uint32_t j, int kx, int ky, int kz)
@@ -95,9 +89,9 @@ __device__ __forceinline__ int list_slot(int k, int nf, int last, int M)
 
 // ---------------------------------------------------------------------------
 // Cell bricks: blocks of cells processed by one workgroup with the particles
-// of the brick and of its one-cell halo staged in LDS (used by the list build
-// and by the derivative kernel).
-// Bricks of cells: the unit of LDS staging of the list build and of the
+// of the brick and of its one-cell halo staged in LDS (by the derivative
+// kernels; the list build numbers them in the same order).
+// Bricks of cells: the unit of work of the list build and of LDS staging of the
 // derivative kernels.  The brick-local lists written by the build index the
 // staging order of the same bricks, so the build and its consumers take the
 // shape from the same grid description (sph_grid.brick).  Supported shapes,
@@ -124,10 +118,6 @@ inline void with_shape(int k, F &&f)
     default: f.template operator()<3, 4, 3>(); break;
     }
 }
-
-// Threads of a workgroup for bricks of `cells` cells: one lane per central
-// particle up to 27 per cell (the densest lattice alignment), in whole waves.
-constexpr int brick_threads(int cells) { return ((27 * cells + 63) / 64) * 64 > 1024 ? 1024 : ((27 * cells + 63) / 64) * 64; }
 
 // Staging geometry of a brick of BX x BY x BZ cells: the brick and its
 // one-cell halo, SX x SY x SZ staged cells numbered x fastest, then z, then y

@@ -1,0 +1,73 @@
+"""The matrix form of the list build where it can go wrong: cells at the edges
+of a group of 16 centrals, more candidates than a list page (640), more
+neighbours than a window of entries (128), lists cut in the middle of a window
+or a group of eight, walls.  Lists against the oracle's float32 build: they
+are whole numbers and have to be the same."""
+import numpy as np
+import pytest
+
+from workloads import scenes as S
+
+from parity import check_forces, compare_build, log, make_sim, oracle_forces_of, torch_sync
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# n, box side, wall share, max_neibs; the particles of a cell, of its neighbourhood
+SCENES = [
+    (2000, 0.3, 0.0, 160),    # 6 to 28: one page
+    (2000, 0.3, 0.3, 160),    # with walls
+    (4100, 0.3, 0.0, 256),    # 19 to 51, to 1000: two pages of a plain list
+    (4100, 0.3, 0.4, 256),    # two pages with walls
+    (4100, 0.3, 0.2, 37),     # cut within a page
+    (4100, 0.3, 0.0, 150),    # cut in the second page
+    (600, 0.12, 0.0, 352),    # 68 to 84, 600: one page, windows of a plain list
+    (600, 0.12, 0.3, 352),    # windows with walls
+    (600, 0.12, 0.0, 133),    # cut within the second window
+    (1500, 0.12, 0.3, 900),   # 165 to 202, 1500: three pages, seven windows
+]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _rows(entries, n, M):
+    """The brick-local lists, one row per particle."""
+    e = entries.view(torch.int16).reshape(-1, -(-M // 8), 64, 8)
+    return e.permute(0, 2, 1, 3).reshape(-1, 8 * -(-M // 8))[:n].cpu().numpy()
+
+
+@pytest.mark.parametrize("brick", [(3, 4, 3), (3, 2, 3)], ids=["3x4x3", "3x2x3"])
+@pytest.mark.parametrize("n,side,walls,M", SCENES)
+def test_lists(n, side, walls, M, brick):
+    sc = S.random_cloud(n=n, box=(side, side, side), dp=0.02, seed=500 + n, boundary_frac=walls, u_sigma=0.1)
+    counts = np.bincount(sc.cell, minlength=int(np.prod(sc.grid.ncell)))
+    log("case lists n=%d M=%d walls=%g cells of %d to %d" % (n, M, walls, counts.min(), counts.max()))
+    sim = make_sim(sc, max_neibs=M, brick=brick, capacity=n + 5)
+    sim.neibs_brick.view(torch.uint8).fill_(0xA5)
+    sim.build()
+    ob = compare_build(sc, sim, max_neibs=M)
+    entries = -(-sim.capacity // 64) * 64 * 8 * -(-M // 8)
+    first = sim.neibs_brick[:entries].clone()
+    if sim.status_host()["overflow"] == 0 and M <= 416:
+        f = sim.forces(bricks=True).clone()
+        torch_sync()
+        _, (acc, drho, sa, sd, _ni) = oracle_forces_of(sc, ob)
+        check_forces(f[: sc.n].cpu().numpy(), acc, drho, sa, sd, label="lists")
+    # the entries and the rest of their last group are the same bytes whatever
+    # the array held
+    other = make_sim(sc, max_neibs=M, brick=brick, capacity=n + 5)
+    other.neibs_brick.view(torch.uint8).fill_(0x5A)
+    other.build()
+    torch_sync()
+    a, b = _rows(first, n, M), _rows(other.neibs_brick[:entries], n, M)
+    cnt = sim.neib_count[:n].cpu().numpy().view(np.uint32).astype(np.int64)
+    kept = ((cnt & 0xFFFF) + (cnt >> 16))[:, None]
+    at = np.arange(a.shape[1])[None, :]
+    written = at < -(-kept // 8) * 8
+    assert (a == b)[written].all()
+    assert (a[written & (at >= kept)] == 0).all()
