@@ -23,7 +23,7 @@
 // one contiguous range of staging slots, and the brick-local lists index into
 // it unchanged.  Whole bricks stage the fewest particles per central one;
 // they are cut into parts where the grid's bricks would leave CUs idle
-// (brick_parts), and where a brick holds somewhat more particles than LDS or
+// (brick_split), and where a brick holds somewhat more particles than LDS or
 // more centrals than lanes.
 #pragma once
 
@@ -31,34 +31,56 @@
 
 namespace sph {
 
-// Into how many runs of rows to cut each of n bricks for wgs workgroups: the
-// smallest of ceil(n parts / wgs) rounds times the cost of an item, about 5 us
-// of staging and latency for a whole brick, 4 for a half, 3.5 for a row, and
-// 16 us of pairs for a whole brick (in halves below).  The still-water tank of
-// 15.5k particles (27 bricks with a pair) takes 18.0 us in rows against 30.0
-// with whole bricks, the 169k-particle dam break (120) 35.8 us in halves
-// against 51.4 (cubic spline, Landrini-Morris, Morris viscosity, diffusion).
-// PAIRS: the time of a whole brick's pairs, LEAST: the parts below which no
-// item would fit in LDS, limit: the most items (there are slots for).
-template <int BY, int PAIRS, int LEAST>
-__device__ __forceinline__ int brick_parts(int n, int wgs, int limit)
+// How the n bricks of the table are cut into items, by their place in it: the
+// first `whole` (the larger ones) into `first` parts each, the others into `rest`.
+struct BrickSplit {
+    int whole, first, rest, items;
+};
+
+// The split for wgs workgroups: rounds of whole bricks, and the bricks left
+// over cut so that their rounds, times the cost of an item, cost least: about
+// 5 us of staging and latency for a whole brick, 4 for a half, 3.5 for a row,
+// and PAIRS halves of a microsecond for the pairs of a 3 x 4 x 3 brick.  From
+// four rounds on the bricks stay whole: what is left over is small.  Tank of
+// 15.5k particles (27 bricks with a pair): 17.1 us in rows against 30.0 with
+// whole bricks; 169k dam break (120, cubic spline, Landrini-Morris, Morris
+// viscosity, diffusion): 34.8 us in halves against 51.4; 300k channel of 3 x 3 x 3 bricks:
+// 58.5 us with the last round in rows against 66.6 with all whole.
+// FIRST: the parts below which no item would fit in LDS, limit: the most items
+// (there are slots for).
+template <int BX, int BY, int BZ, int PAIRS, int FIRST>
+__device__ __forceinline__ BrickSplit brick_split(int n, int wgs, int limit)
 {
-    int best = 1, cost = ((n + wgs - 1) / wgs) * (10 + PAIRS);
-    if constexpr (BY % 2 == 0 && BY > 2) {
-        const int c2 = ((2 * n + wgs - 1) / wgs) * (8 + PAIRS / 2);
-        if (LEAST == 2 || c2 < cost) {
-            best = 2;
-            cost = c2;
+    constexpr int P = PAIRS * BX * BY * BZ / 36;
+    constexpr auto cost = [](int parts) { return (parts == 1 ? 10 : parts == BY ? 7 : 8) + P / parts; };
+    constexpr int HALF = BY % 2 == 0 && BY > 2 ? 2 : FIRST;
+    if (n * FIRST > limit) return {n, 1, 1, n};
+    BrickSplit best = {n, FIRST, FIRST, n * FIRST};
+    if (n * FIRST >= 4 * wgs) return best;
+    int rounds = 0, least = INT32_MAX;
+    while ((rounds + 1) * wgs <= n * FIRST) ++rounds;  // at most 3
+#pragma unroll
+    for (int back = 0; back < 2; ++back) {
+        const int done = max(rounds - back, 0), whole = done * wgs / FIRST, left = n - whole;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int parts = k == 0 ? FIRST : k == 1 ? HALF : BY, items = whole * FIRST + left * parts;
+            if (k == 1 && HALF == FIRST) continue;
+            int c = done * cost(FIRST);
+            for (int i = left * parts; i > 0; i -= wgs) c += cost(parts);  // (2 BY rounds at most)
+            if (c < least && items <= limit) {
+                best = {whole, FIRST, parts, items};
+                least = c;
+            }
         }
     }
-    if (((BY * n + wgs - 1) / wgs) * (7 + PAIRS / BY) < cost) best = BY;
-    return best * n <= limit ? best : 1;
+    return best;
 }
 
-template <int BY, int PAIRS, int LEAST>
-__device__ __forceinline__ int item_parts(int n_listed, const BrickGrid &G)
+template <int BX, int BY, int BZ, int PAIRS, int FIRST>
+__device__ __forceinline__ BrickSplit item_split(int n_listed, const BrickGrid &G)
 {
-    return brick_parts<BY, PAIRS, LEAST>(n_listed, gridDim.x, G.nx * G.ny * G.nz);
+    return brick_split<BX, BY, BZ, PAIRS, FIRST>(n_listed, gridDim.x, G.nx * G.ny * G.nz);
 }
 
 // Descriptor of an item.
@@ -127,15 +149,23 @@ __device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const Br
         ya = pb;
         yend = pe;
     } else {
-        // the first item of a workgroup is its index, the others come from the
-        // counter (zeroed before the launch)
+        // the first item of a workgroup is its index; the others come from the
+        // counter (zeroed before the launch), or, without one, rounds of
+        // workgroups take the items, which are ordered by size, forwards and
+        // backwards in turn
         const int heavy = table[0], n_listed = heavy + table[cap_ids + 1];
         const int guess = first ? table[1 + min((int)blockIdx.x, cap_ids - 1)] : 0;  // (sent for with the counts)
-        const int parts = item_parts<BY, PAIRS, LEAST>(n_listed, G), items = n_listed * parts;
+        const BrickSplit B = item_split<BX, BY, BZ, PAIRS, LEAST>(n_listed, G);
+        const int items = B.items, last = __builtin_amdgcn_readfirstlane(prev.item);
         item = items;
         if (first) {
             item = blockIdx.x;
-        } else if (__builtin_amdgcn_readfirstlane(prev.item) >= 0 && items > (int)gridDim.x) {
+        } else if (!next) {
+            if (last >= 0) {
+                const int g = gridDim.x, round = last / g + 1;
+                item = round * g + (round & 1 ? g - 1 - (int)blockIdx.x : (int)blockIdx.x);
+            }
+        } else if (last >= 0 && items > (int)gridDim.x) {
             int k = 0;
             if (lane == 0) k = atomicAdd(next, 1);
             item = __builtin_amdgcn_readfirstlane(k) + gridDim.x;
@@ -147,9 +177,14 @@ __device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const Br
             }
             return;
         }
-        b = first && parts == 1 && item < heavy ? guess : brick_at(table, cap_ids, item / parts);
-        const int rows = BY / parts;
-        ya = item % parts * rows;
+        const bool cut = item >= B.whole * B.first;
+        const int parts = cut ? B.rest : B.first, of = cut ? item - B.whole * B.first : item;
+        const int quot = parts == 1 ? of : parts == 2 ? of / 2 : parts == 3 ? of / 3 : of / 4;
+        static_assert(BY <= 4, "parts of a brick");
+        const int place = (cut ? B.whole : 0) + quot;
+        b = first && place == (int)blockIdx.x && place < heavy ? guess : brick_at(table, cap_ids, place);
+        const int rows = parts == 1 ? BY : parts == BY ? 1 : BY / 2;
+        ya = (of - quot * parts) * rows;
         yend = ya + rows;
     }
     const int cx0 = (b % G.nbx) * BX, cy0 = ((b / G.nbx) % G.nby) * BY, cz0 = (b / (G.nbx * G.nby)) * BZ;

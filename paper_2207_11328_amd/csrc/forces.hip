@@ -199,9 +199,16 @@ sph_status forces_impl(const sph_grid *grid, const sph_params *params, const sph
     if (bricks && !parts->cell) return SPH_ERR_ARG;
     if (bricks && ((uintptr_t)neibs_brick & 15u)) return SPH_ERR_ARG;  // read in 16-byte groups
     if ((params->delta != 0.0f) && !parts->info) return SPH_ERR_ARG;
-    if (bricks)
+    // Items from a counter even out what the workgroups take longer for; its
+    // launch costs 1.3 to 5 us.  Up to 2560 particles per CU (a few items per
+    // workgroup) the items are dealt out instead.  With a counter and dealt
+    // out: tank of 15.5k particles 18.0 and 17.0 us, 300k channel 58.5 and 52.7, 433k
+    // tank 85.6 and 75.0, 626k tank 93.3 and 91.3; 956k batch 92.8 and 95.0,
+    // 1.62M dam break 141.6 and 145.4, 16.6M channel 1960 and 2030.
+    const bool dealt = n <= 2560 * sph_device_cus();
+    if (bricks && !dealt)
         k_zero_one<int32_t><<<1, 1, 0, s>>>(next);
-    else
+    if (!bricks)
         k_eos<<<sph_blocks(n, kThreads), kThreads, 0, s>>>(n, (const float4 *)parts->vel, aux, parts->cell, C);
     ForceArgs a;
     a.grid = grid;
@@ -220,7 +227,7 @@ sph_status forces_impl(const sph_grid *grid, const sph_params *params, const sph
     a.cap_ids = brick_table_cap(parts->capacity);
     a.table = bricks ? brick_table(reinterpret_cast<const int32_t *>(neibs_brick), parts->capacity, max_neibs)
                      : nullptr;
-    a.next = next;
+    a.next = dealt ? nullptr : next;
     a.out = (float4 *)forces;
     a.bricks = bricks;
     a.K = K;

@@ -348,7 +348,7 @@ __global__ __launch_bounds__(kThreads) void k_forces_backward(
 #endif
 constexpr int kBackThreads = 1024;
 constexpr int kBackCap = 2624;
-constexpr int kBackPairTime = 86;  // of a whole brick, in half microseconds (brick_parts)
+constexpr int kBackPairTime = 86;  // of a whole brick, in half microseconds (brick_split)
 
 // The staged arrays of a run.
 template <int CAP>
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
     if (sLast) {  // uniform
         __threadfence();
         const int n_listed = table[0] + table[cap_ids + 1];
-        sum_partials<NT>(tid, n_listed * item_parts<BY, kBackPairTime, LEAST>(n_listed, G), partial, grad_params,
+        sum_partials<NT>(tid, item_split<BX, BY, BZ, kBackPairTime, LEAST>(n_listed, G).items, partial, grad_params,
                          accumulate, red);
     }
 }

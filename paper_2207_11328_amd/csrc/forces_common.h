@@ -122,7 +122,7 @@ struct ForceArgs {
     const int32_t *cell_start, *cell_end;
     const int32_t *table;  // bricks with a pair (brick_table layout), from the build
     int cap_ids;           // ids of the table
-    int32_t *next;         // brick counter of the persistent workgroups (zeroed before the launch)
+    int32_t *next;         // item counter of the persistent workgroups (zeroed before the launch), null: items dealt out
     float4 *out;  // may be null when K.d_dt is set
     bool bricks;
     Corrector K;

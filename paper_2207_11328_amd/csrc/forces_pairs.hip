@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kThreads) void k_forces(int n, const float4 *__rest
 #define SPH_BRICK_RING 2
 #endif
 constexpr int kRing = SPH_BRICK_RING;
-constexpr int kPairTime = 32;  // of a whole brick, in half microseconds (brick_parts)
+constexpr int kPairTime = 32;  // of a whole brick, in half microseconds (brick_split)
 static_assert(kBrickGroup % kRing == 0, "ring must divide the group");
 
 // The staged arrays of a brick.  P and V are read with one address register
