@@ -71,27 +71,26 @@ def test_few_bricks(n, brick):
     check_forces(f[:n].cpu().numpy(), acc, drho, sa, sd, label="few bricks %d" % n, allowance=edge_allowance(sc, ob))
 
 
-@pytest.mark.parametrize("brick", SHAPES, ids=["x".join(map(str, b)) for b in SHAPES])
-@pytest.mark.parametrize("side", [1.1, 1.3])
+@pytest.mark.parametrize("side,brick", [(1.1, (3, 2, 3)), (1.3, (3, 4, 3))], ids=["3x2x3", "3x4x3"])
 def test_rounds_of_bricks(side, brick):
-    """From somewhat more than one to four rounds of workgroups, so that the
-    bricks left over by the last whole round are cut in each way, dealt out:
-    every particle's derivatives, and the adjoint's parameter sums."""
+    """Somewhat more bricks than workgroups, so that those left over by the
+    whole round are cut, and dealt out: every particle's derivatives, and the
+    adjoint's parameter sums."""
     from test_gpu_adjoint import _backward_parity
     box = (side, side, 0.8 * side)
-    n = int(7000 * side ** 3)  # about two a cell
+    n = int(9000 * side ** 3 * 4)
     sc = S.random_cloud(n=n, box=box, dp=0.02, seed=int(100 * side), boundary_frac=0.1, u_sigma=0.2, alpha=0.2)
     nb = int(np.prod([-(-int(c) // b) for c, b in zip(sc.grid.ncell, brick)]))
     log("case rounds: n=%d, %d bricks of %s" % (n, nb, brick))
-    sim = make_sim(sc, max_neibs=48, brick=brick)
+    sim = make_sim(sc, max_neibs=96, brick=brick)
     sim.build()
     sim.forces_n.fill_(float("nan"))
     f = sim.forces(bricks=True).clone()
     torch_sync()
-    ob = compare_build(sc, sim, max_neibs=48)
+    ob = compare_build(sc, sim, max_neibs=96)
     _, (acc, drho, sa, sd, _ni) = oracle_forces_of(sc, ob)
     check_forces(f[:n].cpu().numpy(), acc, drho, sa, sd, label="rounds", allowance=edge_allowance(sc, ob))
-    _backward_parity(sc, 48, True, brick, "rounds")
+    _backward_parity(sc, 96, True, brick, "rounds")
 
 
 @pytest.mark.parametrize("brick", SHAPES, ids=["x".join(map(str, b)) for b in SHAPES])
