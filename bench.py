@@ -40,7 +40,8 @@ FP32_PEAK_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
 FLOP_PER_INTERACTION = {0: 43, 1: 52}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "forces_traffic_dam_break_1m.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2207_11328_amd", "csrc", f)
-                  for f in ("forces.hip", "forces_pairs.hip", "forces_common.h", "sph_model.h", "sph_device.h")]
+                  for f in ("forces.hip", "forces_pairs.hip", "forces_common.h", "brick_items.h", "sph_model.h",
+                            "sph_device.h")]
 
 
 def sources_sha256():

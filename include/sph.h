@@ -300,7 +300,7 @@ sph_status sph_build_neighbors(const sph_grid *grid, const sph_params *params,
  * precedes the brick kernel.
  * workspace: device buffer of sph_forces_workspace_bytes(capacity, n_cells)
  * bytes (the per-particle equation-of-state terms of the gather form and
- * the brick counter of the persistent brick kernel, set within every call;
+ * the item counter of the persistent brick kernel, set within every call that uses it;
  * its contents on entry do not change any result).  Calls that share a workspace must not overlap.
  * Errors: SPH_ERR_ARG (also for an unknown kernel, formulation or
  * visc_model, a negative or non-finite delta, or delta > 0 without

@@ -95,9 +95,9 @@ struct BrickItem {
     int lds;     // the run fits in LDS
 };
 
-// Bricks with more staged particles than this (the list build's LDS capacity:
-// 1.4 times the lattice density in a 3 x 4 x 3 brick) are not cut into runs
-// but read the global lists, with the bits of the gather form.
+// Bricks with more staged particles than this (1.4 times the lattice density
+// in a 3 x 4 x 3 brick) are not cut into runs but read the global lists, with
+// the bits of the gather form.
 constexpr int kRunTotal = 4800;
 
 // Entry of the table: staged slot (from s_lo) | inner row << 12 | list length << 16.

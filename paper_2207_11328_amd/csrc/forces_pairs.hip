@@ -647,7 +647,7 @@ void launch_brick(const ForceArgs &a, const ForceConst &C, hipStream_t s)
     with_shape(a.shape, [&]<int BX, int BY, int BZ>() {
         const BrickGrid G = brick_grid<BX, BY, BZ>(a.grid->ncell, a.grid->periodic);
         const unsigned blocks = (unsigned)G.nbx * G.nby * G.nbz;
-        // (the brick counter was zeroed before the launch; the table of
+        // (the item counter, if used, was zeroed before the launch; the table of
         // bricks with a pair is the build's; at most one item per row of a brick)
         const unsigned wgs = brick_workgroups(blocks, BY);
         k_forces_brick<MODEL, BX, BY, BZ, kBrickThreads, kBrickCap><<<wgs, kBrickThreads, 0, s>>>(
