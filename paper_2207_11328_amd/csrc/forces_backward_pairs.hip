@@ -63,7 +63,7 @@ struct BackAcc {
 // masked form except with density diffusion, whose longer pair body spills
 // when it runs for every slot.  For the Wendland kernel the mask is the clamp
 // to [0, 1] of t = in - r/(2h), which is 1 - q/2 inside the list: F = -8 c t^3
-// and F'/r = 12 c t^2/(h r) vanish with it.
+// and F'/r = (12 c t^2/h)/r vanish with it.
 template <int MODEL, bool MASKED>
 __device__ __forceinline__ void pair_adjoint_core(BackAcc &G, float xx, float xy, float xz, float mi,
                                                   const float4 &vi, const float4 &xi, const float4 &gi, float mj,
@@ -91,7 +91,7 @@ __device__ __forceinline__ void pair_adjoint_core(BackAcc &G, float xx, float xy
     if constexpr (CLAMPED) {
         const float t = __builtin_amdgcn_fmed3f(fmaf(r, C.neg_inv_2h, in), 0.0f, 1.0f), t2 = t * t;
         F = t2 * (t * C.minus_8c);
-        Fp_r = t2 * (C.c12_h * inv_r);
+        Fp_r = (t2 * C.c12_h) * inv_r;  // (12 c/h times 1e15 may exceed float32: the mask comes first)
     } else {
         kernel_F_dF<KER>(C.fcoeff, r, r2, inv_r, C.inv_h, C.inv_h2, F, Fp_r);
         if (MASKED) {

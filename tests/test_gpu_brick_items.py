@@ -132,3 +132,20 @@ def test_adjoint_same_after_every_build():
             got.append((gp, gv, par))
     for g in got[1:]:
         assert all(torch.equal(a, b) for a, b in zip(got[0], g))
+
+
+@pytest.mark.parametrize("visc", [0, 1], ids=["av", "morris"])
+def test_small_scale_adjoint(visc):
+    """Spacing 0.1 mm, no walls.  The first staged particle of the corner brick
+    is one of its centrals, and the slots past the end of its list point to
+    itself (r = 0), where the kernel's second factor, F'/r, is beyond float32
+    before its mask: such a slot has to add nothing."""
+    import dataclasses
+    from oracle import oracle as O
+    from test_gpu_adjoint import _backward_parity
+    sc = S.random_cloud(n=1100, box=(0.0013, 0.001, 0.001), dp=1e-4, seed=51, boundary_frac=0.0, u_sigma=0.3,
+                        rho_sigma=0.01, alpha=0.3)
+    sc = dataclasses.replace(sc, params=dataclasses.replace(sc.params, visc_model=visc, nu=1e-6 if visc else 0.0))
+    L = O.build_f32(sc.grid, sc.params, sc.cell, sc.pos, sc.vel, sc.info)["lists"]
+    assert (L.nf[0] + L.nb[0]) % 8, "no slot past the list"
+    _backward_parity(sc, 192, True, None, "small scale")
