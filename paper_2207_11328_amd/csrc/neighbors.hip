@@ -477,7 +477,6 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, const uin
 constexpr int kList = 640, kWords = kList / 4 / 32, kTilesPage = 16, kRow = 4 * kTilesPage + 4;
 constexpr int kWindow = 128, kOut = kWindow + 8;
 constexpr float kSlack = 0x1p-17f;
-constexpr uint32_t kNoCandidate = ~0u;  // (no image code has all bits set in a field)
 typedef float vf4 __attribute__((ext_vector_type(4)));
 
 template <int BX, int BY, int BZ, int NW>
@@ -628,12 +627,14 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
                     const int f0 = 32 * k + lane;
                     float4 p[4];
                     uint32_t code[4];
+                    bool there[4];  // (no code is free to say so: all 32 bits of an entry are in use)
                     wave_fence();
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
                         const int f = g * Q + f0;
-                        code[g] = f0 < Q && f < np ? W.code[f] : kNoCandidate;
-                        p[g] = code[g] != kNoCandidate ? A.pos[code[g] & kIndexMask] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                        there[g] = f0 < Q && f < np;
+                        code[g] = there[g] ? W.code[f] : 0u;
+                        p[g] = there[g] ? A.pos[code[g] & kIndexMask] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                     }
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
@@ -643,7 +644,7 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
                         W.page[0][g * kRow + lane] = x;
                         W.page[1][g * kRow + lane] = y;
                         W.page[2][g * kRow + lane] = z;
-                        W.page[3][g * kRow + lane] = code[g] != kNoCandidate ? fmaf(x, x, fmaf(y, y, z * z)) : 1e30f;
+                        W.page[3][g * kRow + lane] = there[g] ? fmaf(x, x, fmaf(y, y, z * z)) : 1e30f;
                     }
                     odd = __builtin_amdgcn_ballot_w64(odd) != 0;
                     wave_fence();

@@ -71,3 +71,49 @@ def test_lists(n, side, walls, M, brick):
     written = at < -(-kept // 8) * 8
     assert (a == b)[written].all()
     assert (a[written & (at >= kept)] == 0).all()
+
+
+def test_last_particle_of_the_largest_capacity():
+    """The particle of index 2^26 - 1, seen from the cell below it along every
+    axis: index and image fields of the entry have all bits set."""
+    from paper_2207_11328_amd import abi
+    dev = torch.device("cuda")
+    n, M, per_cell = abi.MAX_CAPACITY, 8, 4
+    ncell = (256, 512, 128)
+    grid = S.Grid(origin=np.zeros(3), cell_size=np.ones(3, np.float32), ncell=np.array(ncell, np.int32))
+    assert grid.n_cells * per_cell == n
+    params = S.Params(dp=0.05, h=0.09, r_search=0.2)
+    log("case last particle: n=%d, %d cells" % (n, grid.n_cells))
+    ids = torch.arange(n, dtype=torch.int32, device=dev)
+    cell = ids // per_cell
+    pos = torch.zeros((n, 4), device=dev)
+    pos[:, 3] = 1.0
+    vel = torch.zeros((n, 4), device=dev)
+    vel[:, 3] = 1000.0
+    # four coincident particles a cell, but one of the last cell at its lower
+    # corner and one of the cell diagonally below at its upper corner
+    below = (ncell[0] - 2) + ncell[0] * ((ncell[1] - 2) + ncell[1] * (ncell[2] - 2))
+    i = below * per_cell
+    pos[n - 1, :3] = -0.45
+    pos[i, :3] = 0.45
+    neibs = torch.zeros(abi.sph_neib_list_entries(n, M), dtype=torch.int32, device=dev)
+    brick = torch.zeros(abi.sph_neib_brick_entries(n, M), dtype=torch.int16, device=dev)
+    count = torch.zeros(n, dtype=torch.int32, device=dev)
+    ranges = torch.zeros((2, grid.n_cells), dtype=torch.int32, device=dev)
+    status = torch.zeros(abi.STATUS_WORDS, dtype=torch.int32, device=dev)
+    ws = torch.zeros(abi.sph_build_workspace_bytes(n, grid.n_cells), dtype=torch.uint8, device=dev)
+    abi.sph_build_neighbors(abi.grid_struct(grid), abi.params_struct(params),
+                            abi.particles_struct(n, cell, pos, vel, ids), neibs, count, M, ranges[0], ranges[1],
+                            status, ws, None, None, brick)
+    torch_sync()
+    assert status[:4].tolist() == [n, per_cell - 1, 0, 0]
+
+    def listed(k):
+        c = int(count[k])
+        assert c >> 16 == 0
+        return [int(neibs[(k // 64) * 64 * M + 64 * e + k % 64]) & 0xFFFFFFFF for e in range(c)]
+
+    assert listed(i) == [0xFFFFFFFF]
+    assert listed(n - 1) == [i | 0b010101 << 26]
+    assert int((count == per_cell - 1).sum()) == n - 2 * per_cell
+    assert int((count == per_cell - 2).sum()) == 2 * (per_cell - 1)
