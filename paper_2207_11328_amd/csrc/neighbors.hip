@@ -456,8 +456,8 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, const uin
 // The brick-local form of the same lists is for the derivative kernels: entry k
 // is the neighbour's slot in the staging order of the central particle's brick
 // (cells of the brick and its halo in the Staging order, particles of a cell in
-// sorted order), uint16, in scan order with fluid and boundary neighbours
-// interleaved as found (entries 0 .. nf+nb-1), stored in groups of 8 per
+// sorted order), uint16 (slots beyond 65535 as 65535), in scan order with fluid and
+// boundary neighbours interleaved as found (entries 0 .. nf+nb-1), stored in groups of 8 per
 // particle (brick_entry).
 //
 // Bound by VALU issue and the latencies between the steps: of the 545 us that
@@ -609,7 +609,7 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
                     const uint64_t b = __builtin_amdgcn_ballot_w64(f < np && sl >= c.y);
                     mixed |= b != 0;
                     W.code[f] = (uint32_t)(sl + c.z);
-                    W.slot[f] = (uint16_t)sl;
+                    W.slot[f] = (uint16_t)min(sl, 0xFFFF);
                     if (lane == 0) *(uint64_t *)&W.marks[2 * ch] = b;
                 }
                 wave_fence();

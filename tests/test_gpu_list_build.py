@@ -117,3 +117,29 @@ def test_last_particle_of_the_largest_capacity():
     assert listed(n - 1) == [i | 0b010101 << 26]
     assert int((count == per_cell - 1).sum()) == n - 2 * per_cell
     assert int((count == per_cell - 2).sum()) == 2 * (per_cell - 1)
+
+
+def test_slots_beyond_16_bits():
+    """A brick whose halo holds more than 65535 particles: the brick-local
+    entries saturate, as the layout says."""
+    rng = np.random.default_rng(8)
+    sc = S.random_cloud(n=66600, box=(0.29, 0.29, 0.29), dp=0.02, seed=8, boundary_frac=0.0, u_sigma=0.1)
+    nx, ny, nz = (int(v) for v in sc.grid.ncell)
+    assert (nx, ny, nz) == (5, 5, 5)
+    # all but 600 into the cells y = 0, x and z up to 3 (staged by brick 0); the others
+    # into the cells y = 2, x and z up to 2, of the same brick
+    crowd = 66000
+    x, z = rng.integers(0, 4, crowd), rng.integers(0, 4, crowd)
+    sc.cell[:crowd] = x + nx * (ny * z)
+    x, z = rng.integers(0, 3, sc.n - crowd), rng.integers(0, 3, sc.n - crowd)
+    sc.cell[crowd:] = x + nx * (2 + ny * z)
+    log("case 16-bit slots: n=%d" % sc.n)
+    sim = make_sim(sc, max_neibs=96, brick=(3, 3, 3))
+    sim.build()
+    torch_sync()
+    cell = sim.cell[: sc.n].cpu().numpy()
+    mine = (cell // nx) % ny == 2
+    cnt = sim.neib_count[: sc.n].cpu().numpy().view(np.uint32)[mine]
+    assert mine.sum() == 600 and (cnt > 0).all()
+    e = _rows(sim.neibs_brick[: -(-sim.capacity // 64) * 64 * 96], sc.n, 96)[mine].view(np.uint16)
+    assert (e[np.arange(96)[None, :] < cnt[:, None]] == 65535).all()
