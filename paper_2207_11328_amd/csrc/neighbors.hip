@@ -439,8 +439,9 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, const uin
 //   |p|^2, |o|^2 - r_s^2 (3 roundings each)              9 u S
 //   four products and sums of at most 4 S                32 u S
 //   the predicate: x to 2.5 u |cs|, its square and sum   8 u S
-// less than 64 u S together; kSlack = 128 u S.  Where an offset leaves its
-// cell, or is not finite, the predicate decides every pair of the item.
+// less than 64 u S together; kSlack = 128 u S.  (Every particle in a cell has
+// its offset in that cell, or re-binning has dropped it.)  Places without a
+// candidate lie farther away than any r_s whose square is a float.
 //
 // Lanes 16 g .. 16 g + 15 take quarter g of the candidate list, each lane for
 // one central: row 4 g + r of the candidate operand is candidate g Q + 4 t + r
@@ -476,7 +477,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, const uin
 // (kOut apart per central) in the memory of the positions.
 constexpr int kList = 640, kWords = kList / 4 / 32, kTilesPage = 16, kRow = 4 * kTilesPage + 4;
 constexpr int kWindow = 128, kOut = kWindow + 8;
-constexpr float kSlack = 0x1p-17f;
+constexpr float kSlack = 0x1p-17f, kFarAway = 3e38f;  // (times |cs|^2; |p|^2)
 typedef float vf4 __attribute__((ext_vector_type(4)));
 
 template <int BX, int BY, int BZ, int NW>
@@ -534,7 +535,6 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
     const int quarter = lane / 16, m = lane % 16, M = A.M, G = brick_groups(M);
     auto &W = T.wave[wave];
     const float slack = kSlack * (A.csx * A.csx + A.csy * A.csy + A.csz * A.csz);
-    const float farthest = slack * (0.2505f / kSlack);  // the |o|^2 up to which the slack holds
     const int to_index = __builtin_amdgcn_readfirstlane(-T.delta[tc]);
 
     auto of_quarter = [&](int v, int q) { return __builtin_amdgcn_ds_bpermute(4 * (16 * q + m), v); };
@@ -572,7 +572,7 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
         // neighbours found and of fluid ones kept
         int index[2], found[2] = {0, 0}, fluid[2] = {0, 0};
         float bop[2], c_init[2];
-        bool has[2], odd = false;
+        bool has[2];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const int q = q0 + 16 * c + m;
@@ -580,7 +580,6 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
             index[c] = q_begin + min(q, nq - 1) + to_index;
             const float4 o = A.pos[index[c]];
             bop[c] = quarter == 0 ? -2.0f * o.x : quarter == 1 ? -2.0f * o.y : quarter == 2 ? -2.0f * o.z : 1.0f;
-            odd |= !(fmaf(o.x, o.x, fmaf(o.y, o.y, o.z * o.z)) <= farthest);
             c_init[c] = fmaf(o.x, o.x, fmaf(o.y, o.y, fmaf(o.z, o.z, -A.rs2)));
         }
         for (int pg = 0; pg < n_cand; pg += kList) {  // uniform
@@ -638,20 +637,18 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
                     }
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
-                        odd |= !(fmaf(p[g].x, p[g].x, fmaf(p[g].y, p[g].y, p[g].z * p[g].z)) <= farthest);
                         const float4 d = T.shift[code[g] >> 26];
                         const float x = p[g].x + d.x, y = p[g].y + d.y, z = p[g].z + d.z;
                         W.page[0][g * kRow + lane] = x;
                         W.page[1][g * kRow + lane] = y;
                         W.page[2][g * kRow + lane] = z;
-                        W.page[3][g * kRow + lane] = there[g] ? fmaf(x, x, fmaf(y, y, z * z)) : 1e30f;
+                        W.page[3][g * kRow + lane] = there[g] ? fmaf(x, x, fmaf(y, y, z * z)) : kFarAway;
                     }
-                    odd = __builtin_amdgcn_ballot_w64(odd) != 0;
                     wave_fence();
                 }
                 constexpr int kHalf = 4 * kTilesPage / 2;  // candidates of a quarter in a word
                 const float *word = mine + (k % 2) * kHalf;
-                float least[2] = {1e30f, 1e30f};
+                float least[2] = {kFarAway, kFarAway};
                 const int part = min(tiles - 8 * k, 8);  // 4 or 8
 #pragma unroll 1
                 for (int b = 0; b < part; b += 4) {      // uniform
@@ -680,7 +677,7 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     if (c == 1 && !two) continue;  // uniform
-                    if (__builtin_amdgcn_ballot_w64(odd || (has[c] && least[c] < slack))) {  // uniform, rare
+                    if (__builtin_amdgcn_ballot_w64(has[c] && least[c] < slack)) {  // uniform, rare
                         // the candidates of the word that are that near
                         const vf4 c4 = {c_init[c], c_init[c], c_init[c], c_init[c]};
                         uint32_t near = 0u;
@@ -690,10 +687,6 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
                                 near = __builtin_amdgcn_alignbit(near, __float_as_uint(fabsf(r[e]) - slack), 31);
-                        }
-                        if (odd) {  // uniform: all there are
-                            const int there = min(max(np - (quarter * Q + 32 * k), 0), 4 * part);
-                            near = (uint32_t)(((1ull << there) - 1ull) << (4 * part - there));
                         }
                         if (!has[c]) near = 0u;
                         const float4 o = A.pos[index[c]];

@@ -143,3 +143,24 @@ def test_slots_beyond_16_bits():
     assert mine.sum() == 600 and (cnt > 0).all()
     e = _rows(sim.neibs_brick[: -(-sim.capacity // 64) * 64 * 96], sc.n, 96)[mine].view(np.uint16)
     assert (e[np.arange(96)[None, :] < cnt[:, None]] == 65535).all()
+
+
+@pytest.mark.parametrize("scale", [2.0 ** 56, 2.0 ** -30])
+def test_lists_at_any_scale(scale):
+    """Lengths times a power of two: the same lists, bit for bit."""
+    sc = S.random_cloud(n=2000, box=(0.3, 0.3, 0.3), dp=0.02, seed=5, boundary_frac=0.3, u_sigma=0.1)
+    import dataclasses
+    log("case scale %g" % scale)
+    got = []
+    for f in (1.0, scale):
+        g, p = sc.grid, sc.params
+        s = sc.copy()
+        s.grid = dataclasses.replace(g, origin=g.origin * f, cell_size=(g.cell_size * np.float32(f)).astype(np.float32))
+        s.params = dataclasses.replace(p, dp=p.dp * f, h=p.h * f, r_search=p.r_search * f)
+        s.pos[:, :3] *= np.float32(f)
+        sim = make_sim(s, max_neibs=160)
+        sim.build()
+        torch_sync()
+        got.append((sim.neibs, sim.neib_count, sim.neibs_brick))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
