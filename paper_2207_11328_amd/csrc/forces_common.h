@@ -51,10 +51,12 @@ __device__ __forceinline__ float2 eos_terms(float rho, float alpha_h, const Forc
 }
 
 // alpha h of particle j: the coefficient of its cell when a per-cell table is
-// given, else the global one
+// given, else the global one.  A lane without a particle of its own takes
+// particle 0, which is in no cell (-1) when the build dropped all of them: the
+// table is then read at its first cell (and the value not used).
 __device__ __forceinline__ float alpha_h_of(int j, const int32_t *__restrict__ cell, const ForceConst &C)
 {
-    return C.cell_alpha ? C.cell_alpha[cell[j] - C.cell_base] * C.h : C.alpha_h;
+    return C.cell_alpha ? C.cell_alpha[max(cell[j] - C.cell_base, 0)] * C.h : C.alpha_h;
 }
 
 // The corrector stage taken inside the derivative kernel

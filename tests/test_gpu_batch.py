@@ -243,3 +243,33 @@ def test_cells_of_no_scene_are_left_alone():
     assert np.array_equal(after["pos"][sel].view(np.uint32), before["pos"][sel].view(np.uint32))
     assert np.array_equal(after["vel"][sel].view(np.uint32), before["vel"][sel].view(np.uint32))
     assert not np.array_equal(after["pos"][~sel].view(np.uint32), before["pos"][~sel].view(np.uint32))
+
+
+@pytest.mark.parametrize("bricks", [True, False], ids=["bricks", "gather"])
+def test_every_particle_dropped(bricks):
+    """A batch that blew up: every offset is not finite, so the build drops all
+    particles (cell -1).  The derivatives and the fused step, with the per-cell
+    alpha table and cells counted from a base, read no table outside its
+    cells, give zeros and leave the state as it is."""
+    from paper_2207_11328_amd.sim import Simulation
+    stacked, alpha, _, _ = S.stack_scenes(_tanks(3))
+    stacked.grid.cell_base = 5000
+    stacked.cell = stacked.cell + 5000
+    stacked.pos[:, :3] = np.nan
+    log("case all dropped: n=%d bricks=%s" % (stacked.n, bricks))
+    sim = Simulation(stacked.grid, stacked.params, stacked.cell, stacked.pos, stacked.vel, stacked.info,
+                     cell_alpha=alpha, cell_scene=S.scene_cells(stacked), use_bricks=bricks)
+    sim.build()
+    torch_sync()
+    st = sim.status_host()
+    assert st["n_active"] == 0 and st["dropped"] == stacked.n and st["nonfinite"] == stacked.n
+    assert (sim.cell[: sim.n] == -1).all()
+    vel = sim.vel.clone()
+    sim.forces_n.fill_(float("nan"))
+    sim.d_dt.fill_(1e-4)
+    sim.forces()
+    assert (sim.forces_n[: sim.n] == 0).all()
+    sim.integrate(0)
+    sim.corrector()
+    torch_sync()
+    assert torch.equal(sim.vel, vel) and torch.isnan(sim.pos[: sim.n, :3]).all()
