@@ -507,7 +507,8 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         };
         const uint32_t lo2 = (uint32_t)s_lo * 0x10001u, max2 = (uint32_t)(span - 1) * 0x10001u;
         // (without a branch, so that no loaded value is copied: past the table,
-        // or where there is none, a lane loads some particle's list)
+        // or where there is none, a lane loads some particle's list.  An empty
+        // table may hold any bits: particle and group are kept inside the lists)
         auto take = [&](int g) {
             Central c;
             const int q = g * QG + lane / kLanes;
@@ -516,7 +517,7 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
             const uint32_t i = (c.e & kCenSlotMask) + (uint32_t)B.row_shift[c.e >> kCenRowShift & 15u];
             c.i = (int)min(i, (uint32_t)(n - 1));
             c.lg = list_groups(neibs_brick, c.i, brick_groups(M));
-            const int last = max((int)(c.e >> kCenCountShift) - 1, 0) / kEntries;
+            const int last = min(max((int)(c.e >> kCenCountShift) - 1, 0) / kEntries, brick_groups(M) - 1);
             c.list = list_entries(c.lg, min(h, last));
             c.more = list_entries(c.lg, min(h + kLanes, last));
             return c;

@@ -149,3 +149,33 @@ def test_small_scale_adjoint(visc):
     L = O.build_f32(sc.grid, sc.params, sc.cell, sc.pos, sc.vel, sc.info)["lists"]
     assert (L.nf[0] + L.nb[0]) % 8, "no slot past the list"
     _backward_parity(sc, 192, True, None, "small scale")
+
+
+@pytest.mark.parametrize("brick", SHAPES, ids=["x".join(map(str, b)) for b in SHAPES])
+@pytest.mark.parametrize("M", [1, 8, 40])
+def test_short_lists(M, brick):
+    """Lists of fewer groups of eight than a central's lanes request ahead, where
+    an item has no table of centrals: rows without a list, and (the crowd in one
+    corner, beyond what is staged) rows on the gather path.  Both forms take
+    the same kept entries; particles without one get zeros."""
+    sparse = S.random_cloud(n=150, box=(0.6, 0.6, 0.6), dp=0.02, seed=33, boundary_frac=0.0, u_sigma=0.2)
+    crowd = S.random_cloud(n=6000, box=(0.6, 0.6, 0.6), dp=0.02, seed=34, boundary_frac=0.0, u_sigma=0.2)
+    crowd.cell[:] = crowd.cell % 3 + 10 * (crowd.cell // 10 % 3) + 100 * (crowd.cell // 100 % 3)
+    assert tuple(sparse.grid.ncell) == (10, 10, 10)
+    for sc in (sparse, crowd):
+        log("case short lists M=%d n=%d" % (M, sc.n))
+        sim = make_sim(sc, max_neibs=M, brick=brick, capacity=sc.n)
+        sim.build()
+        sim.forces_n.fill_(float("nan"))
+        b = sim.forces(bricks=True).clone()
+        g = sim.forces(bricks=False).clone()
+        torch_sync()
+        cnt = sim.neib_count[: sc.n].cpu().numpy()
+        assert torch.isfinite(b).all() and (b[: sc.n].cpu().numpy()[cnt == 0] == 0).all()
+        scale = g.abs().amax(dim=0)
+        if sc is crowd:
+            assert (cnt == M).all() and _brick_totals(sc, brick).max() > 4800
+            assert torch.equal(b, g)
+        else:
+            assert (cnt == 0).any() and (cnt > 0).any()
+            assert ((b - g).abs() <= 1e-5 * scale).all(), (b - g).abs().max(dim=0)
