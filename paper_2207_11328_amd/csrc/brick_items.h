@@ -218,6 +218,7 @@ __device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const Br
         total += __builtin_amdgcn_readlane(inc, kWave - 1);
     }
     if (lane == 0) Q.base[S] = total;
+    wave_fence();  // (read below by other lanes than wrote them)
     // the inner rows, one per lane (inner cells past the grid edge hold no
     // centrals: on a periodic axis the staged copy is the wrapped cell, owned
     // by another brick)

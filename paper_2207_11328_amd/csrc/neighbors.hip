@@ -504,13 +504,6 @@ struct ScanTables {
     int most, over;             // most neighbours found, centrals with more than max_neibs
 };
 
-// Orders the LDS accesses of the lanes of a wave.
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 struct ScanArgs {
     const float4 *__restrict__ pos;
     float csx, csy, csz, rs2;

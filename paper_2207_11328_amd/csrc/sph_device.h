@@ -72,6 +72,13 @@ __device__ __forceinline__ T wave_sum(T v)
     return v;
 }
 
+// Orders the LDS accesses of the lanes of a wave.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Cell difference k_d in {-1, 0, 1} of axis d, stored as a two's-complement
 // 2-bit field at bit 26 + 2d of a list entry.
 __device__ __forceinline__ float entry_k(uint32_t e, int axis)
