@@ -567,8 +567,8 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
                                               G);
             __builtin_amdgcn_s_setprio(0);
         }
-        while (g * QG < nc) {  // wave-uniform
-            if (use_lds) {
+        if (use_lds) {
+            while (g * QG < nc) {  // wave-uniform
                 const int gn = claim();
                 Central c = now;
                 now = take(gn);
@@ -600,14 +600,17 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
                     }
                 }
                 g = gn;
-            } else {
-                // more particles than LDS holds: the global lists and state with
-                // the arithmetic of k_forces, by the first lane of each central
-                // (a shallow pipeline: this path shares the register budget of
-                // the LDS path)
-                const int q = g * QG + lane / kLanes;
+            }
+        } else {
+            // more particles than LDS holds: the global lists and state with the
+            // arithmetic of k_forces, one lane per central (a shallow pipeline:
+            // this path shares the register budget of the LDS path).  0.9M
+            // particles at h = 1.5 dp: 1021 us, and 1093 with half the lanes of a
+            // wave, 1679 with a quarter
+            while (g * kWave < nc) {  // wave-uniform
+                const int q = g * kWave + lane;
                 const int i = item_central(B, min(q, nc - 1));
-                const uint32_t cw = q < nc && h == 0 ? count[i] : 0u;
+                const uint32_t cw = q < nc ? count[i] : 0u;
                 const int nf = min((int)(cw & 0xFFFFu), M), nt = min(nf + (int)(cw >> 16), M);
                 const int ntw = __builtin_amdgcn_readfirstlane(wave_max(nt));
                 if (ntw > 0) {
