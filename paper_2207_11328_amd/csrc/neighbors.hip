@@ -325,12 +325,14 @@ __global__ __launch_bounds__(kThreads) void k_sort_gather(int n, const int32_t *
 // ids: the persistent kernels that take them in that order end with the cheap
 // ones, and their work is dealt the same way after every build of the same
 // state.  A counting sort over kClasses size classes: per block of bricks a
-// histogram, then every block finds its bricks' places from all histograms.
+// histogram, then every block finds its bricks' places from all histograms.  A
+// block takes kOrderThreads bricks, or a run of as many tiles of them that
+// kOrderBlocks blocks take all: every block reads the histograms of all.
 // keys[b]: 0 for a brick without a pair, else 1 + min(particles / width, 62)
 // (brick_class); a brick is heavy from class 27 on (12 particles per cell).
 // The derivatives of the 1.62M-particle dam break are 2.5% faster in this order
 // than with the heavy and the light bricks each in an arbitrary one.
-constexpr int kClasses = 64, kHeavyClass = 27, kOrderThreads = 1024;
+constexpr int kClasses = 64, kHeavyClass = 27, kOrderThreads = 1024, kOrderBlocks = 256;
 template <int BX, int BY, int BZ>
 __device__ __forceinline__ int brick_class(int particles)
 {
@@ -340,20 +342,23 @@ __device__ __forceinline__ int brick_class(int particles)
     return 1 + min(particles / W, kClasses - 2);
 }
 
-__global__ __launch_bounds__(kOrderThreads) void k_order_count(int nb, const uint8_t *__restrict__ keys,
+__global__ __launch_bounds__(kOrderThreads) void k_order_count(int nb, int tiles, const uint8_t *__restrict__ keys,
                                                                int32_t *__restrict__ hist)
 {
     __shared__ int h[kClasses];
     if (threadIdx.x < kClasses) h[threadIdx.x] = 0;
     __syncthreads();
-    const int b = blockIdx.x * kOrderThreads + threadIdx.x;
-    const int key = b < nb ? keys[b] : 0;
-    if (key) atomicAdd(&h[key], 1);
+    const int64_t b0 = (int64_t)blockIdx.x * tiles * kOrderThreads + threadIdx.x;
+    for (int t = 0; t < tiles; ++t) {
+        const int64_t b = b0 + (int64_t)t * kOrderThreads;
+        const int key = b < nb ? keys[b] : 0;
+        if (key) atomicAdd(&h[key], 1);
+    }
     __syncthreads();
     if (threadIdx.x < kClasses) hist[blockIdx.x * kClasses + threadIdx.x] = h[threadIdx.x];
 }
 
-__global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, const uint8_t *__restrict__ keys,
+__global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, int tiles, const uint8_t *__restrict__ keys,
                                                                const int32_t *__restrict__ hist,
                                                                int32_t *__restrict__ table, int cap_ids)
 {
@@ -372,19 +377,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, const uin
     }
     all[w][lane] = a;
     before[w][lane] = f;
-    const int b = blockIdx.x * kOrderThreads + threadIdx.x;
-    const int key = b < nb ? keys[b] : 0;
-    // lanes of the wave with the same class
-    unsigned long long same = ~0ull;
-#pragma unroll
-    for (int bit = 1; bit < kClasses; bit <<= 1) {
-        const unsigned long long m = __ballot((key & bit) != 0);
-        same &= (key & bit) ? m : ~m;
-    }
-    own[w][lane] = 0;
     __syncthreads();
-    const unsigned long long below = same & ((1ull << lane) - 1ull);
-    if (key && below == 0ull) own[w][key] = (int)__popcll(same);
     if (w == 0) {
         int total = 0, first = 0;
         for (int k = 0; k < NW; ++k) {
@@ -406,12 +399,35 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, const uin
             if (lane == 1) table[cap_ids + 1] = above - h;
         }
     }
-    __syncthreads();
-    if (key) {
-        int p = at[key] + (int)__popcll(below);
-        for (int k = 0; k < w; ++k) p += own[k][key];
-        if (p < heavy) table[1 + p] = b;
-        else table[cap_ids - (p - heavy)] = b;
+    for (int t = 0; t < tiles; ++t) {  // uniform
+        const int64_t b = ((int64_t)blockIdx.x * tiles + t) * kOrderThreads + threadIdx.x;
+        const int key = b < nb ? keys[b] : 0;
+        // lanes of the wave with the same class
+        unsigned long long same = ~0ull;
+#pragma unroll
+        for (int bit = 1; bit < kClasses; bit <<= 1) {
+            const unsigned long long m = __ballot((key & bit) != 0);
+            same &= (key & bit) ? m : ~m;
+        }
+        own[w][lane] = 0;
+        __syncthreads();
+        const unsigned long long below = same & ((1ull << lane) - 1ull);
+        if (key && below == 0ull) own[w][key] = (int)__popcll(same);
+        __syncthreads();
+        if (key) {
+            int p = at[key] + (int)__popcll(below);
+            for (int k = 0; k < w; ++k) p += own[k][key];
+            if (p < heavy) table[1 + p] = (int)b;
+            else table[cap_ids - (p - heavy)] = (int)b;
+        }
+        if (t + 1 == tiles) break;  // uniform
+        __syncthreads();
+        if (w == 0) {  // the places of the next tile
+            int sum = 0;
+            for (int k = 0; k < NW; ++k) sum += own[k][lane];
+            at[lane] += sum;
+        }
+        __syncthreads();
     }
 }
 
@@ -1100,9 +1116,10 @@ extern "C" sph_status sph_build_neighbors(const sph_grid *grid, const sph_params
         with_shape(shape, [&]<int BX, int BY, int BZ>() {
             const BrickGrid G = brick_grid<BX, BY, BZ>(grid->ncell, grid->periodic);
             const int bricks = G.nbx * G.nby * G.nbz;
-            const unsigned blocks = sph_blocks(bricks, kOrderThreads);
-            k_order_count<<<blocks, kOrderThreads, 0, s>>>(bricks, classes, hist);
-            k_order_place<<<blocks, kOrderThreads, 0, s>>>(bricks, classes, hist, table, cap_ids);
+            const int tiles = ((int)sph_blocks(bricks, kOrderThreads) + kOrderBlocks - 1) / kOrderBlocks;
+            const unsigned blocks = sph_blocks(bricks, tiles * kOrderThreads);
+            k_order_count<<<blocks, kOrderThreads, 0, s>>>(bricks, tiles, classes, hist);
+            k_order_place<<<blocks, kOrderThreads, 0, s>>>(bricks, tiles, classes, hist, table, cap_ids);
         });
         SPH_CHECK_LAUNCH();
     }

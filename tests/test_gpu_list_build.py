@@ -164,3 +164,42 @@ def test_lists_at_any_scale(scale):
         got.append((sim.neibs, sim.neib_count, sim.neibs_brick))
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("brick", [(3, 4, 3), (3, 2, 3)], ids=["3x4x3", "3x2x3"])
+def test_table_of_many_bricks(brick):
+    """A long thin grid of more bricks than the ordering blocks take one tile
+    of each: the table holds the bricks with a pair by size class, large ones
+    first, and by id in a class."""
+    rng = np.random.default_rng(3)
+    nx = 3 * 300000 - 1
+    cells = rng.choice(nx, size=3000, replace=False)
+    cell = np.repeat(cells, rng.integers(1, 80, size=cells.size)).astype(np.int32)
+    n = cell.size
+    p = S.sph_params(0.02)
+    cs = np.float32(p.r_search)
+    grid = S.Grid(origin=np.zeros(3), cell_size=np.array([cs, cs, cs]), ncell=np.array([nx, 1, 1], np.int32))
+    pos = np.zeros((n, 4), np.float32)
+    pos[:, :3] = rng.uniform(-0.45, 0.45, (n, 3)) * cs
+    pos[:, 3] = 8e-3
+    vel = np.zeros((n, 4), np.float32)
+    vel[:, 3] = 1000.0
+    log("case table: n=%d, %d bricks" % (n, nx // 3 + 1))
+    sc = S.Scene("thin", grid, p, cell, pos, vel, np.arange(n, dtype=np.uint32), n, 0)
+    M = 256
+    sim = make_sim(sc, max_neibs=M, brick=brick)
+    sim.build()
+    torch_sync()
+    bid = sim.cell[:n].cpu().numpy() // 3
+    listed = np.unique(bid[sim.neib_count[:n].cpu().numpy() > 0])
+    size = np.bincount(bid, minlength=listed.max() + 1)[listed]
+    width = 12 * brick[0] * brick[1] * brick[2] // 27
+    key = np.minimum(size // width, 62)
+    order = listed[np.lexsort((listed, -key))]
+    heavy = int((key >= 27).sum())
+    t = sim.neibs_brick[-(-sim.capacity // 64) * 512 * (M // 8):].view(torch.int32).cpu().numpy()
+    cap = sim.capacity
+    nh, nl = int(t[0]), int(t[cap + 1])
+    got = np.concatenate([t[1:1 + nh], t[cap + 1 - nl:cap + 1][::-1]])
+    assert nh == heavy and nh + nl == order.size
+    assert np.array_equal(got, order)
