@@ -1097,11 +1097,11 @@ extern "C" sph_status sph_build_neighbors(const sph_grid *grid, const sph_params
         with_shape(shape, [&]<int BX, int BY, int BZ>() {
             const BrickGrid G = brick_grid<BX, BY, BZ>(grid->ncell, grid->periodic);
             const unsigned bricks = (unsigned)G.nbx * G.nby * G.nbz;
-            // a workgroup per part of a brick: which bricks have work, and so
-            // the parts, is known on the device
+            // a workgroup per part of a brick: which bricks have work (at most
+            // one per particle), and so the parts, is known on the device
             constexpr int NI = BX * BY * BZ;
-            const int resident = kBuildResident * sph_device_cus();
-            const int items = max((int)bricks * ((NI + 11) / 12), min((int)bricks * ((NI + 3) / 4), 2 * resident));
+            const int resident = kBuildResident * sph_device_cus(), most = min((int)bricks, n);
+            const int items = max(most * ((NI + 11) / 12), min(most * ((NI + 3) / 4), 2 * resident));
             k_active_bricks<BX, BY, BZ><<<sph_blocks(bricks, 256), 256, 0, s>>>(cell_start, cell_end, G, active);
             k_build_brick<BX, BY, BZ, kBuildThreads><<<items, kBuildThreads, 0, s>>>(
                 ScanArgs{pos, grid->cell_size[0], grid->cell_size[1], grid->cell_size[2], rs2, max_neibs, neibs,
