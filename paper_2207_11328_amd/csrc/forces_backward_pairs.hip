@@ -529,12 +529,12 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
         TableMaker<BX, BY, BZ, NT> maker;
         maker.request(Q[0], wave, lane, count);
         load_chunks(Q[0], wave, lane);
+        if (wave == PREP)  // (while the others' loads arrive)
+            prepare_item<BX, BY, BZ, NT, CAP, kBackPairTime, LEAST>(Q[1], Q[0].d, false, lane, table, cap_ids, next,
+                                                                    cell_start, cell_end, G);
         maker.tally(T[0], wave, lane, M);
         __syncthreads();
         maker.place(T[0], wave, lane);
-        if (wave == PREP)
-            prepare_item<BX, BY, BZ, NT, CAP, kBackPairTime, LEAST>(Q[1], Q[0].d, false, lane, table, cap_ids, next,
-                                                                    cell_start, cell_end, G);
         __syncthreads();
     }
     int cur = 0;
