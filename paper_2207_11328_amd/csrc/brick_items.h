@@ -27,6 +27,8 @@
 // more centrals than lanes.
 #pragma once
 
+#include <type_traits>
+
 #include "sph_device.h"
 
 namespace sph {
@@ -131,8 +133,8 @@ __device__ __forceinline__ int lanes_scan(int v, int lane)
 
 // The next item into Q, by one wave: the rows left of item prev, else the next
 // part of a brick from the counter.  CAP: staged particles that fit in LDS;
-// NT: centrals that fit in the table.
-template <int BX, int BY, int BZ, int NT, int CAP, int PAIRS, int LEAST>
+// NC: centrals that fit in the table.
+template <int BX, int BY, int BZ, int NC, int CAP, int PAIRS, int LEAST>
 __device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const BrickItem &prev, bool first, int lane,
                                              const int32_t *__restrict__ table, int cap_ids,
                                              int32_t *__restrict__ next, const int32_t *__restrict__ cell_start,
@@ -233,9 +235,9 @@ __device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const Br
         span = __builtin_amdgcn_readfirstlane(Q.base[(yb + 2) * ROW]) - s_lo;
         nc = lanes_scan<4>(iy >= ya && iy < yb ? all : 0, lane);
         nc = __builtin_amdgcn_readlane(nc, 15);
-        if (yb == ya + 1 || total > kRunTotal || (span <= CAP && nc <= NT)) break;
+        if (yb == ya + 1 || total > kRunTotal || (span <= CAP && nc <= NC)) break;
     }
-    const bool lds = span <= CAP && nc <= NT && total <= kRunTotal;
+    const bool lds = span <= CAP && nc <= NC && total <= kRunTotal;
     const int cnt = iy >= ya && iy < yb ? all : 0;
     const int inc = lanes_scan<4>(cnt, lane);
     if (lane < 16) Q.row_first[lane] = lane < NR ? inc - cnt : INT32_MAX;
@@ -292,14 +294,43 @@ __device__ __forceinline__ void store_at(T *__restrict__ p, int i, const T &v)
 // centrals each: request() sends for the list counts, tally() leaves how many
 // of the wave's centrals have a list, and after a barrier place() writes the
 // entries, in sorted order.
-template <int NT>
+// NC: centrals that fit.  SHORT: an entry takes 3 bytes instead of 4, its list
+// length 8 bits, where kLongList stands for that many or more (length() reads
+// the count again): the 2 KB hold 51 more staged particles.
+constexpr int kLongList = 255;
+template <int NC, int NT, bool SHORT>
 struct CentralTable {
-    uint32_t cen[NT];
+    typename std::conditional<SHORT, uint16_t, uint32_t>::type cen[NC];
+    uint8_t len[SHORT ? NC : 1];
     int tally[NT / kWave];
     int used;  // entries: centrals with a list
+
+    __device__ __forceinline__ uint32_t entry(int q) const
+    {
+        return SHORT ? cen[q] | (uint32_t)len[q] << kCenCountShift : cen[q];
+    }
+    // list length of entry e, particle i (M: list slots per particle)
+    __device__ __forceinline__ static int length(uint32_t e, int i, const uint32_t *__restrict__ count, int M)
+    {
+        int n = (int)(e >> kCenCountShift);
+        if (SHORT && M >= kLongList && n == kLongList) {
+            const uint32_t cw = load_at(count, i);
+            n = min(min((int)(cw & 0xFFFFu), M) + (int)(cw >> 16), M);
+        }
+        return n;
+    }
+    __device__ __forceinline__ void set(int q, uint32_t slot_row, int n)
+    {
+        if constexpr (SHORT) {
+            cen[q] = (uint16_t)slot_row;
+            len[q] = (uint8_t)min(n, kLongList);
+        } else {
+            cen[q] = slot_row | (uint32_t)n << kCenCountShift;
+        }
+    }
 };
 
-template <int BX, int BY, int BZ, int NT>
+template <int BX, int BY, int BZ, int NC, int NT, bool SHORT>
 struct TableMaker {
     uint32_t entry;  // slot and row
     uint32_t cw;     // list count
@@ -323,7 +354,7 @@ struct TableMaker {
     }
 
     // M: list slots per particle
-    __device__ __forceinline__ void tally(CentralTable<NT> &T, int wave, int lane, int M)
+    __device__ __forceinline__ void tally(CentralTable<NC, NT, SHORT> &T, int wave, int lane, int M)
     {
         // (clamped: a stale or foreign list gives wrong numbers but never an
         // access outside the lists)
@@ -333,7 +364,7 @@ struct TableMaker {
         if (lane == 0) T.tally[wave] = some;
     }
 
-    __device__ __forceinline__ void place(CentralTable<NT> &T, int wave, int lane)
+    __device__ __forceinline__ void place(CentralTable<NC, NT, SHORT> &T, int wave, int lane)
     {
         constexpr int NW = NT / kWave;
         const int inc = lanes_scan<4>(lane < NW ? T.tally[min(lane, NW - 1)] : 0, lane);
@@ -342,7 +373,7 @@ struct TableMaker {
         const unsigned long long m = __builtin_amdgcn_ballot_w64(len > 0);
         const int p = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)before));
-        if (len > 0) T.cen[p] = entry | (uint32_t)len << kCenCountShift;
+        if (len > 0) T.set(p, entry, len);
     }
 };
 

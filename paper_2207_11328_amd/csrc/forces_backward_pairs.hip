@@ -472,7 +472,7 @@ __device__ __forceinline__ void store_adjoint(int i, int h, const BackAcc &A, fl
 // that of k_forces_brick.  The parameter derivatives are summed in double in a
 // fixed order: over the centrals of a group by its wave, over the groups of an
 // item, over the items in the order of the build's table.
-template <int MODEL, int BX, int BY, int BZ, int NT, int CAP>
+template <int MODEL, int BX, int BY, int BZ, int NT, int NC, int CAP>
 __global__ __launch_bounds__(NT) void k_forces_backward_brick(
     int n, const float4 *__restrict__ pos, const float4 *__restrict__ vel,
     const float4 *__restrict__ gforce, const uint32_t *__restrict__ neibs, const uint16_t *__restrict__ neibs_brick,
@@ -484,11 +484,11 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
 {
     constexpr int NW = NT / kWave, LEAST = BY == 4 ? 2 : 1;
     // a wave takes QG consecutive centrals of the table at a time
-    constexpr int QG = kWave / kLanes, MAXG = NT / QG;
+    constexpr int QG = kWave / kLanes, MAXG = NC / QG;
     static_assert(MAXG == kWave, "one lane per group in the sum over groups");
     __shared__ StagedBack<CAP> L;
     __shared__ BrickScans<BX, BY, BZ> Q[3];  // this item's, the next one's and the one after
-    __shared__ CentralTable<NT> T[2];        // this item's and the next one's
+    __shared__ CentralTable<NC, NT, false> T[2];        // this item's and the next one's
     __shared__ double par[3][MAXG];          // parameter sums of each group
     __shared__ double red[3][NW];
     __shared__ int sGroup;  // groups of centrals claimed in the item
@@ -517,7 +517,7 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
         if (threadIdx.x == 0) Q[2].d = BrickItem{};
         __syncthreads();
         if (wave == PREP)
-            prepare_item<BX, BY, BZ, NT, CAP, kBackPairTime, LEAST>(Q[0], Q[2].d, true, lane, table, cap_ids, next,
+            prepare_item<BX, BY, BZ, NC, CAP, kBackPairTime, LEAST>(Q[0], Q[2].d, true, lane, table, cap_ids, next,
                                                                     cell_start, cell_end, G);
         else if (!accumulate)
             for (int i = blockIdx.x * (PREP * kWave) + threadIdx.x; i < n; i += gridDim.x * (PREP * kWave))
@@ -526,15 +526,15 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
                     gvel[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 }
         __syncthreads();
-        TableMaker<BX, BY, BZ, NT> maker;
+        TableMaker<BX, BY, BZ, NC, NT, false> maker;
         maker.request(Q[0], wave, lane, count);
         load_chunks(Q[0], wave, lane);
-        if (wave == PREP)  // (while the others' loads arrive)
-            prepare_item<BX, BY, BZ, NT, CAP, kBackPairTime, LEAST>(Q[1], Q[0].d, false, lane, table, cap_ids, next,
-                                                                    cell_start, cell_end, G);
         maker.tally(T[0], wave, lane, M);
         __syncthreads();
         maker.place(T[0], wave, lane);
+        if (wave == PREP)
+            prepare_item<BX, BY, BZ, NC, CAP, kBackPairTime, LEAST>(Q[1], Q[0].d, false, lane, table, cap_ids, next,
+                                                                    cell_start, cell_end, G);
         __syncthreads();
     }
     int cur = 0;
@@ -547,13 +547,13 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
         asm volatile("" : "+v"(tid));
         const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
         const BrickScans<BX, BY, BZ> &B = Q[cur];
-        const CentralTable<NT> &D = T[k & 1];
-        CentralTable<NT> &DN = T[(k & 1) ^ 1];
+        const CentralTable<NC, NT, false> &D = T[k & 1];
+        CentralTable<NC, NT, false> &DN = T[(k & 1) ^ 1];
         if (__builtin_amdgcn_readfirstlane(B.d.item) < 0) break;
         const int s_lo = __builtin_amdgcn_readfirstlane(B.d.s_lo), span = __builtin_amdgcn_readfirstlane(B.d.span);
         const bool use_lds = __builtin_amdgcn_readfirstlane(B.d.lds) != 0;
         const int nc = __builtin_amdgcn_readfirstlane(use_lds ? D.used : B.d.nc);
-        TableMaker<BX, BY, BZ, NT> maker;
+        TableMaker<BX, BY, BZ, NC, NT, false> maker;
         maker.request(Q[nxt], wave, lane, count);
         const int h = lane % kLanes;
         const uint32_t lo2 = (uint32_t)s_lo * 0x10001u, max2 = (uint32_t)(span - 1) * 0x10001u;
@@ -579,7 +579,7 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
         if (wave == PREP) {
             // (few instructions in a long chain of latencies: it goes first)
             __builtin_amdgcn_s_setprio(3);
-            prepare_item<BX, BY, BZ, NT, CAP, kBackPairTime, LEAST>(Q[far], Q[nxt].d, false, lane, table, cap_ids,
+            prepare_item<BX, BY, BZ, NC, CAP, kBackPairTime, LEAST>(Q[far], Q[nxt].d, false, lane, table, cap_ids,
                                                                     next, cell_start, cell_end, G);
             __builtin_amdgcn_s_setprio(0);
         }
@@ -588,7 +588,7 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
             BackAcc A = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             int i, nt;
             if (use_lds) {
-                const uint32_t e = D.cen[min(q, nc - 1)];
+                const uint32_t e = D.entry(min(q, nc - 1));
                 const int si = (int)(e & kCenSlotMask);
                 nt = q < nc ? (int)(e >> kCenCountShift) : 0;
                 i = min(si + B.row_shift[e >> kCenRowShift & 15u], n - 1);
@@ -693,7 +693,7 @@ void launch_backward_brick(const BackArgs &a, const BackConst &C, hipStream_t s)
         const unsigned blocks = (unsigned)G.nbx * G.nby * G.nbz;
         // (the counters were cleared before the launch; the table of bricks
         // with a pair is the build's)
-        k_forces_backward_brick<MODEL, BX, BY, BZ, kBackThreads, kBackCap>
+        k_forces_backward_brick<MODEL, BX, BY, BZ, kBackThreads, kBackThreads, kBackCap>
             <<<brick_workgroups(blocks, BY), kBackThreads, 0, s>>>(
                 a.n, a.pos, a.vel, a.gforce, a.neibs, a.neibs_brick, a.count, a.cell_start, a.cell_end, a.table,
                 a.cap_ids, a.next, a.info, a.gpos, a.gvel, a.partial, a.grad_params, a.accumulate, C, G);

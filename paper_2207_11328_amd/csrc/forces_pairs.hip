@@ -412,7 +412,7 @@ __device__ __forceinline__ void empty_lists(int n, const uint32_t *__restrict__ 
 // Per item on the 1.62M-particle dam break (full bricks, 6.1 items per CU,
 // times of the mean wave): 1.9 us to stage, 0.8 us at the barrier, 13.7 us of
 // pairs, 1.0 us for the next item, 3.3 us waiting for the last wave.
-template <int MODEL, int BX, int BY, int BZ, int NT, int CAP>
+template <int MODEL, int BX, int BY, int BZ, int NT, int NC, int CAP>
 __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__restrict__ pos,
                                                      const float4 *__restrict__ vel,
                                                      const int32_t *__restrict__ cell,
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
     constexpr int NI = St::NI, NW = NT / kWave;
     __shared__ Staged<CAP> L;
     __shared__ BrickScans<BX, BY, BZ> Q[3];  // this item's, the next one's and the one after
-    __shared__ CentralTable<NT> T[2];        // this item's and the next one's
+    __shared__ CentralTable<NC, NT, true> T[2];        // this item's and the next one's
     __shared__ int sGroup;  // groups of centrals claimed in the item
     // (corrector with a step per scene) each inner cell's scene (-1: none) and step
     __shared__ int sSc[NI];
@@ -460,15 +460,15 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         if (threadIdx.x == 0) Q[2].d = BrickItem{};
         __syncthreads();
         if (wave == PREP)
-            prepare_item<BX, BY, BZ, NT, CAP, kPairTime, 1>(Q[0], Q[2].d, true, lane, table, cap_ids, next, cell_start, cell_end, G);
+            prepare_item<BX, BY, BZ, NC, CAP, kPairTime, 1>(Q[0], Q[2].d, true, lane, table, cap_ids, next, cell_start, cell_end, G);
         else
             empty_lists<PREP * kWave>(n, count, vel, out, tau, K);
         __syncthreads();
-        TableMaker<BX, BY, BZ, NT> maker;
+        TableMaker<BX, BY, BZ, NC, NT, true> maker;
         maker.request(Q[0], wave, lane, count);
         load_chunks(Q[0], wave, lane);
         if (wave == PREP)  // (while the others' loads arrive)
-            prepare_item<BX, BY, BZ, NT, CAP, kPairTime, 1>(Q[1], Q[0].d, false, lane, table, cap_ids, next, cell_start, cell_end, G);
+            prepare_item<BX, BY, BZ, NC, CAP, kPairTime, 1>(Q[1], Q[0].d, false, lane, table, cap_ids, next, cell_start, cell_end, G);
         maker.tally(T[0], wave, lane, M);
         __syncthreads();
         maker.place(T[0], wave, lane);
@@ -483,13 +483,13 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         asm volatile("" : "+v"(tid));
         const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
         const BrickScans<BX, BY, BZ> &B = Q[cur];
-        const CentralTable<NT> &D = T[k & 1];
-        CentralTable<NT> &DN = T[(k & 1) ^ 1];
+        const CentralTable<NC, NT, true> &D = T[k & 1];
+        CentralTable<NC, NT, true> &DN = T[(k & 1) ^ 1];
         if (__builtin_amdgcn_readfirstlane(B.d.item) < 0) break;
         const int s_lo = __builtin_amdgcn_readfirstlane(B.d.s_lo), span = __builtin_amdgcn_readfirstlane(B.d.span);
         const bool use_lds = __builtin_amdgcn_readfirstlane(B.d.lds) != 0;
         const int nc = __builtin_amdgcn_readfirstlane(use_lds ? D.used : B.d.nc);
-        TableMaker<BX, BY, BZ, NT> maker;
+        TableMaker<BX, BY, BZ, NC, NT, true> maker;
         maker.request(Q[nxt], wave, lane, count);
 
         // a wave takes QG consecutive centrals of the table at a time
@@ -512,12 +512,13 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         auto take = [&](int g) {
             Central c;
             const int q = g * QG + lane / kLanes;
-            c.e = D.cen[max(min(q, nc - 1), 0)];
-            c.nt = q < nc ? (int)(c.e >> kCenCountShift) : 0;
+            c.e = D.entry(max(min(q, nc - 1), 0));
             const uint32_t i = (c.e & kCenSlotMask) + (uint32_t)B.row_shift[c.e >> kCenRowShift & 15u];
             c.i = (int)min(i, (uint32_t)(n - 1));
+            const int len = D.length(c.e, c.i, count, M);
+            c.nt = q < nc ? len : 0;
             c.lg = list_groups(neibs_brick, c.i, brick_groups(M));
-            const int last = min(max((int)(c.e >> kCenCountShift) - 1, 0) / kEntries, brick_groups(M) - 1);
+            const int last = min(max(len - 1, 0) / kEntries, brick_groups(M) - 1);
             c.list = list_entries(c.lg, min(h, last));
             c.more = list_entries(c.lg, min(h + kLanes, last));
             return c;
@@ -563,7 +564,7 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         if (wave == PREP) {
             // (few instructions in a long chain of latencies: it goes first)
             __builtin_amdgcn_s_setprio(3);
-            prepare_item<BX, BY, BZ, NT, CAP, kPairTime, 1>(Q[far], Q[nxt].d, false, lane, table, cap_ids, next, cell_start, cell_end,
+            prepare_item<BX, BY, BZ, NC, CAP, kPairTime, 1>(Q[far], Q[nxt].d, false, lane, table, cap_ids, next, cell_start, cell_end,
                                               G);
             __builtin_amdgcn_s_setprio(0);
         }
@@ -638,12 +639,16 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
 }
 
 // A workgroup has the LDS of a CU to itself whatever the brick shape: 40
-// bytes per staged particle, 13 KB of scans and tables.  The halo of a brick at the h =
+// bytes per staged particle, 10.5 KB of scans and tables.  The halo of a brick at the h =
 // 1.3 dp, r_s = 2.86 dp lattice density holds up to about 27 particles per
-// staged cell (3 x 4 x 3: 150 cells, 3825 at most in the 1.62M dam break);
-// bricks beyond the capacity are taken in runs of fewer rows.
+// staged cell (3 x 4 x 3: 150 cells, at most 15 x 17 x 15 = 3825 lattice places
+// in the 1.62M dam break and in tanks of 0.1 to 0.4M, and 9 x 12 x 9 = 972
+// centrals); bricks beyond the capacity are taken in runs of fewer rows.  In
+// a call of one round of bricks the last one is waited for: tank of 107k particles, 148
+// bricks, 34.2 us, and 40.7 with room for 3760 (1% of its bricks cut).
 constexpr int kBrickThreads = 1024;
-constexpr int kBrickCap = 3760;
+constexpr int kBrickCentrals = 976;
+constexpr int kBrickCap = 3828;
 
 template <int MODEL>
 void launch_brick(const ForceArgs &a, const ForceConst &C, hipStream_t s)
@@ -654,7 +659,7 @@ void launch_brick(const ForceArgs &a, const ForceConst &C, hipStream_t s)
         // (the item counter, if used, was zeroed before the launch; the table of
         // bricks with a pair is the build's; at most one item per row of a brick)
         const unsigned wgs = brick_workgroups(blocks, BY);
-        k_forces_brick<MODEL, BX, BY, BZ, kBrickThreads, kBrickCap><<<wgs, kBrickThreads, 0, s>>>(
+        k_forces_brick<MODEL, BX, BY, BZ, kBrickThreads, kBrickCentrals, kBrickCap><<<wgs, kBrickThreads, 0, s>>>(
             a.n, a.pos, a.vel, a.cell, a.neibs, a.neibs_brick, a.count, a.cell_start, a.cell_end, a.table,
             a.cap_ids, a.next, a.info, a.out, C, G, a.K);
     });

@@ -179,3 +179,48 @@ def test_short_lists(M, brick):
         else:
             assert (cnt == 0).any() and (cnt > 0).any()
             assert ((b - g).abs() <= 1e-5 * scale).all(), (b - g).abs().max(dim=0)
+
+
+def test_lists_around_255():
+    """Lists on both sides of the length that no longer fits an entry of the
+    table of centrals, in items that are staged."""
+    sc = S.random_cloud(n=640, box=(0.12, 0.12, 0.12), dp=0.02, seed=77, boundary_frac=0.1, u_sigma=0.2)
+    sim = make_sim(sc, max_neibs=512)
+    sim.build()
+    f = sim.forces(bricks=True).clone()
+    torch_sync()
+    cnt = sim.neib_count[: sc.n].cpu().numpy().view(np.uint32)
+    cnt = (cnt & 0xFFFF) + (cnt >> 16)
+    log("case long lists: n=%d, lists of %d to %d" % (sc.n, cnt.min(), cnt.max()))
+    assert np.isin([254, 255, 256], cnt).any() and cnt.min() < 200 and 256 < cnt.max() <= 512
+    ob = compare_build(sc, sim, max_neibs=512)
+    _, (acc, drho, sa, sd, _ni) = oracle_forces_of(sc, ob)
+    check_forces(f[: sc.n].cpu().numpy(), acc, drho, sa, sd, label="long lists")
+
+
+def test_the_largest_whole_brick():
+    """15 x 17 x 15 lattice places in the halo of a brick (the most at 1.3
+    spacings per smoothing length, but for one alignment): within three of
+    what is staged whole."""
+    dp, m = 0.02, (24, 29, 24)
+    p = S.sph_params(dp)
+    grid = S.make_grid((0.0,) * 3, tuple(k * dp for k in m), p.r_search)
+    i = np.stack(np.meshgrid(*[np.arange(k) for k in m], indexing="ij"), -1).reshape(-1, 3)
+    cell, off = S.encode_positions(grid, (i + 0.5) * dp)
+    n = len(i)
+    rng = np.random.default_rng(4)
+    pos = np.zeros((n, 4), np.float32)
+    pos[:, :3] = off
+    pos[:, 3] = 1000.0 * dp ** 3
+    vel = rng.normal(0.0, 0.2, (n, 4)).astype(np.float32)
+    vel[:, 3] = 1000.0 * (1 + rng.normal(0.0, 3e-3, n))
+    sc = S.Scene("lattice", grid, p, cell, pos, vel, np.arange(n, dtype=np.uint32), n, 0)
+    assert _brick_totals(sc, (3, 4, 3)).max() == 3825
+    log("case largest brick: n=%d" % n)
+    sim = make_sim(sc)
+    sim.build()
+    f = sim.forces(bricks=True).clone()
+    torch_sync()
+    ob = compare_build(sc, sim)
+    _, (acc, drho, sa, sd, _ni) = oracle_forces_of(sc, ob)
+    check_forces(f[:n].cpu().numpy(), acc, drho, sa, sd, label="largest brick")
