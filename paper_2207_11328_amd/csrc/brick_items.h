@@ -33,45 +33,55 @@
 
 namespace sph {
 
-// How the n bricks of the table are cut into items, by their place in it: the
-// first `whole` (the larger ones) into `first` parts each, the others into `rest`.
+// How the bricks of the table are cut into items, by their place in it: all but
+// `cut` of them, which come after the first `whole` (the larger ones), into
+// `first` parts each, then those into `rest`.
 struct BrickSplit {
-    int whole, first, rest, items;
+    int whole, cut, first, rest, uncut, items;  // uncut: items of the first kind
 };
 
-// The split for wgs workgroups: rounds of whole bricks, and the bricks left
-// over cut so that their rounds, times the cost of an item, cost least: about
-// 5 us of staging and latency for a whole brick, 4 for a half, 3.5 for a row,
-// and PAIRS halves of a microsecond for the pairs of a 3 x 4 x 3 brick.  From
-// four rounds on the bricks stay whole: what is left over is small.  Tank of
-// 15.5k particles (27 bricks with a pair): 17.1 us in rows against 30.0 with
-// whole bricks; 169k dam break (120, cubic spline, Landrini-Morris, Morris
-// viscosity, diffusion): 34.8 us in halves against 51.4; 300k channel of 3 x 3 x 3 bricks:
-// 58.5 us with the last round in rows against 66.6 with all whole.
+// The split of n bricks, `heavy` of them heavy ones, for wgs workgroups.  Less
+// than a round of bricks: all of them into the parts whose rounds, times the
+// cost of an item, cost least: about 5 us of staging and latency for a whole
+// brick, 4 for a half, 3.5 for a row, and PAIRS halves of a microsecond for the
+// pairs of a full 3 x 4 x 3 brick.  One to two rounds of heavy bricks: a round of
+// whole ones, and those left over (the smallest, about 0.6 of a full one) cut
+// where that costs less; the light ones fill the gaps whole.  Otherwise the
+// bricks stay whole: what is left over is light, or small against the rounds.
+// Tank of 15.5k particles (27 bricks with a pair): 17.1 us in rows against 30.0
+// with whole bricks; 169k dam break (120, cubic spline, Landrini-Morris, Morris
+// viscosity, diffusion): 34.8 us in halves against 51.4; 277k tank (352, nearly
+// all heavy): 44.6 us with the left over cut against 54.9 whole; batch of 18
+// tanks (315, about half of them light): 33.5 us whole against 41.5 with 59 cut; batch
+// of 40 tanks (925): 77.7 us whole against 80.8 with the left over cut.
 // FIRST: the parts below which no item would fit in LDS, limit: the most items
 // (there are slots for).
 template <int BX, int BY, int BZ, int PAIRS, int FIRST>
-__device__ __forceinline__ BrickSplit brick_split(int n, int wgs, int limit)
+__device__ __forceinline__ BrickSplit brick_split(int n, int heavy, int wgs, int limit)
 {
-    constexpr int P = PAIRS * BX * BY * BZ / 36;
-    constexpr auto cost = [](int parts) { return (parts == 1 ? 10 : parts == BY ? 7 : 8) + P / parts; };
+    constexpr int P = PAIRS * BX * BY * BZ / 36, P_LEFT = P * 3 / 5;
+    constexpr auto fixed = [](int parts) { return parts == 1 ? 10 : parts == BY ? 7 : 8; };
     constexpr int HALF = BY % 2 == 0 && BY > 2 ? 2 : FIRST;
-    if (n * FIRST > limit) return {n, 1, 1, n};
-    BrickSplit best = {n, FIRST, FIRST, n * FIRST};
-    if (n * FIRST >= 4 * wgs) return best;
-    int rounds = 0, least = INT32_MAX;
-    while ((rounds + 1) * wgs <= n * FIRST) ++rounds;  // at most 3
+    if (n * FIRST > limit) return {n, 0, 1, 1, n, n};
+    BrickSplit best = {n, 0, FIRST, FIRST, n * FIRST, n * FIRST};
+    const bool few = n * FIRST < wgs;
+    if (few) heavy = n;
+    if (!few && (heavy * FIRST < wgs || heavy * FIRST >= 2 * wgs)) return best;
+    int least = INT32_MAX;
 #pragma unroll
     for (int back = 0; back < 2; ++back) {
-        const int done = max(rounds - back, 0), whole = done * wgs / FIRST, left = n - whole;
+        if (few && !back) continue;
+        const int whole = back ? 0 : wgs / FIRST, left = heavy - whole;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const int parts = k == 0 ? FIRST : k == 1 ? HALF : BY, items = whole * FIRST + left * parts;
+            const int parts = k == 0 ? FIRST : k == 1 ? HALF : BY, items = left * parts + (n - left) * FIRST;
             if (k == 1 && HALF == FIRST) continue;
-            int c = done * cost(FIRST);
-            for (int i = left * parts; i > 0; i -= wgs) c += cost(parts);  // (2 BY rounds at most)
+            int c = back ? 0 : fixed(FIRST) + P / FIRST;
+            const int each = fixed(parts) + (back ? P : P_LEFT) / parts;
+            for (int i = left * parts; i > 0; i -= wgs) c += each;  // (2 BY rounds at most)
             if (c < least && items <= limit) {
-                best = {whole, FIRST, parts, items};
+                const int cut = parts == FIRST ? 0 : left;  // (else all in the table's order)
+                best = {whole, cut, FIRST, parts, (n - cut) * FIRST, items};
                 least = c;
             }
         }
@@ -80,9 +90,10 @@ __device__ __forceinline__ BrickSplit brick_split(int n, int wgs, int limit)
 }
 
 template <int BX, int BY, int BZ, int PAIRS, int FIRST>
-__device__ __forceinline__ BrickSplit item_split(int n_listed, const BrickGrid &G)
+__device__ __forceinline__ BrickSplit item_split(const int32_t *__restrict__ table, int cap_ids, const BrickGrid &G)
 {
-    return brick_split<BX, BY, BZ, PAIRS, FIRST>(n_listed, gridDim.x, G.nx * G.ny * G.nz);
+    const int heavy = table[0], n = heavy + table[cap_ids + 1];
+    return brick_split<BX, BY, BZ, PAIRS, FIRST>(n, heavy, gridDim.x, G.nx * G.ny * G.nz);
 }
 
 // Descriptor of an item.
@@ -155,9 +166,9 @@ __device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const Br
         // counter (zeroed before the launch), or, without one, rounds of
         // workgroups take the items, which are ordered by size, forwards and
         // backwards in turn
-        const int heavy = table[0], n_listed = heavy + table[cap_ids + 1];
+        const int heavy = table[0];
         const int guess = first ? table[1 + min((int)blockIdx.x, cap_ids - 1)] : 0;  // (sent for with the counts)
-        const BrickSplit B = item_split<BX, BY, BZ, PAIRS, LEAST>(n_listed, G);
+        const BrickSplit B = item_split<BX, BY, BZ, PAIRS, LEAST>(table, cap_ids, G);
         const int items = B.items, last = __builtin_amdgcn_readfirstlane(prev.item);
         item = items;
         if (first) {
@@ -179,11 +190,11 @@ __device__ __forceinline__ void prepare_item(BrickScans<BX, BY, BZ> &Q, const Br
             }
             return;
         }
-        const bool cut = item >= B.whole * B.first;
-        const int parts = cut ? B.rest : B.first, of = cut ? item - B.whole * B.first : item;
+        const bool piece = item >= B.uncut;
+        const int parts = piece ? B.rest : B.first, of = piece ? item - B.uncut : item;
         const int quot = parts == 1 ? of : parts == 2 ? of / 2 : parts == 3 ? of / 3 : of / 4;
         static_assert(BY <= 4, "parts of a brick");
-        const int place = (cut ? B.whole : 0) + quot;
+        const int place = piece ? B.whole + quot : quot < B.whole ? quot : quot + B.cut;
         b = first && place == (int)blockIdx.x && place < heavy ? guess : brick_at(table, cap_ids, place);
         const int rows = parts == 1 ? BY : parts == BY ? 1 : BY / 2;
         ya = (of - quot * parts) * rows;

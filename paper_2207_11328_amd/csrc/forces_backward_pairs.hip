@@ -679,8 +679,7 @@ __global__ __launch_bounds__(NT) void k_forces_backward_brick(
     __syncthreads();
     if (sLast) {  // uniform
         __threadfence();
-        const int n_listed = table[0] + table[cap_ids + 1];
-        sum_partials<NT>(tid, item_split<BX, BY, BZ, kBackPairTime, LEAST>(n_listed, G).items, partial, grad_params,
+        sum_partials<NT>(tid, item_split<BX, BY, BZ, kBackPairTime, LEAST>(table, cap_ids, G).items, partial, grad_params,
                          accumulate, red);
     }
 }
