@@ -40,50 +40,53 @@ struct BrickSplit {
     int whole, cut, first, rest, uncut, items;  // uncut: items of the first kind
 };
 
-// The split of n bricks, `heavy` of them heavy ones, for wgs workgroups.  Less
-// than a round of bricks: all of them into the parts whose rounds, times the
-// cost of an item, cost least: about 5 us of staging and latency for a whole
+// The split of n bricks, `heavy` of them heavy ones, for wgs workgroups.
+// Less than a round of bricks: all of them into the parts whose rounds, times
+// the cost of an item, cost least: about 5 us of staging and latency for a whole
 // brick, 4 for a half, 3.5 for a row, and PAIRS halves of a microsecond for the
-// pairs of a full 3 x 4 x 3 brick.  One to two rounds of heavy bricks: a round of
-// whole ones, and those left over (the smallest, about 0.6 of a full one) cut
-// where that costs less; the light ones fill the gaps whole.  Otherwise the
-// bricks stay whole: what is left over is light, or small against the rounds.
-// Tank of 15.5k particles (27 bricks with a pair): 17.1 us in rows against 30.0
-// with whole bricks; 169k dam break (120, cubic spline, Landrini-Morris, Morris
-// viscosity, diffusion): 34.8 us in halves against 51.4; 277k tank (352, nearly
-// all heavy): 44.6 us with the left over cut against 54.9 whole; batch of 18
-// tanks (315, about half of them light): 33.5 us whole against 41.5 with 59 cut; batch
-// of 40 tanks (925): 77.7 us whole against 80.8 with the left over cut.
+// pairs of a full 3 x 4 x 3 brick.  Tank of 15.5k particles (27 bricks with a
+// pair): 16.9 us in rows against 30.0 with whole bricks; 169k dam break (120,
+// cubic spline, Landrini-Morris, Morris viscosity, diffusion): 34.1 us in halves
+// against 51.4.
+// One to three rounds of heavy bricks: whole ones, and the heavy ones left over
+// by the last whole round in the smallest parts that keep all items within one
+// round more; the light ones are short and fill the gaps whole, before the
+// parts.  Tank of 320 bricks, 280 of them heavy: 55.6 us
+// with the 24 left over in rows against 64.5 whole; 378, 325 heavy: 56.5 us in halves
+// against 63.8, and 66.3 in rows (three rounds of items); batch of 497, 364 heavy: 64.6 us
+// whole against 78.7 in halves (as many rounds more); tank of 567, 564 heavy: 70.6 us in rows
+// against 78.1.  From three rounds on what is left over is small against
+// them: no split of 770 to 1030 bricks was faster than whole ones.
 // FIRST: the parts below which no item would fit in LDS, limit: the most items
 // (there are slots for).
 template <int BX, int BY, int BZ, int PAIRS, int FIRST>
 __device__ __forceinline__ BrickSplit brick_split(int n, int heavy, int wgs, int limit)
 {
-    constexpr int P = PAIRS * BX * BY * BZ / 36, P_LEFT = P * 3 / 5;
-    constexpr auto fixed = [](int parts) { return parts == 1 ? 10 : parts == BY ? 7 : 8; };
+    constexpr int P = PAIRS * BX * BY * BZ / 36;
+    constexpr auto cost = [](int parts) { return (parts == 1 ? 10 : parts == BY ? 7 : 8) + P / parts; };
     constexpr int HALF = BY % 2 == 0 && BY > 2 ? 2 : FIRST;
     if (n * FIRST > limit) return {n, 0, 1, 1, n, n};
     BrickSplit best = {n, 0, FIRST, FIRST, n * FIRST, n * FIRST};
-    const bool few = n * FIRST < wgs;
-    if (few) heavy = n;
-    if (!few && (heavy * FIRST < wgs || heavy * FIRST >= 2 * wgs)) return best;
-    int least = INT32_MAX;
-#pragma unroll
-    for (int back = 0; back < 2; ++back) {
-        if (few && !back) continue;
-        const int whole = back ? 0 : wgs / FIRST, left = heavy - whole;
+    if (n * FIRST < wgs) {
+        int least = INT32_MAX;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const int parts = k == 0 ? FIRST : k == 1 ? HALF : BY, items = left * parts + (n - left) * FIRST;
+            const int parts = k == 0 ? FIRST : k == 1 ? HALF : BY;
             if (k == 1 && HALF == FIRST) continue;
-            int c = back ? 0 : fixed(FIRST) + P / FIRST;
-            const int each = fixed(parts) + (back ? P : P_LEFT) / parts;
-            for (int i = left * parts; i > 0; i -= wgs) c += each;  // (2 BY rounds at most)
-            if (c < least && items <= limit) {
-                const int cut = parts == FIRST ? 0 : left;  // (else all in the table's order)
-                best = {whole, cut, FIRST, parts, (n - cut) * FIRST, items};
+            int c = 0;
+            for (int i = n * parts; i > 0; i -= wgs) c += cost(parts);  // (BY rounds at most)
+            if (c < least && n * parts <= limit) {
+                best = {n, 0, parts, parts, n * parts, n * parts};
                 least = c;
             }
+        }
+    } else if (heavy * FIRST > wgs && heavy * FIRST < 3 * wgs) {
+        const int rounds = heavy * FIRST < 2 * wgs ? 1 : 2, whole = rounds * wgs / FIRST, left = heavy - whole;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int parts = k == 0 ? HALF : BY, items = (n - left) * FIRST + left * parts;
+            if (parts > FIRST && items <= (rounds + 1) * wgs && items <= limit)
+                best = {whole, left, FIRST, parts, (n - left) * FIRST, items};
         }
     }
     return best;

@@ -224,3 +224,63 @@ def test_the_largest_whole_brick():
     ob = compare_build(sc, sim)
     _, (acc, drho, sa, sd, _ni) = oracle_forces_of(sc, ob)
     check_forces(f[:n].cpu().numpy(), acc, drho, sa, sd, label="largest brick")
+
+
+def _layers(sizes, brick, dp=0.02, per_cell=8, seed=1):
+    """A row of bricks along x, brick k with every inner cell filled for
+    sizes[k] = 1 and only one layer of cells along y for sizes[k] = 0."""
+    p = S.sph_params(dp)
+    cs = np.float32(p.r_search)
+    nx = brick[0] * len(sizes)
+    grid = S.Grid(origin=np.zeros(3), cell_size=np.array([cs] * 3), ncell=np.array([nx, brick[1], brick[2]], np.int32))
+    x, y, z = np.meshgrid(np.arange(nx), np.arange(brick[1]), np.arange(brick[2]), indexing="ij")
+    full = np.asarray(sizes, bool)[x // brick[0]] | (y == 0)
+    lin = (x + nx * (y + brick[1] * z))[full]
+    cell = np.repeat(lin, per_cell).astype(np.int32)
+    n = cell.size
+    rng = np.random.default_rng(seed)
+    pos = np.zeros((n, 4), np.float32)
+    pos[:, :3] = rng.uniform(-0.49, 0.49, (n, 3)) * cs
+    pos[:, 3] = 1000.0 * float(cs) ** 3 / per_cell
+    vel = rng.normal(0.0, 0.2, (n, 4)).astype(np.float32)
+    vel[:, 3] = 1000.0 * (1 + rng.normal(0.0, 3e-3, n))
+    info = (np.arange(n) | ((rng.random(n) < 0.1).astype(np.int64) << 30)).astype(np.uint32)
+    return S.Scene("layers", grid, p, cell, pos, vel, info, int((info >> 30 == 0).sum()), int((info >> 30 == 1).sum()))
+
+
+# bricks, every how manyth is light (0: none), particles per filled cell (13: heavy)
+ROUNDS = [(300, 0, 13), (300, 0, 8), (400, 3, 13), (430, 4, 13), (520, 0, 13), (560, 5, 13), (700, 0, 13), (800, 2, 13)]
+
+
+@pytest.mark.parametrize("brick", SHAPES, ids=["x".join(map(str, b)) for b in SHAPES])
+@pytest.mark.parametrize("bricks,every,per_cell", ROUNDS)
+def test_rounds_of_heavy_and_light_bricks(bricks, every, per_cell, brick):
+    """One to three rounds of bricks, heavy and light ones, on each side of the
+    lines of the split: every particle's derivatives and adjoint against the
+    gather forms, which have no items, and the parameter sums."""
+    from paper_2207_11328_amd import abi
+    sc = _layers([0 if every and k % every == 0 else 1 for k in range(bricks)], brick, per_cell=per_cell)
+    log("case rounds of %d bricks %s: n=%d" % (bricks, brick, sc.n))
+    sim = make_sim(sc, max_neibs=192, brick=brick)
+    sim.build()
+    assert sim.status_host()["overflow"] == 0
+    cap, E = sim.capacity, -(-sim.capacity // 64) * 512 * 24
+    t = sim.neibs_brick[E:].view(torch.int32)
+    assert int(t[0]) + int(t[cap + 1]) == bricks and (per_cell < 12 or int(t[cap + 1]) == (-(-bricks // every) if every else 0))
+    gf = torch.sin(torch.arange(4 * cap, device=sim.device, dtype=torch.float32)).view(-1, 4)
+    got = []
+    for b in (True, False):
+        sim.forces_n.fill_(float("nan"))
+        f = sim.forces(bricks=b).clone()
+        gp, gv = torch.full_like(sim.pos, float("nan")), torch.full_like(sim.pos, float("nan"))
+        par = torch.zeros(3, dtype=torch.float64, device=sim.device)
+        ws = torch.zeros(abi.sph_forces_backward_workspace_bytes(cap, sim.n_cells), dtype=torch.uint8, device=sim.device)
+        abi.sph_forces_backward(sim.g, sim.p, sim.parts, sim.neibs, sim.neib_count, sim.max_neibs, gf, gp, gv, par,
+                                False, ws, None, *sim.brick_args(b))
+        torch_sync()
+        got.append((f[: sc.n], gp[: sc.n, :3], gv[: sc.n], par))
+    # a particle without its item, or with a part of its sum twice, is off by
+    # the size of its terms; the two forms differ by rounding
+    for a, b in zip(*got):
+        scale = b.abs().amax(dim=0)
+        assert torch.isfinite(a).all() and ((a - b).abs() <= 1e-4 * scale).all(), ((a - b).abs() / scale).amax()
