@@ -429,9 +429,10 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
 {
     using St = Staging<BX, BY, BZ>;
     constexpr int NI = St::NI, NW = NT / kWave;
+    constexpr bool SHORT = NC < NT;  // entries of the table of centrals
     __shared__ Staged<CAP> L;
     __shared__ BrickScans<BX, BY, BZ> Q[3];  // this item's, the next one's and the one after
-    __shared__ CentralTable<NC, NT, true> T[2];        // this item's and the next one's
+    __shared__ CentralTable<NC, NT, SHORT> T[2];        // this item's and the next one's
     __shared__ int sGroup;  // groups of centrals claimed in the item
     // (corrector with a step per scene) each inner cell's scene (-1: none) and step
     __shared__ int sSc[NI];
@@ -464,7 +465,7 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         else
             empty_lists<PREP * kWave>(n, count, vel, out, tau, K);
         __syncthreads();
-        TableMaker<BX, BY, BZ, NC, NT, true> maker;
+        TableMaker<BX, BY, BZ, NC, NT, SHORT> maker;
         maker.request(Q[0], wave, lane, count);
         load_chunks(Q[0], wave, lane);
         if (wave == PREP)  // (while the others' loads arrive)
@@ -483,13 +484,13 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
         asm volatile("" : "+v"(tid));
         const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
         const BrickScans<BX, BY, BZ> &B = Q[cur];
-        const CentralTable<NC, NT, true> &D = T[k & 1];
-        CentralTable<NC, NT, true> &DN = T[(k & 1) ^ 1];
+        const CentralTable<NC, NT, SHORT> &D = T[k & 1];
+        CentralTable<NC, NT, SHORT> &DN = T[(k & 1) ^ 1];
         if (__builtin_amdgcn_readfirstlane(B.d.item) < 0) break;
         const int s_lo = __builtin_amdgcn_readfirstlane(B.d.s_lo), span = __builtin_amdgcn_readfirstlane(B.d.span);
         const bool use_lds = __builtin_amdgcn_readfirstlane(B.d.lds) != 0;
         const int nc = __builtin_amdgcn_readfirstlane(use_lds ? D.used : B.d.nc);
-        TableMaker<BX, BY, BZ, NC, NT, true> maker;
+        TableMaker<BX, BY, BZ, NC, NT, SHORT> maker;
         maker.request(Q[nxt], wave, lane, count);
 
         // a wave takes QG consecutive centrals of the table at a time
@@ -645,10 +646,12 @@ __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__rest
 // in the 1.62M dam break and in tanks of 0.1 to 0.4M, and 9 x 12 x 9 = 972
 // centrals); bricks beyond the capacity are taken in runs of fewer rows.  In
 // a call of one round of bricks the last one is waited for: tank of 107k particles, 148
-// bricks, 34.2 us, and 40.7 with room for 3760 (1% of its bricks cut).
+// bricks, 33.2 us, and 40.7 with room for 3760 (1% of its bricks cut).  The smaller
+// shapes hold at most 3375 at that density and keep the plain table (3 x 2 x 3,
+// cubic spline, 1.38M particles: 208 us, and 212 with the short one).
 constexpr int kBrickThreads = 1024;
-constexpr int kBrickCentrals = 976;
-constexpr int kBrickCap = 3828;
+constexpr int brick_centrals(int cells) { return cells >= 36 ? 976 : kBrickThreads; }
+constexpr int brick_cap(int cells) { return cells >= 36 ? 3828 : 3760; }
 
 template <int MODEL>
 void launch_brick(const ForceArgs &a, const ForceConst &C, hipStream_t s)
@@ -659,7 +662,7 @@ void launch_brick(const ForceArgs &a, const ForceConst &C, hipStream_t s)
         // (the item counter, if used, was zeroed before the launch; the table of
         // bricks with a pair is the build's; at most one item per row of a brick)
         const unsigned wgs = brick_workgroups(blocks, BY);
-        k_forces_brick<MODEL, BX, BY, BZ, kBrickThreads, kBrickCentrals, kBrickCap><<<wgs, kBrickThreads, 0, s>>>(
+        k_forces_brick<MODEL, BX, BY, BZ, kBrickThreads, brick_centrals(BX * BY * BZ), brick_cap(BX * BY * BZ)><<<wgs, kBrickThreads, 0, s>>>(
             a.n, a.pos, a.vel, a.cell, a.neibs, a.neibs_brick, a.count, a.cell_start, a.cell_end, a.table,
             a.cap_ids, a.next, a.info, a.out, C, G, a.K);
     });
