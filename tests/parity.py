@@ -271,6 +271,72 @@ def edge_allowance(sc, ob):
     return aa, ad
 
 
+def adjoint_edge_allowance(sc, ob, abar, dbar):
+    """edge_allowance for the adjoint (Wendland kernel, golden rule, artificial
+    viscosity): what the float32 rounding of the separation (dx per component)
+    and of r (dr) can do to each term, to first order.  Every term is a product
+    of factors; with all of them in absolute value the sum over the pairs is
+    evaluated twice, at |x| and at |x| + dx with F and F'/r larger by the
+    relative change that dr makes (3 dr / (2h - r) and 2 dr / (2h - r) + dr / r),
+    r^2 + eps h^2 smaller by 2 r dr, and the viscosity of the pairs whose u.x is
+    within its own rounding of zero in the second sum only.  Returns the
+    differences for dL/do [n, 3], dL/du [n, 3], dL/drho [n]."""
+    p = sc.params
+    L = ob["lists"]
+    st = O.State.lift(ob["cell"], ob["pos"], ob["vel"], ob["info"])
+    n, h = st.n, O.f32(p.h)
+    period = sc.grid.ncell * sc.grid.cell_size.astype(np.float64)
+    per = np.array([(sc.grid.periodic >> d) & 1 for d in range(3)], bool)
+    ii, jj = [], []
+    for idx, cnt in ((L.fl, L.nf), (L.bl, L.nb)):
+        m = np.arange(idx.shape[1])[None, :] < cnt[:, None]
+        ii.append(np.nonzero(m)[0])
+        jj.append(idx[m])
+    i, j = np.concatenate(ii).astype(np.int64), np.concatenate(jj).astype(np.int64)
+    x_all = O.positions(sc.grid, st)
+    x = x_all[i] - x_all[j]
+    x = np.where(per, x - period * np.round(x / period), x)
+    r = np.sqrt((x * x).sum(1))
+    keep = r < 2.0 * h
+    i, j, x, r = i[keep], j[keep], x[keep], r[keep]
+    rho0, c0, eps = O.f32(p.rho0), O.f32(p.c0), O.f32(p.eps_visc) * h * h
+    B = rho0 * c0 * c0 / 7.0
+    b = st.rho / rho0
+    P, c = B * (b ** 7 - 1.0), c0 * b ** 3
+    pr, dpr = np.abs(P) / st.rho ** 2, np.abs(c * c / st.rho ** 2 - 2.0 * P / st.rho ** 3)
+    dc = 3.0 * c / st.rho
+    rs, cs = st.rho[i] + st.rho[j], c[i] + c[j]
+    ah = O.f32(p.alpha) * h
+    u = np.abs(st.vel[i] - st.vel[j])
+    w = ((st.vel[i] - st.vel[j]) * x).sum(1)
+    mi, mj = st.mass[i], st.mass[j]
+    da = np.abs(mj[:, None] * abar[i]) + np.abs(mi[:, None] * abar[j])
+    sd = np.abs(mj * dbar[i]) + np.abs(mi * dbar[j])
+    coef = 105.0 / (128.0 * np.pi * h ** 5)
+    t = 1.0 - r / (2.0 * h)
+    F, Fr = 8.0 * coef * t ** 3, 12.0 * coef * t * t / (h * r)
+    dx = SEP_ULPS * float(np.max(sc.grid.cell_size))
+    dr = np.sqrt(3.0) * dx + EPS_R * r
+    dw = u.sum(1) * dx
+
+    def sums(X, F, Fr, dd, act):
+        W, DA = (u * X).sum(1), (da * X).sum(1)
+        K = np.where(act, ah * cs / (rs * dd), 0.0)
+        S_ = pr[i] + pr[j] + K * W
+        o = (S_ * F)[:, None] * da + (DA * S_ * Fr + sd * W * Fr + 2.0 * DA * F * K * W / dd)[:, None] * X \
+            + (DA * F * K + sd * F)[:, None] * u
+        v = (F * K * DA + sd * F)[:, None] * X
+        q = F * DA * (dpr[i] + np.where(act, ah * W / dd * (dc[i] + cs / rs) / rs, 0.0))
+        add = lambda y: np.bincount(i, y, n)
+        return (np.stack([add(o[:, d]) for d in range(3)], 1), np.stack([add(v[:, d]) for d in range(3)], 1), add(q))
+
+    ax, dd = np.abs(x), r * r + eps
+    edge = dr / (2.0 * h - r)
+    low = sums(ax, F, Fr, dd, w < -dw)
+    high = sums(ax + dx, F * (1.0 + 3.0 * edge), Fr * (1.0 + 2.0 * edge + dr / r), dd - 2.0 * r * dr, w < dw)
+    return tuple(b_ - a_ for a_, b_ in zip(low, high))
+
+
 def check_forces(gpu_f, acc, drho, s_acc, s_drho, tol=FORCE_TOL, label="", exclude=None, allowance=None):
     """Returns the max normalised errors (acc, drho); asserts <= tol.
     exclude: optional mask of particles left out (see support_edge_rows).

@@ -384,3 +384,50 @@ def test_taped_blocks_match_recomputation():
         for a, b in zip(ref, val):
             assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), key
     log("taped and recomputed reverses agree bit for bit")
+
+
+@pytest.mark.parametrize("side,shape", [(1.1, (3, 2, 3)), (1.1, (3, 4, 3)), (1.3, (3, 3, 3)), (1.3, (3, 4, 3))],
+                         ids=["1.1-3x2x3", "1.1-3x4x3", "1.3-3x3x3", "1.3-3x4x3"])
+def test_forces_backward_parity_sparse(side, shape):
+    """Two particles a cell: a particle's few pairs may all be nearly
+    perpendicular to an axis or at the edge of the support, where the float32
+    rounding of the separation moves a term by more than 1e-5 of itself.  The
+    bar is the same, beyond what that rounding allows
+    (parity.adjoint_edge_allowance)."""
+    from parity import adjoint_edge_allowance
+    from paper_2207_11328_amd import abi
+    sc = S.random_cloud(n=int(7000 * side ** 3), box=(side, side, 0.8 * side), dp=0.02, seed=int(100 * side),
+                        boundary_frac=0.1, u_sigma=0.2, alpha=0.2)
+    log("case sparse n=%d shape=%s" % (sc.n, shape))
+    sim = make_sim(sc, max_neibs=48, brick=shape)
+    sim.build()
+    torch_sync()
+    ob = compare_build(sc, sim, max_neibs=48)
+    st = O.State.lift(ob["cell"], ob["pos"], ob["vel"], ob["info"])
+    rng = np.random.default_rng(7)
+    gf = np.zeros((sc.n, 4), np.float32)
+    gf[:, :3] = rng.normal(size=(sc.n, 3))
+    gf[:, 3] = rng.normal(size=sc.n) * 1e-3
+    ab, db = gf[:, :3].astype(np.float64), gf[:, 3].astype(np.float64)
+    adj, gp = O.forces_reverse(sc.grid, sc.params, st, ob["lists"], ab, db)
+    scl, sp = O.forces_reverse_scales(sc.grid, sc.params, st, ob["lists"], ab, db)
+    allow = adjoint_edge_allowance(sc, ob, ab, db)
+    gpos, gvel = torch.zeros_like(sim.pos), torch.zeros_like(sim.pos)
+    par = torch.zeros(3, dtype=torch.float64, device=sim.device)
+    ws = torch.zeros(abi.sph_forces_backward_workspace_bytes(sim.capacity, sim.n_cells), dtype=torch.uint8,
+                     device=sim.device)
+    for bricks in (True, False):
+        abi.sph_forces_backward(sim.g, sim.p, sim.parts, sim.neibs, sim.neib_count, sim.max_neibs,
+                                torch.from_numpy(gf).to(sim.device), gpos, gvel, par, False, ws, None,
+                                *sim.brick_args(bricks))
+        torch_sync()
+        p, v = gpos[: sc.n].cpu().numpy().astype(np.float64), gvel[: sc.n].cpu().numpy().astype(np.float64)
+        for name, got, ref, s, a in (("dL/do", p[:, :3], adj.go, scl.go, allow[0]),
+                                     ("dL/du", v[:, :3], adj.gu, scl.gu, allow[1]),
+                                     ("dL/drho", v[:, 3], adj.grho, scl.grho, allow[2])):
+            d, z = np.abs(got - ref), np.where(s > 0, s, 1.0)
+            log("sparse %s bricks=%s: max |d|/S %.2e, beyond the allowance %.2e, allowance %.1e of S in the median"
+                % (name, bricks, (d / z).max(), (np.maximum(d - a, 0.0) / z).max(), np.median(a / z)))
+            assert (d[s == 0] == 0).all() and (d - a <= ADJ_TOL * s).all(), name
+        g = par.cpu().numpy()
+        assert (np.abs(g - gp) <= ADJ_TOL * sp).all()
