@@ -20,8 +20,8 @@
 using namespace sph;
 
 // Device scratch of the allocation-free entry point sph_forces_noalloc: it
-// holds the workspace of sph_forces (equation-of-state terms, brick list and
-// counters, cell flags) for problems whose sph_forces_workspace_bytes is at
+// holds the workspace of sph_forces (equation-of-state terms and the item
+// counter) for problems whose sph_forces_workspace_bytes is at
 // most SPH_NOALLOC_SCRATCH_BYTES.  Each device the library runs on holds its
 // own copy from module load to the end of the process.  Host code never uses
 // this name as an address: the device address comes from

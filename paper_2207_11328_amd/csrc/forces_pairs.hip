@@ -264,10 +264,11 @@ __global__ __launch_bounds__(kThreads) void k_forces(int n, const float4 *__rest
 // their work items are twice as long, and the waves of a brick then wait 5.1
 // instead of 3.3 us for the last one (1.62M-particle dam break).
 //
-// What bounds the loop is VALU issue: 36 instructions per pair, the method's
-// own 31 (two of them at half rate) and 5 for slot, address and list end; LDS
-// is busy 60% of the time, and its bank conflicts (half of its accesses'
-// cycles) cost nothing measurable.
+// What bounds the loop is VALU issue (85% busy over the whole kernel at 1.62M
+// particles): 36 instructions per pair, the method's own 31 (two of them at half
+// rate) and 5 for slot, address and list end; the waves wait for LDS in 4% of
+// their cycles, and its bank conflicts (half of its accesses' cycles) cost
+// nothing measurable.
 #ifndef SPH_BRICK_RING
 #define SPH_BRICK_RING 2
 #endif
@@ -409,9 +410,10 @@ __device__ __forceinline__ void empty_lists(int n, const uint32_t *__restrict__ 
 //     prepares item k + 2;
 //   * a wave without a group writes its part of the table of item k + 1 and
 //     requests its share of that item's particles.
-// Per item on the 1.62M-particle dam break (full bricks, 6.1 items per CU,
-// times of the mean wave): 1.9 us to stage, 0.8 us at the barrier, 13.7 us of
-// pairs, 1.0 us for the next item, 3.3 us waiting for the last wave.
+// 1.62M-particle dam break, 5.9 items per CU: a full brick (800 to 972 centrals)
+// takes 3.0 us to the end of the barrier after its staging and 22.4 us from
+// there to its last wave, one of 100 to 300 centrals 1.7 and 6.4 us; the first
+// item starts 13 to 16 us into the kernel.
 template <int MODEL, int BX, int BY, int BZ, int NT, int NC, int CAP>
 __global__ __launch_bounds__(NT) void k_forces_brick(int n, const float4 *__restrict__ pos,
                                                      const float4 *__restrict__ vel,
@@ -680,7 +682,7 @@ bool sph::SPH_PAIRS_FN(SPH_KERNEL_KIND)(int model, const ForceArgs &a, const For
         if (a.bricks) {
             // cell ranges and brick-local lists of the last build: LDS cell-brick
             // kernel (it writes the derivatives of every particle, those with an
-            // empty list and those dropped by the build after its last brick)
+            // empty list and those dropped by the build while it prepares its first item)
             launch_brick<M>(a, C, s);
         } else {
             k_forces<M><<<sph_blocks(a.n, kThreads), kThreads, 0, s>>>(a.n, a.pos, a.vel, a.aux, a.neibs, a.count,

@@ -477,7 +477,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_place(int nb, int tiles
 // boundary neighbours interleaved as found (entries 0 .. nf+nb-1), stored in groups of 8 per
 // particle (brick_entry).
 //
-// Bound by VALU issue and the latencies between the steps: of the 545 us that
+// Bound by VALU issue and the latencies between the steps: of the 530 us that
 // the scan of the 1.62M-particle dam break takes (92 neighbours a particle, 0.9 GB of
 // lists), the vector ALU issues for 330; the lists alone would take 175 at the
 // rate of a large copy.  Taking away in turn the writing of the lists, the
@@ -866,7 +866,7 @@ __device__ __forceinline__ void scan_item(ScanTables<BX, BY, BZ, NW> &T, const S
     }
 }
 
-// Workgroups of 4 waves, four to a CU (128 VGPRs, 33 KB of LDS), so that the
+// Workgroups of 4 waves, four to a CU (127 VGPRs, 38 KB of LDS), so that the
 // ranges of one are read while the others scan.
 constexpr int kBuildThreads = 256, kBuildResident = 4;
 
